@@ -66,41 +66,68 @@ constexpr double DE1 = D71 - 5179.0 / 57600.0, DE3 = D73 - 7571.0 / 16695.0,
                  DE6 = D76 - 187.0 / 2100.0, DE7 = -1.0 / 40.0;
 
 // Both tableaux again as tables in constant memory.  An attempt reads its
-// coefficients through scalar_table(): a handful of wide scalar loads per
-// attempt instead of two 32-bit immediates per double, which also leaves the
+// coefficients from there: a handful of wide scalar loads per attempt instead of two 32-bit immediates per double, which also leaves the
 // scalar registers that the immediates took to the rest of the loop.
 struct CkTab {
   double a21, a31, a32, a41, a42, a43, a51, a52, a53, a54, a61, a62, a63, a64, a65;
   double b1, b3, b4, b6, e1, e3, e4, e5, e6;
 };
-__constant__ CkTab kCkTab = {A21, A31, A32, A41, A42, A43, A51, A52, A53, A54,
+constexpr CkTab kCkTab = {A21, A31, A32, A41, A42, A43, A51, A52, A53, A54,
                              A61, A62, A63, A64, A65, B1,  B3,  B4,  B6,  E1,
                              E3,  E4,  E5,  E6};
 struct DpTab {
   double a21, a31, a32, a41, a42, a43, a51, a52, a53, a54, a61, a62, a63, a64, a65;
   double b1, b3, b4, b5, b6, e1, e3, e4, e5, e6, e7;
 };
-__constant__ DpTab kDpTab = {D21, D31, D32, D41, D42, D43, D51, D52, D53, D54,
+constexpr DpTab kDpTab = {D21, D31, D32, D41, D42, D43, D51, D52, D53, D54,
                              D61, D62, D63, D64, D65, D71, D73, D74, D75, D76,
                              DE1, DE3, DE4, DE5, DE6, DE7};
 
-// A table in constant memory as the attempt sees it.  The pointer passes
-// through an empty asm in scalar registers, so the compiler cannot hoist the
-// loads out of the step loop (which would pin the values in scalar registers
-// for the whole loop and spill others); the constant address space lets it
-// use scalar loads.
+// The step-size controller's constants, next to the tableau.
+struct CtlTab {
+  double e_lo, e_hi, safety, f_lo, c12, c2;
+};
 template <class T>
-__device__ __forceinline__ const __attribute__((address_space(4))) T &scalar_table(const T &t) {
-  const T *p = &t;
-  asm volatile("" : "+s"(p));
-  return *(const __attribute__((address_space(4))) T *)p;
+struct alignas(64) StepTab {
+  T tab;
+  CtlTab ctl;
+};
+constexpr CtlTab kCtl = {1e-4, 4e3, 0.9, 0.2, 0.12, 0.2};
+
+// The tables of a scheme as an attempt sees them: the pointer (kept in scalar
+// registers for the whole kernel) passes through an empty asm, so the
+// compiler cannot hoist the loads out of the step loop (which would pin the
+// values in scalar registers for the whole loop and spill others); the
+// constant address space lets it use scalar loads.
+template <class T>
+using Tables = const __attribute__((address_space(4))) StepTab<T> *;
+template <class T>
+__device__ __forceinline__ Tables<T> fresh(Tables<T> &t) {
+  asm volatile("" : "+s"(t));
+  return t;
+}
+
+// Conditions of the wave's lanes as one scalar mask, and a mask as a lane's
+// condition.  The step logic works on masks: a condition that is combined or
+// kept as a lane's bool goes through vector registers (a select and a
+// compare) wherever it crosses a block.
+typedef unsigned long long Mask;
+__device__ __forceinline__ Mask ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+__device__ __forceinline__ bool in(Mask m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// n + 1 in the lanes of m, as one add with the mask as its carry.  m is the
+// result of scalar instructions, which a vector instruction may read at once.
+__device__ __forceinline__ uint32_t count(uint32_t n, Mask m) {
+  Mask carry;
+  asm("v_addc_co_u32 %0, %1, %2, 0, %3" : "=v"(n), "=s"(carry) : "v"(n), "s"(m));
+  return n;
 }
 
 // Occupancy floor per (model, scheme, located maxima): the seventh stage and
-// the carried k1 of Dormand--Prince, or Cash--Karp's end-point evaluations
-// for located maxima, cost one wave per SIMD.
+// the carried k1 of Dormand--Prince cost one wave per SIMD; Cash--Karp's
+// end-point evaluations for located maxima leave three (139 registers for the
+// single drive, 167 for the dual one).
 constexpr int min_waves(int base, int sc, bool loc) {
-  return (sc == kDP || loc) ? base - 1 : base;
+  return sc == kDP ? base - 1 : (loc && base > 3 ? 3 : base);
 }
 
 // 1/d from the hardware reciprocal estimate r (relative error e = 1 - d r
@@ -150,6 +177,11 @@ __device__ __forceinline__ double vmax(double a, double b) {
   asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
   return r;
 }
+__device__ __forceinline__ double vmin(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
 __device__ __forceinline__ double vmax_s(double a, double b) {     // b uniform
   double r;
   asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "s"(b));
@@ -177,51 +209,52 @@ __device__ __forceinline__ double rfifth_c(double x, double c12, double c2) {
 }
 __device__ __forceinline__ double rfifth(double x) { return rfifth_c(x, 0.12, 0.2); }
 
-// The step-size controller's constants as a table in constant memory, read
-// with one scalar load per attempt (scalar_table).  The valve's step takes
-// them from there (its scalar registers are short, and the compiler would
-// rebuild each double from two 32-bit immediates in every attempt); the
-// Keller--Miksis steps keep them as immediates, which its kernel holds.
-struct CtlTab {
-  double e_lo, e_hi, safety, f_lo, f_hi, c12, c2;
+__constant__ StepTab<CkTab> kCkTabs = {kCkTab, kCtl};
+__constant__ StepTab<DpTab> kDpTabs = {kDpTab, kCtl};
+template <int SC>
+struct Scheme {
+  typedef CkTab Tab;
+  __device__ static Tables<Tab> tables() { return (Tables<Tab>)&kCkTabs; }
 };
-__constant__ CtlTab kCtlTab = {1e-4, 4e3, 0.9, 0.2, 5.0, 0.12, 0.2};
-constexpr CtlTab kCtlImm = {1e-4, 4e3, 0.9, 0.2, 5.0, 0.12, 0.2};
+template <>
+struct Scheme<kDP> {
+  typedef DpTab Tab;
+  __device__ static Tables<Tab> tables() { return (Tables<Tab>)&kDpTabs; }
+};
 
-// Step-size factor 0.9 E^(-1/5), clamped to [0.2, 5] (E = 0 gives 5), for a
-// finite E >= 0.  The root is taken of E limited to [1e-4, 4e3], where FP32
-// holds it: below, 0.9 (1e-4)^(-1/5) = 5.68 clamps to 5, and above,
-// 0.9 (4e3)^(-1/5) = 0.171 clamps to 0.2, the factors of the unlimited E.
+// Step-size factor 0.9 E^(-1/5) for a finite E >= 0, clamped to [0.2, 5]
+// (E = 0 gives 5) after an accepted step and to [0.2, 1] after a rejected
+// one (a step only shrinks after a rejection): the upper bound is the one
+// select, of the high words of 5.0 and 1.0.  The root is taken of E limited
+// to [1e-4, 4e3], where FP32 holds it: below, 0.9 (1e-4)^(-1/5) = 5.68 clamps
+// to 5, and above, 0.9 (4e3)^(-1/5) = 0.171 clamps to 0.2, the factors of the
+// unlimited E.
 template <class T>
-__device__ __forceinline__ double step_factor_with(const T &c, double E) {
+__device__ __forceinline__ double step_factor(const T &c, double E, bool grow) {
   const double f = c.safety * rfifth_c(vmin_s(vmax_s(E, c.e_lo), c.e_hi), c.c12, c.c2);
-  return vmin_s(vmax_s(f, c.f_lo), c.f_hi);
-}
-template <bool TABLE>
-__device__ __forceinline__ double step_factor(double E) {
-  if constexpr (TABLE)
-    return step_factor_with(scalar_table(kCtlTab), E);
-  else
-    return step_factor_with(kCtlImm, E);
+  return vmin(vmax_s(f, c.f_lo), grow ? 5.0 : 1.0);
 }
 
 // Scaled error of an attempt, E = max_c |err_c| / (rtol max(|y_c|, |y5_c|) +
-// atol), and whether every new component and ratio is finite: 0 v is 0 for a
-// finite v and NaN otherwise, so one compare of the sum of those products
-// decides.
+// atol), and the lanes where a ratio is not finite: 0 r is 0 for a finite r and NaN
+// otherwise, so one compare of the sum of those products decides.  The new
+// components need no test of their own: an infinite y5_c makes the scale
+// infinite and its reciprocal's correction, and so the ratio, NaN; a NaN y5_c
+// comes from a NaN state or slope, which the error estimate holds too (it
+// weighs every slope that y5 does, and every right-hand side passes a NaN
+// component on to its own or another slope).
 template <int D>
-__device__ __forceinline__ bool error_ratio(double rtol, double atol, const double *y,
+__device__ __forceinline__ Mask error_ratio(double rtol, double atol, const double *y,
                                             const double *y5, const double *err, double &E) {
-  double z = 0.0;
+  double z;
 #pragma unroll
   for (int c = 0; c < D; ++c) {
     const double sc = fma(rtol, vmax_abs(y[c], y5[c]), atol);
     const double r = fabs(err[c]) * rcp_nr(sc);
-    z = fma(0.0, y5[c], z);
-    z = fma(0.0, r, z);
+    z = c == 0 ? 0.0 * r : fma(0.0, r, z);
     E = c == 0 ? r : vmax(E, r);
   }
-  return z == 0.0;
+  return ballot(!(z == 0.0));
 }
 
 // ------------------------------------------------------------------ models
@@ -322,16 +355,22 @@ __device__ __forceinline__ void sincos_taylor(double x, double *s, double *c) {
   *c = fma(-pc, x2, 1.0);
 }
 
-// sin(pi x) and cos(pi x), |x| < 2^50: x minus the nearest multiple of 1/2
+// sin(pi x) and cos(pi x), |x| < 2^50: x minus the nearest multiple q / 2
 // (exact) leaves |r| <= 1/4; pi r is formed as a rounded product plus its
 // error (FMA) and the error of pi's double, the series above gives sin and
 // cos of the rounded part, a first-order term adds the rest, and the quarter
-// turns swap and negate.  Within an ulp of the correctly rounded values;
-// about half the instructions of the general library routine, which
-// reduces any argument.
+// turns q swap and negate.  q is the integer that 2 x + 1.5 2^52 rounds to
+// (half to even, like rint), whose low word then holds q modulo 2^32: one
+// addition gives q, the subtraction of 1.5 2^52 its value as a double, and
+// the signs are its bits shifted to the sign place.  Within an ulp of the
+// correctly rounded values; about half the instructions of the general
+// library routine, which reduces any argument.
 __device__ __forceinline__ void sincospi_quarter(double x, double *s, double *c) {
   constexpr double kPiLo = 1.2246467991473532e-16;  // pi - (double)pi
-  const double q = rint(2.0 * x);
+  constexpr double kRound = 6755399441055744.0;     // 1.5 2^52
+  const double u = fma(2.0, x, kRound);
+  const unsigned k = (unsigned)__double2loint(u);
+  const double q = u - kRound;
   const double r = fma(q, -0.5, x);
   const double t = M_PI * r;
   const double tl = fma(M_PI, r, -t) + kPiLo * r;
@@ -340,11 +379,12 @@ __device__ __forceinline__ void sincospi_quarter(double x, double *s, double *c)
   const double sr1 = fma(tl, cr, sr), cr1 = fma(-tl, sr, cr);
   sr = sr1;
   cr = cr1;
-  const int k = (int)(q - 4.0 * floor(0.25 * q));  // quarter turns modulo 4 (exact)
   const double ss = (k & 1) ? cr : sr;
   const double cc = (k & 1) ? sr : cr;
-  *s = (k & 2) ? -ss : ss;            // k = 2, 3
-  *c = ((k + 1) & 2) ? -cc : cc;      // k = 1, 2
+  // sin < 0 for k = 2, 3, cos < 0 for k = 1, 2 (modulo 4)
+  const unsigned ns = (k << 30) & 0x80000000u, nc = ((k + 1) << 30) & 0x80000000u;
+  *s = __hiloint2double((int)((unsigned)__double2hiint(ss) ^ ns), __double2loint(ss));
+  *c = __hiloint2double((int)((unsigned)__double2hiint(cc) ^ nc), __double2loint(cc));
 }
 
 // Dimensionless Keller--Miksis equation (Sec. 4.2), single-frequency drive.
@@ -616,7 +656,7 @@ struct MKM {
 struct MPRV {
   static constexpr int D = 3;
   static constexpr bool kEvents = true;
-  static constexpr int kMinWaves = 5;
+  static constexpr int kMinWaves = 4;
   static constexpr bool kPrio = false;  // issue priority by remaining work
   static constexpr bool kLocate = false;
   static constexpr bool kDrive2 = false;
@@ -624,36 +664,37 @@ struct MPRV {
   static constexpr bool kTangent = false;
   static constexpr int kNCoef = 0;  // no precomputed coefficients
   double q, kappa, delta, beta, r;
-  bool seated;
+  double flight;   // 1, or 0 while seated
+  __device__ bool seated() const { return flight == 0.0; }
   __device__ void init(const double *P, int64_t n, int64_t i, const double *sh) {
     q = P[i];
     kappa = sh[0];
     delta = sh[1];
     beta = sh[2];
     r = sh[3];
-    seated = false;
+    flight = 1.0;
   }
   __device__ void begin(double) {}
-  template <int SC, int S>
   // Seated, the body rests with y1 = y2 = +0 (the seating sets both and
   // every stage keeps them), so the free-flight expressions give dy1/dt = 0
-  // and dy3/dt = beta q exactly; only the acceleration is held at 0.  No
-  // branch: the attempt stays one basic block.
+  // and dy3/dt = beta q exactly; only the acceleration is held at 0, by the
+  // factor `flight` (a zero of either sign leaves y2 = +0).
+  template <int SC, int S>
   __device__ void rhs(double, double, const double *y, double *f) const {
     const double acc = fma(-kappa, y[1], y[2] - (y[0] + delta));
     f[0] = y[1];
-    f[1] = seated ? 0.0 : acc;
+    f[1] = flight * acc;
     f[2] = beta * fma(-y[0], sqrt_nr(y[2]), q);
   }
 };
 
 // One attempted Cash--Karp step: y5 and err = h sum (b5 - b4) k.
 template <class M>
-__device__ __forceinline__ void ck_attempt(M &m, double t, const double *y, double h,
-                                           double *y5, double *err) {
+__device__ __forceinline__ void ck_attempt(M &m, Tables<CkTab> tabs, double t, const double *y,
+                                           double h, double *y5, double *err) {
   constexpr int D = M::D;
   double k1[D], k2[D], k3[D], k4[D], k5[D], k6[D], yt[D];
-  const auto &T = scalar_table(kCkTab);
+  const auto &T = tabs->tab;
   m.begin(t);
   m.template rhs<kCK, 1>(t, h, y, k1);
 #pragma unroll
@@ -682,19 +723,36 @@ __device__ __forceinline__ void ck_attempt(M &m, double t, const double *y, doub
   }
 }
 
+// Dormand--Prince: k1 = f(t, y) of the next attempt, valid when `have` (0 or
+// 1).  An attempt leaves its k1 here (a rejected step retries from the same
+// point); an accepted one replaces it by its k7 (first same as last); a phase
+// end, an impact or a lift-off clears it, so that every phase starts by
+// evaluating k1.
+template <int D>
+struct Fsal {
+  double k[D];
+  uint32_t have;
+};
+
 // One attempted Dormand--Prince step from (t, y): k1 = f(t, y) is taken from
-// kf when have_k1 (first same as last), else evaluated and left in kf; k7
-// receives f(t + h, y5).  Returns the number of RHS evaluations.
+// fs where it has it, else evaluated (counted in nrhs) and left there; k7
+// receives f(t + h, y5).
 template <class M>
-__device__ __forceinline__ int dp_attempt(M &m, double t, const double *y, double h,
-                                          double *kf, bool have_k1, double *y5, double *err,
-                                          double *k7) {
+__device__ __forceinline__ void dp_attempt(M &m, Tables<DpTab> tabs, double t, const double *y,
+                                           double h, Fsal<M::D> &fs, uint32_t &nrhs, double *y5,
+                                           double *err, double *k7) {
   constexpr int D = M::D;
   double k2[D], k3[D], k4[D], k5[D], k6[D], yt[D];
-  const auto &T = scalar_table(kDpTab);
+  const auto &T = tabs->tab;
   m.begin(t);
-  if (!have_k1) m.template rhs<kDP, 1>(t, h, y, kf);
-  const double *k1 = kf;
+  if (__builtin_expect(ballot(fs.have == 0) != 0, 0)) {
+    if (fs.have == 0) {
+      m.template rhs<kDP, 1>(t, h, y, fs.k);
+      nrhs++;
+      fs.have = 1;
+    }
+  }
+  const double *k1 = fs.k;
 #pragma unroll
   for (int c = 0; c < D; ++c) yt[c] = fma(h, T.a21 * k1[c], y[c]);
   m.template rhs<kDP, 2>(fma(DC2, h, t), h, yt, k2);
@@ -723,7 +781,6 @@ __device__ __forceinline__ int dp_attempt(M &m, double t, const double *y, doubl
   for (int c = 0; c < D; ++c)
     err[c] = h * fma(T.e7, k7[c], fma(T.e6, k6[c], fma(T.e5, k5[c], fma(T.e4, k4[c],
                                                       fma(T.e3, k3[c], T.e1 * k1[c])))));
-  return have_k1 ? 6 : 7;
 }
 
 // x limited to [lo, hi] for a finite x and lo <= hi (the host checks
@@ -744,7 +801,10 @@ struct MTan : M {
   static_assert(!M::kEvents, "the tangent is built for fixed-length phases");
   static_assert(K >= 1 && K <= M::D, "1 .. D tangents");
   static constexpr int D = M::D * (1 + K);
-  static constexpr int kMinWaves = M::kMinWaves > K + 1 ? M::kMinWaves - K : 2;
+  // (the one-dimensional model's lanes finish after few attempts: its waves wait
+  // on refills, which six of them hide better than five)
+  static constexpr int kMinWaves =
+      M::D == 1 ? 6 : (M::kMinWaves > K + 1 ? M::kMinWaves - K : 2);
   static constexpr bool kLocate = false;
   static constexpr int kF = 1 + K;       // (y1max, log growth of each tangent)
   static constexpr bool kTangent = true;
@@ -785,23 +845,16 @@ struct MTan : M {
 struct Lane {
   int64_t sys;
   double t, h, t_ps, ymax, ymin;
+  double t_late;       // valve: no time before it is t_cap after t_ps
   int64_t n_phases, max_impacts;
-  uint32_t phase, accepted, rejected, evretry, impacts, attempts;
+  // every attempt is one of accepted, rejected, event retry, or the system's
+  // last (a non-finite one): the rejected ones are the difference
+  uint32_t phase, accepted, evretry, impacts, attempts;
   uint32_t phase_att;  // attempts when the current phase began
   float rem;           // estimated attempts left: last phase's x phases left
-  uint32_t nrhs;       // Dormand--Prince: RHS evaluations (6 or 7 per attempt)
+  uint32_t nrhs;       // RHS evaluations beyond 6 per attempt
   int32_t status, ev_iter;
   bool head;           // taken from the spread head of the queue
-};
-
-// Dormand--Prince: k1 = f(t, y) of the next attempt, valid when `have`.  An
-// attempt leaves its k1 here (a rejected step retries from the same point);
-// an accepted one replaces it by its k7 (first same as last); a phase end, an
-// impact or a lift-off clears it, so that every phase starts by evaluating k1.
-template <int D>
-struct Fsal {
-  double k[D];
-  bool have;
 };
 
 // Estimated work left after a completed phase.
@@ -861,12 +914,16 @@ __device__ __forceinline__ void store_lane(const RkckArgs &a, const Lane &L, con
   for (int c = 0; c < D; ++c) cp->y[c * n + i] = y[c];
   cp->t[i] = L.t;
   cp->h[i] = L.h;
-  const int64_t att = (int64_t)L.accepted + L.rejected + L.evretry;
+  const uint32_t bad = (L.status & ENS_SYS_NONFINITE) ? 1u : 0u;
+  const uint32_t rejected = L.attempts - L.accepted - L.evretry - bad;
+  const int64_t att = (int64_t)L.accepted + rejected + L.evretry;
   int64_t *stats = cp->stats;
   stats[ENS_ST_ACCEPTED * n + i] = L.accepted;
-  stats[ENS_ST_REJECTED * n + i] = L.rejected;
-  // Cash--Karp: 6 per attempt plus the evaluations of located maxima
-  stats[ENS_ST_NRHS * n + i] = SC == kDP ? (int64_t)L.nrhs : 6 * att + (int64_t)L.nrhs;
+  stats[ENS_ST_REJECTED * n + i] = rejected;
+  // 6 per attempt (Dormand--Prince counts a non-finite one, too), plus
+  // Cash--Karp's evaluations for located maxima, or Dormand--Prince's first
+  // stages that no earlier attempt had left
+  stats[ENS_ST_NRHS * n + i] = 6 * (att + (SC == kDP ? bad : 0u)) + (int64_t)L.nrhs;
   stats[ENS_ST_IMPACTS * n + i] = L.impacts;
   stats[ENS_ST_PHASES * n + i] = L.phase;
   stats[ENS_ST_EVRETRY * n + i] = L.evretry;
@@ -882,7 +939,7 @@ __device__ __forceinline__ void store_lane(const RkckArgs &a, const Lane &L, con
 template <class M>
 __device__ __forceinline__ bool seated_of(const M &m) {
   if constexpr (M::kEvents)
-    return m.seated;
+    return m.seated();
   else
     return false;
 }
@@ -913,40 +970,57 @@ __device__ __noinline__ double located_max(const double *y0, const double *y1, c
   return hermite<D>(y0, y1, f0, f1, h, 0, 0.5 * (lo + hi));
 }
 
-// One attempted step of a fixed-length-phase model; returns true when the
-// system is finished.
+// How an attempt's outcome is split.  What every attempt does, the attempt
+// itself, the step-size factor and the update of an accepted step, is one
+// straight run of instructions.  Everything that few attempts need (a phase's
+// end, an event, a seat change, a non-finite state, the step-size floor, the
+// step cap, settling) is a `rare` outcome, and one wave-uniform test skips the
+// code of all of them together.  A wave that issues alone on its SIMD, as the
+// longest systems' waves do at the end of a sweep, takes 5 cycles for each
+// instruction of any kind, about 11 for a branch that is not taken and 25 for
+// one that is, so the instructions and branches on the common path are the
+// sweep's time.
+struct Outcome {
+  Mask rare;             // the lanes that need settle_*()
+  Mask bad;              // not finite
+  Mask floor;            // over the error bound at the step-size floor
+  Mask end;              // fixed-length phases: accepted, truncated at the phase end
+  Mask special;          // valve: rare for another reason than the step cap
+  double h_try, h_keep;  // the attempted step; the step size before it
+};
+
+// The lanes whose attempts reach the step cap (max_steps < 2^32; without a
+// cap, 2^32 - 1 attempts, which settle_*() then lets pass).
+__device__ __forceinline__ Mask at_cap(const RkckArgs &a, const Lane &L) {
+  return ballot(L.attempts >= (a.max_steps > 0 ? (uint32_t)a.max_steps : UINT32_MAX));
+}
+
+// One attempted step of a fixed-length-phase model, without its rare outcomes.
 template <class M, int SC, bool LOC>
-__device__ __forceinline__ bool step_fixed(const RkckArgs &a, M &m, Lane &L, double *y,
-                                           Fsal<M::D> &fs) {
+__device__ __forceinline__ void step_fixed(const RkckArgs &a,
+                                           Tables<typename Scheme<SC>::Tab> tabs, M &m, Lane &L,
+                                           double *y, Fsal<M::D> &fs, Outcome &o) {
   constexpr int D = M::D;
   double y5[D], err[D], k7[D];
   double h_try = L.h;
-  const bool trunc = L.t + h_try >= a.t_phase;
-  if (trunc) h_try = a.t_phase - L.t;
-  if constexpr (SC == kDP) {
-    L.nrhs += dp_attempt(m, L.t, y, h_try, fs.k, fs.have, y5, err, k7);
-    fs.have = true;
-  } else {
-    ck_attempt(m, L.t, y, h_try, y5, err);
-  }
+  const Mask trunc = ballot(L.t + h_try >= a.t_phase);
+  h_try = in(trunc) ? a.t_phase - L.t : h_try;
   L.attempts++;
+  const Mask cap = at_cap(a, L);
+  if constexpr (SC == kDP)
+    dp_attempt(m, tabs, L.t, y, h_try, fs, L.nrhs, y5, err, k7);
+  else
+    ck_attempt(m, tabs, L.t, y, h_try, y5, err);
   double E;
-  const bool finite = error_ratio<D>(a.rtol, a.atol, y, y5, err, E);
-  if (!finite) {
-    L.status |= ENS_SYS_NONFINITE;
-    return true;
-  }
-  const double fac = step_factor<false>(E);
-  // Accept (E <= 1, or at the step-size floor) or reject, by selects: only
-  // the rare phase end and located maximum branch.  After a rejection the
-  // step only shrinks.
-  const bool acc = !(E > 1.0 && h_try > a.dt_min);
-  const double h_new = clampd(h_try * (acc ? fac : fmin(fac, 1.0)), a.dt_min, a.dt_max);
-  L.status |= (acc && E > 1.0) ? ENS_SYS_DT_MIN : 0;
-  L.accepted += acc ? 1 : 0;
-  L.rejected += acc ? 0 : 1;
+  o.bad = error_ratio<D>(a.rtol, a.atol, y, y5, err, E);
+  // Accept (E <= 1, or at the step-size floor) or reject, by selects.
+  const Mask over = ballot(E > 1.0), rej = over & ballot(h_try > a.dt_min);
+  const Mask acc = ~(rej | o.bad);
+  const double fac = step_factor(kCtl, E, in(acc));
+  const double h_new = clampd(h_try * fac, a.dt_min, a.dt_max);
+  L.accepted = count(L.accepted, acc);
   if constexpr (LOC) {
-    if (acc && y[1] > 0.0 && y5[1] <= 0.0) {
+    if (in(acc) && y[1] > 0.0 && y5[1] <= 0.0) {
       // the maximum of y1 between the step points, on the interpolant
       // (Dormand--Prince has f at both ends; Cash--Karp evaluates them)
       double f0[D], f1[D];
@@ -968,16 +1042,35 @@ __device__ __forceinline__ bool step_fixed(const RkckArgs &a, M &m, Lane &L, dou
     }
   }
 #pragma unroll
-  for (int c = 0; c < D; ++c) y[c] = acc ? y5[c] : y[c];
+  for (int c = 0; c < D; ++c) y[c] = in(acc) ? y5[c] : y[c];
   if constexpr (SC == kDP) {
 #pragma unroll
-    for (int c = 0; c < D; ++c) fs.k[c] = acc ? k7[c] : fs.k[c];
+    for (int c = 0; c < D; ++c) fs.k[c] = in(acc) ? k7[c] : fs.k[c];
   }
-  L.ymax = (acc && y[0] > L.ymax) ? y[0] : L.ymax;
-  if (acc && trunc) {
+  L.ymax = in(acc & ballot(y5[0] > L.ymax)) ? y5[0] : L.ymax;
+  L.t += in(acc) ? h_try : 0.0;
+  o.h_keep = L.h;
+  L.h = h_new;
+  o.floor = over & acc;
+  o.end = trunc & acc;
+  o.rare = o.bad | ((o.end | o.floor | cap) & ballot(true));
+}
+
+// The rare outcomes of that attempt; returns true when the system is finished.
+template <class M>
+__device__ __forceinline__ bool settle_fixed(const RkckArgs &a, M &m, Lane &L, double *y,
+                                             Fsal<M::D> &fs, const Outcome &o) {
+  if (in(o.bad)) {
+    L.h = o.h_keep;
+    L.status |= ENS_SYS_NONFINITE;
+    return true;
+  }
+  L.status |= in(o.floor) ? ENS_SYS_DT_MIN : 0;
+  if (in(o.end)) {
     // phase end: the next phase starts with the step proposed before the
-    // truncation (L.h is left as it was)
-    fs.have = false;
+    // truncation
+    L.h = o.h_keep;
+    fs.have = 0;
     if constexpr (M::kTangent) {
       double g[M::kK];
       m.renormalise(y, g);
@@ -993,9 +1086,6 @@ __device__ __forceinline__ bool step_fixed(const RkckArgs &a, M &m, Lane &L, dou
     L.t_ps = 0.0;
     L.ymax = -INFINITY;
     if (L.phase >= L.n_phases) return true;
-  } else {
-    L.t += acc ? h_try : 0.0;
-    L.h = h_new;
   }
   if (a.max_steps > 0 && L.attempts >= a.max_steps) {
     L.status |= ENS_SYS_MAX_STEPS;
@@ -1004,116 +1094,144 @@ __device__ __forceinline__ bool step_fixed(const RkckArgs &a, M &m, Lane &L, dou
   return false;
 }
 
-// One attempted step of the relief valve with events; true when finished.
+// Before t_late no time t has t - t_ps >= t_cap: any such t is at least
+// t_ps + t_cap (1 - 2^-53), and the rounding of a smaller sum cannot pass it.
+// Every attempt of a seated system counts as late (its lift-off is an event).
+__device__ __forceinline__ void note_late(const RkckArgs &a, const MPRV &m, Lane &L) {
+  L.t_late = m.seated() ? -INFINITY : fma(a.t_cap, 1.0 - 0x1p-40, L.t_ps);
+}
+
+// One attempted step of the relief valve, without its rare outcomes: events
+// (an impact, a local maximum or a lift-off that the step reached or passed),
+// seated systems, and the cap of a phase's length.  A lane with such an
+// outcome leaves its state as it was (its new state stays in y5, k7).
 template <int SC>
-__device__ __forceinline__ bool step_valve(const RkckArgs &a, MPRV &m, Lane &L, double *y,
-                                           Fsal<3> &fs) {
+__device__ __forceinline__ void step_valve(const RkckArgs &a,
+                                           Tables<typename Scheme<SC>::Tab> tabs, MPRV &m,
+                                           Lane &L, double *y, Fsal<3> &fs, Outcome &o,
+                                           double *y5, double *k7) {
   constexpr int D = 3;
-  double y5[D], err[D], k7[D];
+  double err[D];
   const double h_try = L.h;
-  if constexpr (SC == kDP) {
-    L.nrhs += dp_attempt(m, L.t, y, h_try, fs.k, fs.have, y5, err, k7);
-    fs.have = true;
-  } else {
-    ck_attempt(m, L.t, y, h_try, y5, err);
-  }
   L.attempts++;
+  const Mask cap = at_cap(a, L);
+  if constexpr (SC == kDP)
+    dp_attempt(m, tabs, L.t, y, h_try, fs, L.nrhs, y5, err, k7);
+  else
+    ck_attempt(m, tabs, L.t, y, h_try, y5, err);
   double E;
-  const bool finite = error_ratio<D>(a.rtol, a.atol, y, y5, err, E);
-  if (!finite) {
+  o.bad = error_ratio<D>(a.rtol, a.atol, y, y5, err, E);
+  const Mask over = ballot(E > 1.0), rej = over & ballot(h_try > a.dt_min);
+  o.h_try = h_try;
+  o.h_keep = L.h;
+  L.h = clampd(h_try * step_factor(tabs->ctl, E, !in(rej)), a.dt_min, a.dt_max);
+  const double t_new = L.t + h_try;
+  const Mask cross = ballot(y5[0] <= 0.0) | (ballot(y[1] > 0.0) & ballot(y5[1] <= 0.0));
+  o.floor = over & ~rej;
+  o.special = ((over | cross | ballot(t_new >= L.t_late)) & ~rej) | o.bad;
+  if (in(~(rej | o.special))) {
+    L.accepted++;
+    L.ev_iter = 0;
+#pragma unroll
+    for (int c = 0; c < D; ++c) y[c] = y5[c];
+    if constexpr (SC == kDP) {
+#pragma unroll
+      for (int c = 0; c < D; ++c) fs.k[c] = k7[c];
+    }
+    L.t = t_new;
+    L.ymax = vmax(L.ymax, y5[0]);
+    L.ymin = vmin(L.ymin, y5[0]);
+  }
+  o.rare = (o.special | cap) & ballot(true);
+}
+
+// The rare outcomes of that attempt; returns true when the system is finished.
+template <int SC>
+__device__ __forceinline__ bool settle_valve(const RkckArgs &a, MPRV &m, Lane &L, double *y,
+                                             Fsal<3> &fs, const Outcome &o, const double *y5,
+                                             const double *k7) {
+  constexpr int D = 3;
+  if (in(o.bad)) {
+    L.h = o.h_keep;
     L.status |= ENS_SYS_NONFINITE;
     return true;
   }
-  const double fac = step_factor<true>(E);
-  // The common outcomes (rejection, event retry, plain acceptance) by
-  // selects; only the rare ones branch: an event's secant step, a seat
-  // change or impact, a Poincare point, settling.
-  const bool rej = E > 1.0 && h_try > a.dt_min;
-  // after a rejection the step only shrinks
-  const double h_next = clampd(h_try * (rej ? fmin(fac, 1.0) : fac), a.dt_min, a.dt_max);
-  const double tol = a.event_tol;
-  // event detection: overshoot -> secant retry from the same point.  The
-  // tests are plain compares; the secant steps (divisions) are formed only
-  // when one of them fired, which few steps do.
-  const double g3o = y[2] - m.delta, g3n = y5[2] - m.delta;  // lift-off
-  const bool free = !m.seated;
-  // y1 crossing below the seat: an impact (y1 > 0 before), or a rebound
-  // swallowed by one step (y1 = 0 before)
-  const bool ev_y1 = free && y[0] >= 0.0 && y5[0] < -tol;
-  const bool ev_max = free && y[1] > 0.0 && y5[1] < -tol;   // local maximum, y2 decreasing
-  const bool ev_lift = !free && g3o < 0.0 && g3n > tol;
-  const bool over = !rej && (ev_y1 || ev_max || ev_lift);
-  double hs = INFINITY;
-  if (over) {
-    if (ev_y1) hs = fmin(hs, y[0] > 0.0 ? h_try * y[0] / (y[0] - y5[0]) : 0.5 * h_try);
-    if (ev_max) hs = fmin(hs, h_try * y[1] / (y[1] - y5[1]));
-    if (ev_lift) hs = fmin(hs, h_try * (-g3o) / (g3n - g3o));
-  }
-  const bool retry = over && L.ev_iter < a.max_event_iter;
-  const bool take = !rej && !retry;   // the step is accepted
-  L.rejected += rej ? 1 : 0;
-  L.evretry += retry ? 1 : 0;
-  L.accepted += take ? 1 : 0;
-  L.status |= (!rej && E > 1.0) ? ENS_SYS_DT_MIN : 0;   // at the step-size floor
-  L.status |= (take && over) ? ENS_SYS_EVENT_ITER : 0;  // secant retries exhausted
-  L.ev_iter = retry ? L.ev_iter + 1 : (take ? 0 : L.ev_iter);
-  L.h = retry ? hs : h_next;
-  const double y2o = y[1];
-#pragma unroll
-  for (int c = 0; c < D; ++c) y[c] = take ? y5[c] : y[c];
-  if constexpr (SC == kDP) {
-#pragma unroll
-    for (int c = 0; c < D; ++c) fs.k[c] = take ? k7[c] : fs.k[c];
-  }
-  L.t += take ? h_try : 0.0;
-  // an accepted step may lift the body off its seat, or end in a located
-  // impact (Newtonian restitution, Sec. 4.3), or at a located local maximum
-  // of the free flight (the Poincare point)
-  const bool lift = take && !free && y[2] - m.delta >= 0.0;
-  const bool impact = take && free && y[0] <= 0.0 && y[1] < 0.0;
-  const bool pmax = take && free && !impact && y2o > 0.0 && y[1] <= 0.0;
   bool done = false;
-  // The rare outcomes (a seat change or impact, a Poincare point, settling)
-  // behind one wave-uniform test: most attempts of most waves have none, and
-  // then skip their exec-mask bookkeeping altogether.
-  const bool cap = take && L.t - L.t_ps >= a.t_cap;
-  if (__ballot(lift || impact || pmax || cap) == 0ull) {
-    L.ymax = take ? fmax(L.ymax, y[0]) : L.ymax;
-    L.ymin = take ? fmin(L.ymin, y[0]) : L.ymin;
-  } else {
-    if (lift || impact) {
-      fs.have = false;
+  if (in(o.special)) {   // otherwise step_valve did all but the step cap
+    const double tol = a.event_tol;
+    // event detection: overshoot -> secant retry from the same point
+    const double g3o = y[2] - m.delta, g3n = y5[2] - m.delta;  // lift-off
+    const bool free = !m.seated();
+    // y1 crossing below the seat: an impact (y1 > 0 before), or a rebound
+    // swallowed by one step (y1 = 0 before)
+    const bool ev_y1 = free && y[0] >= 0.0 && y5[0] < -tol;
+    const bool ev_max = free && y[1] > 0.0 && y5[1] < -tol;   // local maximum, y2 decreasing
+    const bool ev_lift = !free && g3o < 0.0 && g3n > tol;
+    const bool over = ev_y1 || ev_max || ev_lift;
+    const bool retry = over && L.ev_iter < a.max_event_iter;
+    L.status |= in(o.floor) ? ENS_SYS_DT_MIN : 0;
+    if (retry) {
+      double hs = INFINITY;
+      if (ev_y1) hs = fmin(hs, y[0] > 0.0 ? o.h_try * y[0] / (y[0] - y5[0]) : 0.5 * o.h_try);
+      if (ev_max) hs = fmin(hs, o.h_try * y[1] / (y[1] - y5[1]));
+      if (ev_lift) hs = fmin(hs, o.h_try * (-g3o) / (g3n - g3o));
+      L.evretry++;
+      L.ev_iter++;
+      L.h = hs;
+    } else {
+      // the step is accepted: it may lift the body off its seat, or end in a
+      // located impact (Newtonian restitution, Sec. 4.3), or at a located
+      // local maximum of the free flight (the Poincare point)
+      L.status |= over ? ENS_SYS_EVENT_ITER : 0;  // secant retries exhausted
+      L.accepted++;
+      L.ev_iter = 0;
+      const double y2o = y[1];
+#pragma unroll
+      for (int c = 0; c < D; ++c) y[c] = y5[c];
+      if constexpr (SC == kDP) {
+#pragma unroll
+        for (int c = 0; c < D; ++c) fs.k[c] = k7[c];
+      }
+      L.t += o.h_try;
+      const bool lift = !free && y[2] - m.delta >= 0.0;
+      const bool impact = free && y[0] <= 0.0 && y[1] < 0.0;
+      const bool pmax = free && !impact && y2o > 0.0 && y[1] <= 0.0;
       if (lift) {
-        m.seated = false;
-      } else {
+        fs.have = 0;
+        m.flight = 1.0;
+        note_late(a, m, L);
+      } else if (impact) {
+        fs.have = 0;
         const double v_in = y[1];
         y[0] = 0.0;
         y[1] = -m.r * v_in;
         L.impacts++;
         if (fabs(v_in) < a.v_stick && y[2] < m.delta) {
-          m.seated = true;
+          m.flight = 0.0;
+          note_late(a, m, L);
           y[1] = 0.0;
           L.status |= ENS_SYS_SEATED;
         }
         if (L.max_impacts > 0 && (int64_t)L.impacts >= L.max_impacts) done = true;
       }
-    }
-    L.ymax = take ? fmax(L.ymax, y[0]) : L.ymax;
-    L.ymin = take ? fmin(L.ymin, y[0]) : L.ymin;
-    if (pmax) {
-      fs.have = false;
-      store_record<MPRV>(a, L, y[0], L.ymin);
-      L.phase++;
-      if constexpr (MPRV::kPrio) note_phase_end(L);
-      L.ymax = -INFINITY;
-      L.ymin = INFINITY;
-      L.t_ps = L.t;
-      if (L.phase >= L.n_phases) done = true;
-    } else if (take && L.t - L.t_ps >= a.t_cap) {
-      store_record<MPRV>(a, L, L.ymax, L.ymin);
-      L.phase++;
-      L.status |= ENS_SYS_SETTLED;
-      done = true;
+      L.ymax = fmax(L.ymax, y[0]);
+      L.ymin = fmin(L.ymin, y[0]);
+      if (pmax) {
+        fs.have = 0;
+        store_record<MPRV>(a, L, y[0], L.ymin);
+        L.phase++;
+        if constexpr (MPRV::kPrio) note_phase_end(L);
+        L.ymax = -INFINITY;
+        L.ymin = INFINITY;
+        L.t_ps = L.t;
+        note_late(a, m, L);
+        if (L.phase >= L.n_phases) done = true;
+      } else if (L.t - L.t_ps >= a.t_cap) {
+        store_record<MPRV>(a, L, L.ymax, L.ymin);
+        L.phase++;
+        L.status |= ENS_SYS_SETTLED;
+        done = true;
+      }
     }
   }
   if (!done && a.max_steps > 0 && L.attempts >= a.max_steps) {
@@ -1207,10 +1325,11 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
           L.ymax = cy[ENS_CARRY_YMAX * a.n + i];
           L.ymin = cy[ENS_CARRY_YMIN * a.n + i];
           L.t_ps = cy[ENS_CARRY_TPS * a.n + i];
-          if constexpr (M::kEvents) m.seated = cy[ENS_CARRY_SEATED * a.n + i] != 0.0;
+          if constexpr (M::kEvents) m.flight = cy[ENS_CARRY_SEATED * a.n + i] != 0.0 ? 0.0 : 1.0;
           L.n_phases = sdesc[e].n_phases;
           L.max_impacts = sdesc[e].max_impacts;
-          L.phase = L.accepted = L.rejected = L.evretry = L.impacts = L.attempts = 0;
+          L.phase = L.accepted = L.evretry = L.impacts = L.attempts = 0;
+          if constexpr (M::kEvents) note_late(a, m, L);
           if constexpr (M::kPrio) {
             L.phase_att = 0;
             L.rem = 3.0e38f;  // unknown until the first phase ends: treat as long
@@ -1219,7 +1338,7 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
           L.ev_iter = 0;
           L.nrhs = 0;
           L.head = use_head;
-          fs.have = false;
+          fs.have = 0;
           active = true;
           if (L.n_phases <= 0) {
             store_lane<M, SC>(a, L, y, seated_of(m));
@@ -1247,40 +1366,51 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
       continue;
     }
     // Attempts until a lane finishes its system: only then can the refill
-    // rule above fire or the wave run out of work, so the refill bookkeeping
-    // is skipped on the other attempts (one ballot each).
-    while (true) {
-      const uint32_t ph_before = M::kPrio ? L.phase : 0u;
-      bool fin = false;
-      if (active) {
-        bool done;
-        if constexpr (M::kEvents)
-          done = step_valve<SC>(a, m, L, y, fs);
-        else
-          done = step_fixed<M, SC, LOC>(a, m, L, y, fs);
-        if (done) {
-          store_lane<M, SC>(a, L, y, seated_of(m));
-          if constexpr (M::kDrive2) cold(a)->phi2[L.sys] = m.phi;
-          active = false;
-          fin = true;
+    // rule above fire or the wave run out of work.  The loop runs in the
+    // lanes that carry a system; a wave whose attempt had no rare outcome goes
+    // straight to the next.
+    if (active) {
+      auto tabs = Scheme<SC>::tables();
+      Mask done = 0;
+      do {
+        Outcome o;
+        double y5[D], k7[D];   // the valve's new state, for its rare outcomes
+        do {
+          if constexpr (M::kEvents)
+            step_valve<SC>(a, fresh(tabs), m, L, y, fs, o, y5, k7);
+          else
+            step_fixed<M, SC, LOC>(a, fresh(tabs), m, L, y, fs, o);
+        } while (o.rare == 0);
+        const uint32_t ph_before = M::kPrio ? L.phase : 0u;
+        bool fin = false;
+        if (in(o.rare)) {
+          if constexpr (M::kEvents)
+            fin = settle_valve<SC>(a, m, L, y, fs, o, y5, k7);
+          else
+            fin = settle_fixed<M>(a, m, L, y, fs, o);
+          if (fin) {
+            store_lane<M, SC>(a, L, y, seated_of(m));
+            if constexpr (M::kDrive2) cold(a)->phi2[L.sys] = m.phi;
+          }
         }
-      }
-      // Issue priority follows the wave's longest remaining work, so that the
-      // systems that will finish last are not slowed by short ones sharing the
-      // SIMD (a wave's own priority; results do not depend on it).
-      // (the wave's largest estimate against each level, by ballots)
-      if (M::kPrio && a.prioritize && __ballot(active && L.phase != ph_before) != 0ull) {
-        const float r = active ? L.rem : 0.0f;
-        if (__ballot(r > 1.0e6f) != 0ull)
-          __builtin_amdgcn_s_setprio(3);
-        else if (__ballot(r > 2.5e5f) != 0ull)
-          __builtin_amdgcn_s_setprio(2);
-        else if (__ballot(r > 6.0e4f) != 0ull)
-          __builtin_amdgcn_s_setprio(1);
-        else
-          __builtin_amdgcn_s_setprio(0);
-      }
-      if (__ballot(fin) != 0ull) break;
+        // Issue priority follows the wave's longest remaining work, so that the
+        // systems that will finish last are not slowed by short ones sharing the
+        // SIMD (a wave's own priority; results do not depend on it).
+        // (the wave's largest estimate against each level, by ballots)
+        if (M::kPrio && a.prioritize && __ballot(!fin && L.phase != ph_before) != 0ull) {
+          const float r = fin ? 0.0f : L.rem;
+          if (__ballot(r > 1.0e6f) != 0ull)
+            __builtin_amdgcn_s_setprio(3);
+          else if (__ballot(r > 2.5e5f) != 0ull)
+            __builtin_amdgcn_s_setprio(2);
+          else if (__ballot(r > 6.0e4f) != 0ull)
+            __builtin_amdgcn_s_setprio(1);
+          else
+            __builtin_amdgcn_s_setprio(0);
+        }
+        done = ballot(fin);
+      } while (done == 0);
+      active = !in(done);
     }
   }
 }
