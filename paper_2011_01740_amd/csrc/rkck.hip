@@ -997,7 +997,7 @@ __device__ __forceinline__ Mask at_cap(const RkckArgs &a, const Lane &L) {
 
 // One attempted step of a fixed-length-phase model, without its rare outcomes.
 template <class M, int SC, bool LOC>
-__device__ __forceinline__ void step_fixed(const RkckArgs &a,
+__device__ __forceinline__ void step_fixed(const RkckArgs &a, Mask act,
                                            Tables<typename Scheme<SC>::Tab> tabs, M &m, Lane &L,
                                            double *y, Fsal<M::D> &fs, Outcome &o) {
   constexpr int D = M::D;
@@ -1020,7 +1020,7 @@ __device__ __forceinline__ void step_fixed(const RkckArgs &a,
   const double h_new = clampd(h_try * fac, a.dt_min, a.dt_max);
   L.accepted = count(L.accepted, acc);
   if constexpr (LOC) {
-    if (in(acc) && y[1] > 0.0 && y5[1] <= 0.0) {
+    if (in(acc & act & ballot(y[1] > 0.0) & ballot(y5[1] <= 0.0))) {
       // the maximum of y1 between the step points, on the interpolant
       // (Dormand--Prince has f at both ends; Cash--Karp evaluates them)
       double f0[D], f1[D];
@@ -1053,7 +1053,7 @@ __device__ __forceinline__ void step_fixed(const RkckArgs &a,
   L.h = h_new;
   o.floor = over & acc;
   o.end = trunc & acc;
-  o.rare = o.bad | ((o.end | o.floor | cap) & ballot(true));
+  o.rare = (o.bad | o.end | o.floor | cap) & act;
 }
 
 // The rare outcomes of that attempt; returns true when the system is finished.
@@ -1106,7 +1106,7 @@ __device__ __forceinline__ void note_late(const RkckArgs &a, const MPRV &m, Lane
 // seated systems, and the cap of a phase's length.  A lane with such an
 // outcome leaves its state as it was (its new state stays in y5, k7).
 template <int SC>
-__device__ __forceinline__ void step_valve(const RkckArgs &a,
+__device__ __forceinline__ void step_valve(const RkckArgs &a, Mask act,
                                            Tables<typename Scheme<SC>::Tab> tabs, MPRV &m,
                                            Lane &L, double *y, Fsal<3> &fs, Outcome &o,
                                            double *y5, double *k7) {
@@ -1142,7 +1142,7 @@ __device__ __forceinline__ void step_valve(const RkckArgs &a,
     L.ymax = vmax(L.ymax, y5[0]);
     L.ymin = vmin(L.ymin, y5[0]);
   }
-  o.rare = (o.special | cap) & ballot(true);
+  o.rare = (o.special | cap) & act;
 }
 
 // The rare outcomes of that attempt; returns true when the system is finished.
@@ -1257,11 +1257,20 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
   const int lane = __lane_id();
   const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
   if (M::kPrio && a.prioritize) __builtin_amdgcn_s_setprio(3);
-  M m;
-  Lane L;
-  Fsal<D> fs;
-  double y[D];
-  bool active = false;
+  // The lanes that carry a system.  The step loop runs in all 64 lanes all the
+  // same, the others stepping whatever they last held, with no effect: a wave
+  // whose exec mask is sparse issues slower.  Measured on a chain of FMAs,
+  // cycles an instruction: 5.08 in every lane; 5.08 to 6.9, from one launch to
+  // the next, in 1 to 32 lanes of a wave alone on its CU; 12 (5.5 to 19) in
+  // 1 to 4 lanes of each of four waves on a CU.  At the end of a sweep, which
+  // its longest systems make, every wave is sparse: Keller--Miksis 64 x 64 with
+  // a tangent, 8 cycles, 47 to 59 ms in the carrying lanes, 35 ms in all.
+  Mask act = 0;
+  M m{};
+  Lane L{};
+  Fsal<D> fs{};
+  fs.have = 1;
+  double y[D] = {};
   bool drained = false;
   // Two queues over the positions of the queue order: the head [0, spread)
   // and the rest [spread, n), each with its own counter.  The wave in slot 0
@@ -1275,7 +1284,7 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
   bool head_prio = false;  // the wave raised its issue priority for head systems
 
   while (true) {
-    const unsigned long long idle = __ballot(!active);
+    const Mask idle = ~act;
     const int n_idle = __popcll(idle);
     if (!drained && n_idle > 0 && (n_idle >= a.refill || idle == ~0ull)) {
       const bool use_head = !head_done && (slot0 || rest_done);
@@ -1296,7 +1305,8 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
           rest_done = true;
       }
       drained = head_done && rest_done;
-      if (!active) {
+      bool took = false;
+      if (in(idle)) {
         const unsigned long long k = base + (unsigned long long)__popcll(idle & below);
         const unsigned long long me = first + k;
         if (k < limit) {
@@ -1339,19 +1349,20 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
           L.nrhs = 0;
           L.head = use_head;
           fs.have = 0;
-          active = true;
+          took = true;
           if (L.n_phases <= 0) {
             store_lane<M, SC>(a, L, y, seated_of(m));
             if constexpr (M::kDrive2) cold(a)->phi2[i] = m.phi;
-            active = false;
+            took = false;
           }
         }
       }
+      act |= ballot(took);
       // A wave that carries head systems raises its issue priority, so that
       // the long systems are not slowed by short ones sharing the SIMD (models
       // without their own remaining-work priority; results do not change).
       if constexpr (!M::kPrio) {
-        const bool want = spread > 0 && __ballot(active && L.head) != 0ull;
+        const bool want = spread > 0 && (act & ballot(L.head)) != 0;
         if (want != head_prio) {
           head_prio = want;
           if (want)
@@ -1361,57 +1372,53 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
         }
       }
     }
-    if (__ballot(active) == 0ull) {
+    if (act == 0) {
       if (drained) break;
       continue;
     }
     // Attempts until a lane finishes its system: only then can the refill
-    // rule above fire or the wave run out of work.  The loop runs in the
-    // lanes that carry a system; a wave whose attempt had no rare outcome goes
-    // straight to the next.
-    if (active) {
-      auto tabs = Scheme<SC>::tables();
-      Mask done = 0;
+    // rule above fire or the wave run out of work.  A wave whose attempt had no
+    // rare outcome goes straight to the next.
+    auto tabs = Scheme<SC>::tables();
+    Mask done = 0;
+    do {
+      Outcome o;
+      double y5[D], k7[D];   // the valve's new state, for its rare outcomes
       do {
-        Outcome o;
-        double y5[D], k7[D];   // the valve's new state, for its rare outcomes
-        do {
-          if constexpr (M::kEvents)
-            step_valve<SC>(a, fresh(tabs), m, L, y, fs, o, y5, k7);
-          else
-            step_fixed<M, SC, LOC>(a, fresh(tabs), m, L, y, fs, o);
-        } while (o.rare == 0);
-        const uint32_t ph_before = M::kPrio ? L.phase : 0u;
-        bool fin = false;
-        if (in(o.rare)) {
-          if constexpr (M::kEvents)
-            fin = settle_valve<SC>(a, m, L, y, fs, o, y5, k7);
-          else
-            fin = settle_fixed<M>(a, m, L, y, fs, o);
-          if (fin) {
-            store_lane<M, SC>(a, L, y, seated_of(m));
-            if constexpr (M::kDrive2) cold(a)->phi2[L.sys] = m.phi;
-          }
+        if constexpr (M::kEvents)
+          step_valve<SC>(a, act, fresh(tabs), m, L, y, fs, o, y5, k7);
+        else
+          step_fixed<M, SC, LOC>(a, act, fresh(tabs), m, L, y, fs, o);
+      } while (o.rare == 0);
+      const uint32_t ph_before = M::kPrio ? L.phase : 0u;
+      bool fin = false;
+      if (in(o.rare)) {
+        if constexpr (M::kEvents)
+          fin = settle_valve<SC>(a, m, L, y, fs, o, y5, k7);
+        else
+          fin = settle_fixed<M>(a, m, L, y, fs, o);
+        if (fin) {
+          store_lane<M, SC>(a, L, y, seated_of(m));
+          if constexpr (M::kDrive2) cold(a)->phi2[L.sys] = m.phi;
         }
-        // Issue priority follows the wave's longest remaining work, so that the
-        // systems that will finish last are not slowed by short ones sharing the
-        // SIMD (a wave's own priority; results do not depend on it).
-        // (the wave's largest estimate against each level, by ballots)
-        if (M::kPrio && a.prioritize && __ballot(!fin && L.phase != ph_before) != 0ull) {
-          const float r = fin ? 0.0f : L.rem;
-          if (__ballot(r > 1.0e6f) != 0ull)
-            __builtin_amdgcn_s_setprio(3);
-          else if (__ballot(r > 2.5e5f) != 0ull)
-            __builtin_amdgcn_s_setprio(2);
-          else if (__ballot(r > 6.0e4f) != 0ull)
-            __builtin_amdgcn_s_setprio(1);
-          else
-            __builtin_amdgcn_s_setprio(0);
-        }
-        done = ballot(fin);
-      } while (done == 0);
-      active = !in(done);
-    }
+      }
+      done = ballot(fin);
+      act &= ~done;
+      // Issue priority follows the wave's longest remaining work, so that the
+      // systems that will finish last are not slowed by short ones sharing the
+      // SIMD (a wave's own priority; results do not depend on it).
+      // (the wave's largest estimate against each level, by ballots)
+      if (M::kPrio && a.prioritize && (act & ballot(L.phase != ph_before)) != 0) {
+        if ((act & ballot(L.rem > 1.0e6f)) != 0)
+          __builtin_amdgcn_s_setprio(3);
+        else if ((act & ballot(L.rem > 2.5e5f)) != 0)
+          __builtin_amdgcn_s_setprio(2);
+        else if ((act & ballot(L.rem > 6.0e4f)) != 0)
+          __builtin_amdgcn_s_setprio(1);
+        else
+          __builtin_amdgcn_s_setprio(0);
+      }
+    } while (done == 0);
   }
 }
 
