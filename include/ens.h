@@ -304,7 +304,8 @@ typedef struct {
   int32_t spl;        /* RK4: systems per lane, 1, 2 or 4                    */
   int32_t refill;     /* RKCK45: idle lanes a wave waits for before it takes
                          new systems from the queue (1..64)                  */
-  int32_t grid;       /* RKCK45: persistent blocks (0 = resident capacity)   */
+  int32_t grid;       /* RKCK45: persistent blocks (0 = as many as the systems
+                         fill, at most the resident capacity)              */
   int32_t use_graph;  /* RKCK45: capture the launch sequence in a hipGraph
                          and replay it                                       */
   /* accessory */

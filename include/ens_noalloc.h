@@ -66,7 +66,7 @@ typedef struct {
 } ens_noalloc_args;
 
 /* Enqueues the adaptive solve of the n systems described by `args` with the
- * options `opts` (launch fields 0 = block 256, refill 1, the resident grid;
+ * options `opts` (launch fields 0 = block 256, refill 1, the grid of ens_solve;
  * use_graph ignored).  Results are bit-identical to ens_solve's on the same
  * inputs.  Errors (nothing enqueued): ENS_E_INVAL (bad arguments or sizes
  * beyond the scratch), ENS_E_UNSUPPORTED, ENS_E_HIP; message in

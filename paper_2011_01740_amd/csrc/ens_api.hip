@@ -777,8 +777,9 @@ static int solve_rkck(ens_t h, const ens_solve_opts *o) {
   int grid = o->grid;
   const int cap = ens::rkck_max_blocks(kmodel, h->solver, o->locate_max != 0, block);
   if (cap <= 0) return fail(h, ENS_E_HIP, "ens_solve: occupancy query failed");
-  if (grid <= 0) grid = cap;
   if (grid > cap) return fail(h, ENS_E_INVAL, "ens_solve: grid above resident capacity");
+  int32_t share_head = 64, share_rest = 64;
+  ens::rkck_plan(cap, block, h->n, o->spread, &grid, &share_head, &share_rest);
 
   // records
   const int64_t R = o->n_record;
@@ -840,6 +841,8 @@ static int solve_rkck(ens_t h, const ens_solve_opts *o) {
   a.R = R;
   a.n_ens = h->n_ens;
   a.refill = refill;
+  a.share_head = share_head;
+  a.share_rest = share_rest;
   a.t_phase = o->t_phase;
   a.dt_min = o->dt_min;
   a.dt_max = o->dt_max;

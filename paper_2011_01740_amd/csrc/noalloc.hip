@@ -161,7 +161,7 @@ extern "C" int ens_solve_noalloc(const ens_noalloc_args *a, const ens_solve_opts
   const int kmodel = ens::kernel_model(a->model, a->tangent, shared, a->n_ensembles, o->dt_max);
   const int cap = ens::rkck_max_blocks(kmodel, a->solver, o->locate_max != 0, block);
   if (cap <= 0) return fail(ENS_E_HIP, "ens_solve_noalloc: occupancy query failed");
-  const int grid = o->grid > 0 ? o->grid : cap;
+  int grid = o->grid;
   if (grid > cap) return fail(ENS_E_INVAL, "ens_solve_noalloc: grid above resident capacity");
   unsigned char *base = nullptr;
   NA_HIP(scratch_of(a->device, &base));
@@ -200,6 +200,7 @@ extern "C" int ens_solve_noalloc(const ens_noalloc_args *a, const ens_solve_opts
   ka.R = R;
   ka.n_ens = a->n_ensembles;
   ka.refill = refill;
+  ens::rkck_plan(cap, block, n, o->spread, &grid, &ka.share_head, &ka.share_rest);
   ka.t_phase = o->t_phase;
   ka.dt_min = o->dt_min;
   ka.dt_max = o->dt_max;

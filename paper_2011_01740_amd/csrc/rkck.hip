@@ -4,12 +4,14 @@
 // arXiv:2011.01740), with a device work queue that refills a lane as soon as
 // its system is finished.
 //
-// Work distribution.  The grid is the resident capacity of the chip.  A wave
-// keeps stepping its active lanes; when at least `refill` of its lanes are
-// idle (or all are), the lowest idle lane claims that many consecutive system
-// indices with one atomic add on the queue head, and the idle lanes take
-// base + (number of idle lanes below them).  A wave whose claim reaches n
-// stops refilling and retires when its last lane finishes.  Systems are
+// Work distribution.  The grid is the resident capacity of the chip, or as
+// many waves per SIMD as the systems fill.  A wave keeps stepping its active
+// lanes; when at least `refill` of its lanes are idle (or all are), the lowest
+// idle lane claims that many consecutive system indices with one atomic add on
+// the queue head, and the idle lanes take base + (number of idle lanes below
+// them).  A wave carries at most its share of the systems, so that few systems
+// spread over all SIMDs.  A wave whose claim reaches n stops refilling and
+// retires when its last lane finishes.  Systems are
 // handed out in index order, so neighbouring lanes integrate neighbouring
 // parameters (the paper's advice against divergence, Sec. 3.2.1) and
 // sub-ensembles are started in the order they are given.
@@ -114,6 +116,11 @@ __device__ __forceinline__ Tables<T> fresh(Tables<T> &t) {
 typedef unsigned long long Mask;
 __device__ __forceinline__ Mask ballot(bool b) { return __builtin_amdgcn_ballot_w64(b); }
 __device__ __forceinline__ bool in(Mask m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// A mask that the compiler may hold in vector registers, as the scalar that it is.
+__device__ __forceinline__ Mask uniform(Mask m) {
+  return ((Mask)(uint32_t)__builtin_amdgcn_readfirstlane((int)(m >> 32)) << 32) |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)m);
+}
 // n + 1 in the lanes of m, as one add with the mask as its carry.  m is the
 // result of scalar instructions, which a vector instruction may read at once.
 __device__ __forceinline__ uint32_t count(uint32_t n, Mask m) {
@@ -1271,7 +1278,7 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
   Fsal<D> fs{};
   fs.have = 1;
   double y[D] = {};
-  bool drained = false;
+  uint32_t drained = 0;
   // Two queues over the positions of the queue order: the head [0, spread)
   // and the rest [spread, n), each with its own counter.  The wave in slot 0
   // of its SIMD (one per SIMD, from the hardware id) prefers the head, all
@@ -1280,34 +1287,42 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
   // instead of sharing a SIMD with each other.
   const uint64_t spread = (uint64_t)a.spread, nsys = (uint64_t)a.n;
   const bool slot0 = (__builtin_amdgcn_s_getreg((3 << 11) | 4) & 0xF) == 0;  // HW_ID.WAVE_ID
-  bool head_done = spread == 0, rest_done = spread >= nsys;
+  uint32_t head_done = spread == 0, rest_done = spread >= nsys;
   bool head_prio = false;  // the wave raised its issue priority for head systems
+
+  uint32_t sparse = 0;     // the wave carries its share of a short head
 
   while (true) {
     const Mask idle = ~act;
-    const int n_idle = __popcll(idle);
-    if (!drained && n_idle > 0 && (n_idle >= a.refill || idle == ~0ull)) {
-      const bool use_head = !head_done && (slot0 || rest_done);
+    const bool use_head = (head_done ^ 1u) & ((slot0 ? 1u : 0u) | rest_done);
+    // Idle lanes that may take a system: up to the wave's share of its queue
+    // (64, that is all, unless the systems fit the chip's lanes).
+    const int carried = __popcll(act);
+    const int share = use_head ? a.share_head : a.share_rest;
+    const int room = sparse && !use_head && carried > 0 ? 0 : share - carried;
+    if (!drained && room > 0 && (room >= a.refill || carried == 0)) {
+      sparse = use_head && share < 64;
       const int leader = __ffsll((long long)idle) - 1;
       unsigned long long base = 0;
       if (lane == leader)
-        base = atomicAdd(cold(a)->queue + (use_head ? 1 : 0), (unsigned long long)n_idle);
+        base = atomicAdd(cold(a)->queue + (use_head ? 1 : 0), (unsigned long long)room);
       // the leader's value to the whole wave as a scalar (so that the queue
       // flags below are wave-uniform values in scalar registers)
       base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(base >> 32), leader)
               << 32) |
              (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)base, leader);
       const uint64_t first = use_head ? 0 : spread, limit = use_head ? spread : nsys - spread;
-      if (base + (unsigned long long)n_idle >= limit) {
+      if (base + (unsigned long long)room >= limit) {
         if (use_head)
-          head_done = true;
+          head_done = 1;
         else
-          rest_done = true;
+          rest_done = 1;
       }
-      drained = head_done && rest_done;
+      drained = head_done & rest_done;
+      const int nth = __popcll(idle & below);
       bool took = false;
-      if (in(idle)) {
-        const unsigned long long k = base + (unsigned long long)__popcll(idle & below);
+      if (in(idle) && nth < room) {
+        const unsigned long long k = base + (unsigned long long)nth;
         const unsigned long long me = first + k;
         if (k < limit) {
           const RkckCold *cp = cold(a);
@@ -1380,6 +1395,7 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
     // rule above fire or the wave run out of work.  A wave whose attempt had no
     // rare outcome goes straight to the next.
     auto tabs = Scheme<SC>::tables();
+    act = uniform(act);
     Mask done = 0;
     do {
       Outcome o;
@@ -1428,17 +1444,21 @@ hipError_t launch_model(int block, int grid, const RkckArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
+int cu_count() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 0;
+  return cus;
+}
+
 template <class M, int SC, bool LOC>
 int max_blocks_model(int block) {
   int per_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_rkck<M, SC, LOC>, block, 0) !=
       hipSuccess)
     return 0;
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return 0;
-  return per_cu * cus;
+  return per_cu * cu_count();
 }
 
 // The kernel instantiation behind a host model id: calls fn(Pick<M, LOC>{})
@@ -1571,6 +1591,37 @@ hipError_t launch_rkck(int model, int solver, int block, int grid, const RkckArg
   if (solver == ENS_RKDP45) return launch_scheme<kDP>(model, loc, block, grid, a, s);
   if (solver == ENS_RKCK45) return launch_scheme<kCK>(model, loc, block, grid, a, s);
   return hipErrorInvalidValue;
+}
+
+// A system is a serial chain of attempts, and a wave that has a SIMD to itself
+// issues faster than waves that share one (5 cycles an instruction each, until
+// their sum fills the SIMD's one per 4).  So the default grid has no more
+// waves per SIMD than the systems fill with 64 lanes each, and a wave's share
+// of the queue is what spreads them evenly over those waves: fewer systems in
+// a wave also means fewer attempts in which one of them needs the code of a
+// rare outcome.  With more systems than lanes both are as before: the resident
+// capacity, and every idle lane refilled.  Full waves on the resident grid
+// against the share: three valve ensembles (2^15 + 2^16 + 2^17 systems, the first
+// at the head) 94.9 and 86.7 ms, 10500 valves with Dormand--Prince 33.9 and
+// 26.8 ms, 2025 dual-drive systems 19.3 and 17.2 ms, 1000 quadratic ones, 3
+// phases, 131 and 82 us.
+void rkck_plan(int cap, int block, int64_t n, int64_t spread, int *grid, int32_t *share_head,
+               int32_t *share_rest) {
+  const int wpb = block / 64, simds = 4 * cu_count();
+  if (*grid <= 0) {
+    const int64_t one = simds > 0 ? (simds + wpb - 1) / wpb : cap;   // blocks: a wave per SIMD
+    const int64_t rounds = (n + one * block - 1) / (one * block);
+    const int64_t want = one * (rounds > 0 ? rounds : 1);
+    *grid = want < cap ? (int)want : cap;
+  }
+  const int64_t waves = (int64_t)*grid * wpb;
+  auto share = [](int64_t systems, int64_t over) {
+    const int64_t q = over > 0 ? (systems + over - 1) / over : 64;
+    return (int32_t)(q < 1 ? 1 : (q > 64 ? 64 : q));
+  };
+  // the head of the queue goes to one wave per SIMD
+  *share_head = share(spread, waves < simds ? waves : simds);
+  *share_rest = spread > 0 ? 64 : share(n, waves);
 }
 
 int rkck_max_blocks(int model, int solver, bool locate_max, int block) {
