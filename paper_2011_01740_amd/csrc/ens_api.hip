@@ -778,8 +778,9 @@ static int solve_rkck(ens_t h, const ens_solve_opts *o) {
   const int cap = ens::rkck_max_blocks(kmodel, h->solver, o->locate_max != 0, block);
   if (cap <= 0) return fail(h, ENS_E_HIP, "ens_solve: occupancy query failed");
   if (grid > cap) return fail(h, ENS_E_INVAL, "ens_solve: grid above resident capacity");
-  int32_t share_head = 64, share_rest = 64;
-  ens::rkck_plan(cap, block, h->n, o->spread, &grid, &share_head, &share_rest);
+  ens::RkckArgs a;
+  std::memset(&a, 0, sizeof(a));  // padding too: the struct is compared bytewise
+  ens::rkck_plan(cap, block, h->n, o->spread, h->use_order, &grid, &a);
 
   // records
   const int64_t R = o->n_record;
@@ -832,8 +833,6 @@ static int solve_rkck(ens_t h, const ens_solve_opts *o) {
   c.coef = h->d_coef;
   ENS_HIP(h, ens::launch_set_cold(h->d_cold, c, h->stream));
 
-  ens::RkckArgs a;
-  std::memset(&a, 0, sizeof(a));  // padding too: the struct is compared bytewise
   a.cold = h->d_cold;
   a.spread = o->spread;
   a.desc = h->d_desc;
@@ -841,8 +840,6 @@ static int solve_rkck(ens_t h, const ens_solve_opts *o) {
   a.R = R;
   a.n_ens = h->n_ens;
   a.refill = refill;
-  a.share_head = share_head;
-  a.share_rest = share_rest;
   a.t_phase = o->t_phase;
   a.dt_min = o->dt_min;
   a.dt_max = o->dt_max;

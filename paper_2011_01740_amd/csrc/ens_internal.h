@@ -53,11 +53,15 @@ struct RkckArgs {
   int64_t spread;           // head [0, spread) of the queue order: one wave per SIMD
   const EnsDesc *desc;      // [n_ens]
   int64_t n;
+  int64_t taken;            // systems given out by place, before the queue
   int64_t R;
   int32_t n_ens;
   int32_t refill;           // idle lanes a wave waits for before refilling
   int32_t share_head;       // systems a wave carries at most, of the queue's head
   int32_t share_rest;       // ... and of the rest (rkck_plan)
+  int32_t place;            // blocks of a round of the chip, whose waves take their first
+                            // share by place; 0: by the queue
+  int32_t ordered;          // the queue has an order
   double t_phase, dt_min, dt_max, rtol, atol, event_tol, t_cap, v_stick;
   int64_t max_steps;
   int32_t max_event_iter;
@@ -109,10 +113,11 @@ hipError_t launch_rkck(int model, int solver, int block, int grid, const RkckArg
                        hipStream_t s);
 // Resident-wave capacity of the persistent kernel for this model, solver and block.
 int rkck_max_blocks(int model, int solver, bool locate_max, int block);
-// The grid (if *grid is not given: at most `cap`) and each wave's share of
-// the queue for n systems, the first `spread` of them at the head.
-void rkck_plan(int cap, int block, int64_t n, int64_t spread, int *grid, int32_t *share_head,
-               int32_t *share_rest);
+// The grid (if *grid is not given: at most `cap`) and how the waves share n
+// systems out, the first `spread` of them at the head of the queue (the
+// share_*, place, taken and ordered fields of *a).
+void rkck_plan(int cap, int block, int64_t n, int64_t spread, bool order, int *grid,
+               RkckArgs *a);
 hipError_t launch_fill_f64(double *p, double v, int64_t count, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, int64_t count,
                            hipStream_t s);

@@ -200,7 +200,7 @@ extern "C" int ens_solve_noalloc(const ens_noalloc_args *a, const ens_solve_opts
   ka.R = R;
   ka.n_ens = a->n_ensembles;
   ka.refill = refill;
-  ens::rkck_plan(cap, block, n, o->spread, &grid, &ka.share_head, &ka.share_rest);
+  ens::rkck_plan(cap, block, n, o->spread, a->order != nullptr, &grid, &ka);
   ka.t_phase = o->t_phase;
   ka.dt_min = o->dt_min;
   ka.dt_max = o->dt_max;

@@ -23,6 +23,7 @@
 // stream for every lane.  Sub-ensemble descriptors (shared parameters and
 // budgets) sit in LDS.
 #include <cmath>
+#include <cstddef>
 
 #include "ens_internal.h"
 
@@ -120,6 +121,9 @@ __device__ __forceinline__ bool in(Mask m) { return __builtin_amdgcn_inverse_bal
 __device__ __forceinline__ Mask uniform(Mask m) {
   return ((Mask)(uint32_t)__builtin_amdgcn_readfirstlane((int)(m >> 32)) << 32) |
          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)m);
+}
+__device__ __forceinline__ uint32_t uniform32(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
 // n + 1 in the lanes of m, as one add with the mask as its carry.  m is the
 // result of scalar instructions, which a vector instruction may read at once.
@@ -278,7 +282,8 @@ struct MQuad {  // dx/dt = x^2 - p (Sec. 3)
   static constexpr bool kTangent = false;
   static constexpr int kNCoef = 0;  // no precomputed coefficients
   double p;
-  __device__ void init(const double *P, int64_t n, int64_t i, const double *sh) { p = P[i]; }
+  template <class Ptr>
+  __device__ void init(Ptr P, int64_t n, int64_t i, const double *sh) { p = P[i]; }
   __device__ void begin(double) {}
   template <int SC, int S>
   __device__ void rhs(double, double, const double *y, double *f) const {
@@ -306,7 +311,8 @@ struct MLorenz {  // Sec. 4.1
   static constexpr bool kTangent = false;
   static constexpr int kNCoef = 0;  // no precomputed coefficients
   double rho, sigma, beta;
-  __device__ void init(const double *P, int64_t n, int64_t i, const double *sh) {
+  template <class Ptr>
+  __device__ void init(Ptr P, int64_t n, int64_t i, const double *sh) {
     rho = P[i];
     sigma = sh[0];
     beta = sh[1];
@@ -436,7 +442,8 @@ struct MKM {
   // step, so that each stage forms its forcing terms from its angle offset
   // directly: K5 sin(a + b) = K5 s0 cos b + K5 c0 sin b, and the same for cos
   double k5s, k5c, k7s, k7c;
-  __device__ void init(const double *P, int64_t n, int64_t i, const double *sh) {
+  template <class Ptr>
+  __device__ void init(Ptr P, int64_t n, int64_t i, const double *sh) {
     const double pa = P[i], f = P[n + i];
     const double rhoL = sh[0], cL = sh[1], pV = sh[2], sig = sh[3], mu = sh[4];
     const double gam = sh[5], pinf = sh[6];
@@ -492,7 +499,8 @@ struct MKM {
       c[15 * n + i] = dual ? 1.0 : 0.0;
     }
   }
-  __device__ void load_coef(const double *c, int64_t n, int64_t i) {
+  template <class Ptr>
+  __device__ void load_coef(Ptr c, int64_t n, int64_t i) {
     K0 = c[0 * n + i];
     K1 = c[1 * n + i];
     K2 = c[2 * n + i];
@@ -673,7 +681,8 @@ struct MPRV {
   double q, kappa, delta, beta, r;
   double flight;   // 1, or 0 while seated
   __device__ bool seated() const { return flight == 0.0; }
-  __device__ void init(const double *P, int64_t n, int64_t i, const double *sh) {
+  template <class Ptr>
+  __device__ void init(Ptr P, int64_t n, int64_t i, const double *sh) {
     q = P[i];
     kappa = sh[0];
     delta = sh[1];
@@ -874,49 +883,72 @@ __device__ __forceinline__ void note_phase_end(Lane &L) {
   L.phase_att = L.attempts;
 }
 
-// The cold pointers, read from device memory where they are used (the
-// empty asm hides that the address is the same on every iteration, so the
-// loads are not hoisted out of the step loop into scalar registers).
-__device__ __forceinline__ const RkckCold *cold(const RkckArgs &a) {
-  const RkckCold *c = a.cold;
-  asm volatile("" : "+s"(c));
-  return c;
+// The launch's arguments and the per-system arrays, as the code off the common
+// path reads them: with scalar loads at the place of use (the empty asm hides
+// that the address is the same every time, so nothing is loaded ahead and held
+// in scalar registers through the step loop).  The arrays are global memory: a
+// store through a generic pointer would also hold up the next scalar load of
+// the step loop until it is done.
+#define ENS_GLOBAL __attribute__((address_space(1)))
+#define ENS_CONST __attribute__((address_space(4)))
+typedef const ENS_CONST RkckArgs ColdArgs;
+struct ColdArrays {   // RkckCold with its address space
+  const ENS_GLOBAL double *p;
+  ENS_GLOBAL double *y, *phi2, *t, *h, *rec;
+  ENS_GLOBAL int64_t *stats;
+  ENS_GLOBAL int32_t *status;
+  unsigned long long *queue;
+  const ENS_GLOBAL int64_t *order;
+  ENS_GLOBAL double *carry, *coef;
+};
+static_assert(sizeof(ColdArrays) == sizeof(RkckCold) &&
+                  offsetof(ColdArrays, stats) == offsetof(RkckCold, stats) &&
+                  offsetof(ColdArrays, order) == offsetof(RkckCold, order) &&
+                  offsetof(ColdArrays, coef) == offsetof(RkckCold, coef),
+              "the same layout");
+__device__ __forceinline__ ColdArgs &cold_args() {   // the kernel's only argument
+  ColdArgs *p = (ColdArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *p;
+}
+__device__ __forceinline__ const ENS_CONST ColdArrays *cold(ColdArgs &a) {
+  return (const ENS_CONST ColdArrays *)a.cold;
 }
 
 // Ring slot of the current phase: phase mod R in 32 bits (phases are
 // counted below 2^32; a ring that long never wraps).
-__device__ __forceinline__ int64_t ring_slot(const RkckArgs &a, const Lane &L) {
+__device__ __forceinline__ int64_t ring_slot(ColdArgs &a, const Lane &L) {
   return a.R > (int64_t)UINT32_MAX ? (int64_t)L.phase
                                    : (int64_t)(L.phase % (uint32_t)a.R);
 }
 
 template <class M>
-__device__ __forceinline__ void store_record(const RkckArgs &a, const Lane &L, double v0,
+__device__ __forceinline__ void store_record(ColdArgs &a, const Lane &L, double v0,
                                              double v1) {
   if (a.R <= 0) return;
   constexpr int F = M::kF;
   const int64_t slot = ring_slot(a, L);
-  double *rec = cold(a)->rec;
+  ENS_GLOBAL double *rec = cold(a)->rec;
   rec[(slot * F) * a.n + L.sys] = v0;
   if (F > 1) rec[(slot * F + 1) * a.n + L.sys] = v1;
 }
 
 // Record fields 1 .. K of a phase with tangents: their log growths.
 template <class M, int K>
-__device__ __forceinline__ void store_growth(const RkckArgs &a, const Lane &L, const double *g) {
+__device__ __forceinline__ void store_growth(ColdArgs &a, const Lane &L, const double *g) {
   if (a.R <= 0) return;
   const int64_t slot = ring_slot(a, L);
-  double *rec = cold(a)->rec;
+  ENS_GLOBAL double *rec = cold(a)->rec;
 #pragma unroll
   for (int v = 0; v < K; ++v) rec[(slot * M::kF + 1 + v) * a.n + L.sys] = g[v];
 }
 
 template <class M, int SC>
-__device__ __forceinline__ void store_lane(const RkckArgs &a, const Lane &L, const double *y,
+__device__ __forceinline__ void store_lane(ColdArgs &a, const Lane &L, const double *y,
                                            bool seated) {
   constexpr int D = M::D;
   const int64_t n = a.n, i = L.sys;
-  const RkckCold *cp = cold(a);
+  const ENS_CONST ColdArrays *cp = cold(a);
 #pragma unroll
   for (int c = 0; c < D; ++c) cp->y[c * n + i] = y[c];
   cp->t[i] = L.t;
@@ -924,7 +956,7 @@ __device__ __forceinline__ void store_lane(const RkckArgs &a, const Lane &L, con
   const uint32_t bad = (L.status & ENS_SYS_NONFINITE) ? 1u : 0u;
   const uint32_t rejected = L.attempts - L.accepted - L.evretry - bad;
   const int64_t att = (int64_t)L.accepted + rejected + L.evretry;
-  int64_t *stats = cp->stats;
+  ENS_GLOBAL int64_t *stats = cp->stats;
   stats[ENS_ST_ACCEPTED * n + i] = L.accepted;
   stats[ENS_ST_REJECTED * n + i] = rejected;
   // 6 per attempt (Dormand--Prince counts a non-finite one, too), plus
@@ -935,7 +967,7 @@ __device__ __forceinline__ void store_lane(const RkckArgs &a, const Lane &L, con
   stats[ENS_ST_PHASES * n + i] = L.phase;
   stats[ENS_ST_EVRETRY * n + i] = L.evretry;
   cp->status[i] = L.status;
-  double *cy = cp->carry;
+  ENS_GLOBAL double *cy = cp->carry;
   cy[ENS_CARRY_YMAX * n + i] = L.ymax;
   cy[ENS_CARRY_YMIN * n + i] = L.ymin;
   cy[ENS_CARRY_TPS * n + i] = L.t_ps;
@@ -996,15 +1028,25 @@ struct Outcome {
   double h_try, h_keep;  // the attempted step; the step size before it
 };
 
-// The lanes whose attempts reach the step cap (max_steps < 2^32; without a
-// cap, 2^32 - 1 attempts, which settle_*() then lets pass).
-__device__ __forceinline__ Mask at_cap(const RkckArgs &a, const Lane &L) {
-  return ballot(L.attempts >= (a.max_steps > 0 ? (uint32_t)a.max_steps : UINT32_MAX));
+// The arguments that every attempt reads, held in scalar registers: the empty
+// asm keeps the compiler from loading them again in every attempt (five loads
+// and their waits) to free the registers for constants.
+struct HotArgs {
+  double t_phase, dt_min, dt_max, rtol, atol;
+  uint32_t cap;   // the step cap (max_steps < 2^32); without one, 2^32 - 1
+                  // attempts, which settle_*() then lets pass
+};
+__device__ __forceinline__ HotArgs hot_args(const RkckArgs &a) {
+  HotArgs h{a.t_phase, a.dt_min, a.dt_max, a.rtol, a.atol,
+            a.max_steps > 0 ? (uint32_t)a.max_steps : UINT32_MAX};
+  asm volatile("" : "+s"(h.t_phase), "+s"(h.dt_min), "+s"(h.dt_max), "+s"(h.rtol), "+s"(h.atol),
+               "+s"(h.cap));
+  return h;
 }
 
 // One attempted step of a fixed-length-phase model, without its rare outcomes.
 template <class M, int SC, bool LOC>
-__device__ __forceinline__ void step_fixed(const RkckArgs &a, Mask act,
+__device__ __forceinline__ void step_fixed(const HotArgs &a, Mask act,
                                            Tables<typename Scheme<SC>::Tab> tabs, M &m, Lane &L,
                                            double *y, Fsal<M::D> &fs, Outcome &o) {
   constexpr int D = M::D;
@@ -1013,7 +1055,7 @@ __device__ __forceinline__ void step_fixed(const RkckArgs &a, Mask act,
   const Mask trunc = ballot(L.t + h_try >= a.t_phase);
   h_try = in(trunc) ? a.t_phase - L.t : h_try;
   L.attempts++;
-  const Mask cap = at_cap(a, L);
+  const Mask cap = ballot(L.attempts >= a.cap);
   if constexpr (SC == kDP)
     dp_attempt(m, tabs, L.t, y, h_try, fs, L.nrhs, y5, err, k7);
   else
@@ -1065,7 +1107,7 @@ __device__ __forceinline__ void step_fixed(const RkckArgs &a, Mask act,
 
 // The rare outcomes of that attempt; returns true when the system is finished.
 template <class M>
-__device__ __forceinline__ bool settle_fixed(const RkckArgs &a, M &m, Lane &L, double *y,
+__device__ __forceinline__ bool settle_fixed(ColdArgs &a, M &m, Lane &L, double *y,
                                              Fsal<M::D> &fs, const Outcome &o) {
   if (in(o.bad)) {
     L.h = o.h_keep;
@@ -1113,7 +1155,7 @@ __device__ __forceinline__ void note_late(const RkckArgs &a, const MPRV &m, Lane
 // seated systems, and the cap of a phase's length.  A lane with such an
 // outcome leaves its state as it was (its new state stays in y5, k7).
 template <int SC>
-__device__ __forceinline__ void step_valve(const RkckArgs &a, Mask act,
+__device__ __forceinline__ void step_valve(const HotArgs &a, Mask act,
                                            Tables<typename Scheme<SC>::Tab> tabs, MPRV &m,
                                            Lane &L, double *y, Fsal<3> &fs, Outcome &o,
                                            double *y5, double *k7) {
@@ -1121,7 +1163,7 @@ __device__ __forceinline__ void step_valve(const RkckArgs &a, Mask act,
   double err[D];
   const double h_try = L.h;
   L.attempts++;
-  const Mask cap = at_cap(a, L);
+  const Mask cap = ballot(L.attempts >= a.cap);
   if constexpr (SC == kDP)
     dp_attempt(m, tabs, L.t, y, h_try, fs, L.nrhs, y5, err, k7);
   else
@@ -1154,7 +1196,7 @@ __device__ __forceinline__ void step_valve(const RkckArgs &a, Mask act,
 
 // The rare outcomes of that attempt; returns true when the system is finished.
 template <int SC>
-__device__ __forceinline__ bool settle_valve(const RkckArgs &a, MPRV &m, Lane &L, double *y,
+__device__ __forceinline__ bool settle_valve(const RkckArgs &a, ColdArgs &ca, MPRV &m, Lane &L, double *y,
                                              Fsal<3> &fs, const Outcome &o, const double *y5,
                                              const double *k7) {
   constexpr int D = 3;
@@ -1225,7 +1267,7 @@ __device__ __forceinline__ bool settle_valve(const RkckArgs &a, MPRV &m, Lane &L
       L.ymin = fmin(L.ymin, y[0]);
       if (pmax) {
         fs.have = 0;
-        store_record<MPRV>(a, L, y[0], L.ymin);
+        store_record<MPRV>(ca, L, y[0], L.ymin);
         L.phase++;
         if constexpr (MPRV::kPrio) note_phase_end(L);
         L.ymax = -INFINITY;
@@ -1234,7 +1276,7 @@ __device__ __forceinline__ bool settle_valve(const RkckArgs &a, MPRV &m, Lane &L
         note_late(a, m, L);
         if (L.phase >= L.n_phases) done = true;
       } else if (L.t - L.t_ps >= a.t_cap) {
-        store_record<MPRV>(a, L, L.ymax, L.ymin);
+        store_record<MPRV>(ca, L, L.ymax, L.ymin);
         L.phase++;
         L.status |= ENS_SYS_SETTLED;
         done = true;
@@ -1246,6 +1288,28 @@ __device__ __forceinline__ bool settle_valve(const RkckArgs &a, MPRV &m, Lane &L
     done = true;
   }
   return done;
+}
+
+// The wave's first share of the systems, counted over the launch: block b of a
+// round of a.place blocks (one per CU; a block and the one a round later share
+// a CU, and their waves its SIMDs) and wave w of the block.  In index order the
+// four waves of a block take places a quarter of the round apart, so that
+// whichever SIMD each is on, the CU's SIMDs get alike parts of a parameter
+// grid's fast axis, and each round is turned by 99 blocks (3 modulo 8) against
+// the one before, so that the waves that share a SIMD do not all get the part
+// with the longest systems.  In a given order, longest first, every other round
+// runs backwards: the longest share a SIMD with the shortest.
+__device__ __forceinline__ uint32_t place_of_wave(ColdArgs &a) {
+  const uint32_t cus = (uint32_t)a.place, wpb = blockDim.x >> 6;
+  const uint32_t r = blockIdx.x / cus, b = blockIdx.x % cus, w = uniform32(threadIdx.x >> 6);
+  uint32_t in_round;
+  if (a.ordered) {
+    in_round = b * wpb + w;
+    if (r & 1) in_round = cus * wpb - 1 - in_round;
+  } else {
+    in_round = w * cus + (b + r * 99u) % cus;
+  }
+  return r * cus * wpb + in_round;
 }
 
 // Each model states the occupancy floor the register allocator must respect
@@ -1279,40 +1343,51 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
   fs.have = 1;
   double y[D] = {};
   uint32_t drained = 0;
+  const HotArgs hot = hot_args(a);
   // Two queues over the positions of the queue order: the head [0, spread)
   // and the rest [spread, n), each with its own counter.  The wave in slot 0
   // of its SIMD (one per SIMD, from the hardware id) prefers the head, all
   // others the rest; a wave takes from the other queue once its own is
   // empty.  Systems at the head (the longest) thus start one wave per SIMD
   // instead of sharing a SIMD with each other.
-  const uint64_t spread = (uint64_t)a.spread, nsys = (uint64_t)a.n;
   const bool slot0 = (__builtin_amdgcn_s_getreg((3 << 11) | 4) & 0xF) == 0;  // HW_ID.WAVE_ID
-  uint32_t head_done = spread == 0, rest_done = spread >= nsys;
+  uint32_t head_done = a.spread == 0, rest_done = a.spread + a.taken >= a.n;
   bool head_prio = false;  // the wave raised its issue priority for head systems
 
   uint32_t sparse = 0;     // the wave carries its share of a short head
+  // A wave's first systems by its place in the launch (rkck_plan); the queue
+  // starts behind them.
+  uint32_t placed = a.place != 0;
 
   while (true) {
+    ColdArgs &ca = cold_args();
     const Mask idle = ~act;
     const bool use_head = (head_done ^ 1u) & ((slot0 ? 1u : 0u) | rest_done);
     // Idle lanes that may take a system: up to the wave's share of its queue
     // (64, that is all, unless the systems fit the chip's lanes).
     const int carried = __popcll(act);
-    const int share = use_head ? a.share_head : a.share_rest;
+    const int share = use_head ? ca.share_head : ca.share_rest;
     const int room = sparse && !use_head && carried > 0 ? 0 : share - carried;
-    if (!drained && room > 0 && (room >= a.refill || carried == 0)) {
+    if (!drained && room > 0 && (room >= ca.refill || carried == 0)) {
       sparse = use_head && share < 64;
+      const uint64_t spread = (uint64_t)ca.spread, taken = (uint64_t)ca.taken;
       const int leader = __ffsll((long long)idle) - 1;
       unsigned long long base = 0;
-      if (lane == leader)
-        base = atomicAdd(cold(a)->queue + (use_head ? 1 : 0), (unsigned long long)room);
+      if (placed == 0 && lane == leader)
+        base = atomicAdd(cold(ca)->queue + (use_head ? 1 : 0), (unsigned long long)room);
       // the leader's value to the whole wave as a scalar (so that the queue
       // flags below are wave-uniform values in scalar registers)
       base = ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(base >> 32), leader)
               << 32) |
              (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)base, leader);
-      const uint64_t first = use_head ? 0 : spread, limit = use_head ? spread : nsys - spread;
-      if (base + (unsigned long long)room >= limit) {
+      uint64_t first = use_head ? 0 : spread + taken;
+      const uint64_t limit = use_head ? spread : (uint64_t)ca.n - spread - taken;
+      uint64_t last = limit;
+      if (placed) {
+        first = (uint64_t)share * place_of_wave(ca);
+        last = first < taken ? (taken - first < (uint64_t)share ? taken - first : share) : 0;
+        placed = 0;
+      } else if (base + (unsigned long long)room >= limit) {
         if (use_head)
           head_done = 1;
         else
@@ -1324,33 +1399,33 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
       if (in(idle) && nth < room) {
         const unsigned long long k = base + (unsigned long long)nth;
         const unsigned long long me = first + k;
-        if (k < limit) {
-          const RkckCold *cp = cold(a);
-          const int64_t *order = cp->order;
+        if (k < last) {
+          const ENS_CONST ColdArrays *cp = cold(ca);
+          const ENS_GLOBAL int64_t *order = cp->order;
           const int64_t i = order ? order[me] : (int64_t)me;
           int e = 0;
-          while (e + 1 < a.n_ens && i >= sdesc[e].last) ++e;
+          while (e + 1 < ca.n_ens && i >= sdesc[e].last) ++e;
           if constexpr (M::kNCoef > 0) {
             if (cp->coef)
-              m.load_coef(cp->coef, a.n, i);
+              m.load_coef(cp->coef, ca.n, i);
             else
-              m.init(cp->p, a.n, i, sdesc[e].shared);
+              m.init(cp->p, ca.n, i, sdesc[e].shared);
           } else {
-            m.init(cp->p, a.n, i, sdesc[e].shared);
+            m.init(cp->p, ca.n, i, sdesc[e].shared);
           }
           if constexpr (M::kDrive2) m.phi = cp->phi2[i];
 #pragma unroll
-          for (int c = 0; c < D; ++c) y[c] = cp->y[c * a.n + i];
+          for (int c = 0; c < D; ++c) y[c] = cp->y[c * ca.n + i];
           L.sys = i;
           L.t = cp->t[i];
           L.h = cp->h[i];
           // the running phase as the previous solve left it (a fresh state
           // carries no maximum or minimum, its phase starting at t0)
-          const double *cy = cp->carry;
-          L.ymax = cy[ENS_CARRY_YMAX * a.n + i];
-          L.ymin = cy[ENS_CARRY_YMIN * a.n + i];
-          L.t_ps = cy[ENS_CARRY_TPS * a.n + i];
-          if constexpr (M::kEvents) m.flight = cy[ENS_CARRY_SEATED * a.n + i] != 0.0 ? 0.0 : 1.0;
+          const ENS_GLOBAL double *cy = cp->carry;
+          L.ymax = cy[ENS_CARRY_YMAX * ca.n + i];
+          L.ymin = cy[ENS_CARRY_YMIN * ca.n + i];
+          L.t_ps = cy[ENS_CARRY_TPS * ca.n + i];
+          if constexpr (M::kEvents) m.flight = cy[ENS_CARRY_SEATED * ca.n + i] != 0.0 ? 0.0 : 1.0;
           L.n_phases = sdesc[e].n_phases;
           L.max_impacts = sdesc[e].max_impacts;
           L.phase = L.accepted = L.evretry = L.impacts = L.attempts = 0;
@@ -1366,8 +1441,8 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
           fs.have = 0;
           took = true;
           if (L.n_phases <= 0) {
-            store_lane<M, SC>(a, L, y, seated_of(m));
-            if constexpr (M::kDrive2) cold(a)->phi2[i] = m.phi;
+            store_lane<M, SC>(ca, L, y, seated_of(m));
+            if constexpr (M::kDrive2) cold(ca)->phi2[i] = m.phi;
             took = false;
           }
         }
@@ -1377,7 +1452,7 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
       // the long systems are not slowed by short ones sharing the SIMD (models
       // without their own remaining-work priority; results do not change).
       if constexpr (!M::kPrio) {
-        const bool want = spread > 0 && (act & ballot(L.head)) != 0;
+        const bool want = ca.spread > 0 && (act & ballot(L.head)) != 0;
         if (want != head_prio) {
           head_prio = want;
           if (want)
@@ -1402,20 +1477,21 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
       double y5[D], k7[D];   // the valve's new state, for its rare outcomes
       do {
         if constexpr (M::kEvents)
-          step_valve<SC>(a, act, fresh(tabs), m, L, y, fs, o, y5, k7);
+          step_valve<SC>(hot, act, fresh(tabs), m, L, y, fs, o, y5, k7);
         else
-          step_fixed<M, SC, LOC>(a, act, fresh(tabs), m, L, y, fs, o);
+          step_fixed<M, SC, LOC>(hot, act, fresh(tabs), m, L, y, fs, o);
       } while (o.rare == 0);
       const uint32_t ph_before = M::kPrio ? L.phase : 0u;
       bool fin = false;
+      ColdArgs &ra = cold_args();
       if (in(o.rare)) {
         if constexpr (M::kEvents)
-          fin = settle_valve<SC>(a, m, L, y, fs, o, y5, k7);
+          fin = settle_valve<SC>(a, ra, m, L, y, fs, o, y5, k7);
         else
-          fin = settle_fixed<M>(a, m, L, y, fs, o);
+          fin = settle_fixed<M>(ra, m, L, y, fs, o);
         if (fin) {
-          store_lane<M, SC>(a, L, y, seated_of(m));
-          if constexpr (M::kDrive2) cold(a)->phi2[L.sys] = m.phi;
+          store_lane<M, SC>(ra, L, y, seated_of(m));
+          if constexpr (M::kDrive2) cold(ra)->phi2[L.sys] = m.phi;
         }
       }
       done = ballot(fin);
@@ -1424,7 +1500,7 @@ __attribute__((amdgpu_waves_per_eu(min_waves(M::kMinWaves, SC, LOC), 8))) void k
       // systems that will finish last are not slowed by short ones sharing the
       // SIMD (a wave's own priority; results do not depend on it).
       // (the wave's largest estimate against each level, by ballots)
-      if (M::kPrio && a.prioritize && (act & ballot(L.phase != ph_before)) != 0) {
+      if (M::kPrio && ra.prioritize && (act & ballot(L.phase != ph_before)) != 0) {
         if ((act & ballot(L.rem > 1.0e6f)) != 0)
           __builtin_amdgcn_s_setprio(3);
         else if ((act & ballot(L.rem > 2.5e5f)) != 0)
@@ -1605,9 +1681,15 @@ hipError_t launch_rkck(int model, int solver, int block, int grid, const RkckArg
 // at the head) 94.9 and 86.7 ms, 10500 valves with Dormand--Prince 33.9 and
 // 26.8 ms, 2025 dual-drive systems 19.3 and 17.2 ms, 1000 quadratic ones, 3
 // phases, 131 and 82 us.
-void rkck_plan(int cap, int block, int64_t n, int64_t spread, int *grid, int32_t *share_head,
-               int32_t *share_rest) {
-  const int wpb = block / 64, simds = 4 * cu_count();
+// The first share of each wave goes by its place in the launch rather than by
+// which wave reaches the queue first (place_of_wave): by arrival it is chance
+// how many of the longest systems meet on one SIMD.  Keller--Miksis 512 x 512,
+// 16 cycles in index order, four waves to a SIMD: 95 to 104 ms by arrival,
+// 61.4 ms by place.  The queue then holds what is left.  Not with a head, which has its own
+// rule, nor on a grid that is no whole number of rounds of the chip.
+void rkck_plan(int cap, int block, int64_t n, int64_t spread, bool order, int *grid,
+               RkckArgs *a) {
+  const int wpb = block / 64, cus = cu_count(), simds = 4 * cus;
   if (*grid <= 0) {
     const int64_t one = simds > 0 ? (simds + wpb - 1) / wpb : cap;   // blocks: a wave per SIMD
     const int64_t rounds = (n + one * block - 1) / (one * block);
@@ -1620,8 +1702,11 @@ void rkck_plan(int cap, int block, int64_t n, int64_t spread, int *grid, int32_t
     return (int32_t)(q < 1 ? 1 : (q > 64 ? 64 : q));
   };
   // the head of the queue goes to one wave per SIMD
-  *share_head = share(spread, waves < simds ? waves : simds);
-  *share_rest = spread > 0 ? 64 : share(n, waves);
+  a->share_head = share(spread, waves < simds ? waves : simds);
+  a->share_rest = spread > 0 ? 64 : share(n, waves);
+  a->place = spread == 0 && cus > 0 && *grid % cus == 0 ? cus : 0;
+  a->taken = a->place ? (waves * a->share_rest < n ? waves * a->share_rest : n) : 0;
+  a->ordered = order ? 1 : 0;
 }
 
 int rkck_max_blocks(int model, int solver, bool locate_max, int block) {
