@@ -3,20 +3,22 @@
 //
 // Every product of the network has the form
 //     C[r][c] = sum_k X[r][k] * Y[c][k]
-// with X and Y row-major BF16 and the reduction index k contiguous:
+// with X and Y BF16 operands:
 //   forward      Z = A W^T       X = A  [batch][in],   Y = W   [out][in]
 //   data grad    dA = dZ W       X = dZ [batch][out],  Y = W^T [in][out]
 //   weight grad  dW = dZ^T A     X = dZ^T [out][batch], Y = A^T [in][batch]
+// Every operand that a kernel reads from global memory is stored in fragment
+// order (below), so that a wave's load of an MFMA operand is 1 KB contiguous.
 // A training step is 3 launches.  The work local to a batch row (the feature
 // layer, the forward products, the loss gradient, the data gradients) runs in
 // one kernel per 16-row tile with the activations in LDS (k_train_fb), which
 // also writes each activation and gradient transposed for the weight
 // gradients.  Those are split over the batch (k_gemm, the three products in
-// one launch, one wave per 32 x 32 output tile, operands read as 16-byte vectors straight from global memory,
-// a whole group of K steps at a time); bias gradients are column sums per
+// one launch, one wave per 32 x 32 output tile, a whole group of K steps
+// loaded at a time); bias gradients are column sums per
 // 16-row tile; one kernel then reduces every partial sum in a fixed order, so
 // every result is deterministic, and takes each parameter's Adam step on the
-// FP32 master copy at once, refreshing both W and W^T in BF16.  The first layer is a fixed random
+// FP32 master copy at once, refreshing its BF16 copies.  The first layer is a fixed random
 // Fourier-feature map of the two inputs (sin of x W1^T + b1, on the vector
 // unit) and is not trained, so no gradient is propagated to it.  Inference
 // runs the whole network in one kernel (k_fused).
@@ -104,64 +106,137 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
   return fmaf(z, e * 0.39894228040143268f, cdf);
 }
 
+// ------------------------------------------------------------ fragment order
+// An operand matrix [rows][K] as the MFMA fragments that its products read:
+// fragment (fb, c) covers rows 16 fb .. 16 fb + 15 and k = 32 c .. 32 c + 31,
+// and holds for lane l the 8 values of row 16 fb + l mod 16 that the lane
+// supplies, 16 bytes per lane, 1 KB in all.  Standard k order: lane group g =
+// l / 16, slot s <-> k = 32 c + 8 g + s.  Permuted order (the inputs of layers
+// 3 and 4 in k_fused): k = 32 c + 16 (s / 4) + 4 g + s mod 4.
+// In both, element (row, k) within its fragment:
+__device__ __forceinline__ int frag_std(int row, int k) {
+  return ((((k >> 3) & 3) << 4) | (row & 15)) * 8 + (k & 7);
+}
+__device__ __forceinline__ int frag_perm(int row, int k) {
+  return ((((k >> 2) & 3) << 4) | (row & 15)) * 8 + (((k >> 4) & 1) << 2 | (k & 3));
+}
+constexpr int kFrag = 512;   // elements of a fragment
+
+// The BF16 copies of the weights, all in fragment order, fragments of a row
+// block after each other ([fb][c]): W2, W3, W4 [out][in] and W3, W4 transposed
+// [in][out] for training, W3 and W4 in the permuted order for inference (which
+// shares W2).  Whoever changes a master weight writes its copies.
+struct WeightCopies {
+  bf16 *W2, *W3, *W4, *W3T, *W4T, *W3p, *W4p;
+};
+// Layer (2, 3 or 4) weights [o][in .. in + 3] (in a multiple of 4) = v in all
+// their copies.
+template <int LAYER>
+__device__ __forceinline__ void put_weights(const WeightCopies &c, int o, int in, bf16x4 v) {
+  constexpr int NC = kH / 32, NT = (LAYER == 4 ? kOut : kH) / 32;
+  const int at = ((o >> 4) * NC + (in >> 5)) * kFrag;
+  bf16 *W = LAYER == 2 ? c.W2 : (LAYER == 3 ? c.W3 : c.W4);
+  *(bf16x4 *)(W + at + frag_std(o, in)) = v;
+  if (LAYER == 2) return;
+  bf16 *Wp = LAYER == 3 ? c.W3p : c.W4p, *WT = LAYER == 3 ? c.W3T : c.W4T;
+  *(bf16x4 *)(Wp + at + frag_perm(o, in)) = v;
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    WT[((in >> 4) * NT + (o >> 5)) * kFrag + frag_std(in + q, o)] = v[q];
+}
+
 // ---------------------------------------------------------------- GEMM tile
 // Weight-gradient products: C = sum_k X[r][k] Y[c][k] over one share of the
 // batch (k), written as a partial sum.
 struct GemmArgs {
-  const bf16 *X;
-  int64_t ldx;
-  const bf16 *Y;
-  int64_t ldy;
-  int64_t R, C, K;       // C[R][C], reduction length K (split over gridDim.z)
-  float *out_f32;        // [split][R][C] partial sums
+  const bf16 *X, *Y;     // batch-major fragments: [k / 32][R / 16], [k / 32][16]
+  int R;                 // C[R][256], reduction over the batch
+  float *out_f32;        // [split][R][256] partial sums
 };
 
 constexpr int kTile = 32;  // output tile edge per wave
+constexpr int kLSplit = 3, kSplit = 1 << kLSplit;  // largest batch split
 
-// Up to three products in one launch (a training step's weight gradients),
-// each split over its K range in `split` equal parts.
+// The constants of one Adam step (Kingma and Ba, 2015), for k_reduce_grads:
+// h = lr, beta1, beta2, eps, 1 / (1 - beta1^t), 1 / (1 - beta2^t) with
+// t = t_base + step + 1.  With hyper != NULL the learning rate, betas, epsilon
+// and t_base are read from device memory (hyper[0..4]), so a captured epoch
+// replays with new values.  h == NULL: no step follows.
+struct AdamHyper {
+  const double *hyper;
+  double lr, b1, b2, eps, t_base;
+  int step;
+  float *h;
+};
+__device__ __forceinline__ void adam_constants(const AdamHyper &a) {
+  double lr = a.lr, b1 = a.b1, b2 = a.b2, eps = a.eps, t0 = a.t_base;
+  if (a.hyper) {
+    lr = a.hyper[0];
+    b1 = a.hyper[1];
+    b2 = a.hyper[2];
+    eps = a.hyper[3];
+    t0 = a.hyper[4];
+  }
+  const double t = t0 + (double)a.step + 1.0;
+  a.h[0] = (float)lr;
+  a.h[1] = (float)b1;
+  a.h[2] = (float)b2;
+  a.h[3] = (float)eps;
+  a.h[4] = (float)(1.0 / (1.0 - pow(b1, t)));
+  a.h[5] = (float)(1.0 / (1.0 - pow(b2, t)));
+}
+
+// Three products in one launch (a training step's weight gradients), each
+// split over the batch rows in `split` equal parts of `kchunk` rows.
 struct GemmBatch {
   GemmArgs g[3];
-  int64_t nblk[3];  // blocks of each product: (R/32) (C/32) split
-  int split;
+  int ntile[3];  // tiles of each product: (R/32) (256/32)
+  int lsplit;    // log2 split
+  int kchunk;
+  AdamHyper ad;
 };
 
-// One wave per 32 x 32 output tile (2 x 2 accumulators).  The blocks of the
-// products follow each other; within one, the tile row runs fastest, then
-// the tile column, then the K part, so consecutive blocks share the rows of
-// X, and blocks are spread over the XCDs by block index, so each XCD reads
-// its own share of X.  The K range is taken KG MFMA steps (32 each) at a
-// time: all operand loads of a group are issued before its products, so one
-// memory latency covers KG steps.
+// One wave per 32 x 32 output tile and part of the batch (2 x 2 accumulators).
+// Consecutive blocks take the parts: blocks go round the 8 XCDs, and with 8
+// parts every XCD multiplies the rows that its own k_train_fb blocks wrote, out of
+// its own L2.  The K range is taken KG MFMA steps (32 each) at a time: all
+// operand loads of a group are issued before its products, so one memory
+// latency covers KG steps.  One block more than the products need forms the
+// step's Adam constants (two FP64 powers) beside the products.
+// At 4096 rows: 6.6 us, before 12.0 us with row-major operands and the parts
+// spread over all XCDs; 75 MB through L2.
 template <int KG>
 __global__ __launch_bounds__(64) void k_gemm(GemmBatch bt) {
-  int64_t bid = blockIdx.x;
-  const int p = bid < bt.nblk[0] ? 0 : (bid < bt.nblk[0] + bt.nblk[1] ? 1 : 2);
-  bid -= p == 0 ? 0 : (p == 1 ? bt.nblk[0] : bt.nblk[0] + bt.nblk[1]);
+  int tile = (int)blockIdx.x >> bt.lsplit;
+  if (tile >= bt.ntile[0] + bt.ntile[1] + bt.ntile[2]) {
+    if (threadIdx.x == 0 && bt.ad.h) adam_constants(bt.ad);
+    return;
+  }
+  const int bz = (int)blockIdx.x & ((1 << bt.lsplit) - 1);
+  const int p = tile < bt.ntile[0] ? 0 : (tile < bt.ntile[0] + bt.ntile[1] ? 1 : 2);
+  tile -= p == 0 ? 0 : (p == 1 ? bt.ntile[0] : bt.ntile[0] + bt.ntile[1]);
   const GemmArgs g = p == 0 ? bt.g[0] : (p == 1 ? bt.g[1] : bt.g[2]);
-  const int64_t tr = g.R / kTile, tc = g.C / kTile;
-  const int64_t bx = bid % tr, by = (bid / tr) % tc, bz = bid / (tr * tc);
-  const int64_t r0 = bx * kTile, c0 = by * kTile;
-  const int64_t kchunk = g.K / bt.split;
-  const int64_t kb = bz * kchunk, ke = kb + kchunk;
+  // every product has kH columns
+  const int c0 = (tile % (kH / kTile)) * kTile, r0 = (tile / (kH / kTile)) * kTile;
+  const int nx = g.R / 16, ny = kH / 16;   // fragments per 32 rows of the batch
+  const int kb = bz * (bt.kchunk / 32), ke = kb + bt.kchunk / 32;
   const int l = threadIdx.x & 63;
-  const int64_t lr = l & 15, lk = (l >> 4) * 8;
-  const int64_t lc = l & 15, lrow = (l >> 4) * 4;
+  const int lc = l & 15, lrow = (l >> 4) * 4;
   f32x4 acc[2][2];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const bf16 *xp = g.X + (r0 + lr) * g.ldx + lk;
-  const bf16 *yp = g.Y + (c0 + lr) * g.ldy + lk;
-  for (int64_t k = kb; k < ke; k += 32 * KG) {
+  const bf16 *xp = g.X + (r0 / 16) * kFrag + l * 8;
+  const bf16 *yp = g.Y + (c0 / 16) * kFrag + l * 8;
+  for (int k = kb; k < ke; k += KG) {
     bf16x8 a[KG][2], b[KG][2];
 #pragma unroll
     for (int u = 0; u < KG; ++u) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) a[u][i] = *(const bf16x8 *)(xp + 16 * i * g.ldx + k + 32 * u);
+      for (int i = 0; i < 2; ++i) a[u][i] = *(const bf16x8 *)(xp + ((k + u) * nx + i) * kFrag);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) b[u][j] = *(const bf16x8 *)(yp + 16 * j * g.ldy + k + 32 * u);
+      for (int j = 0; j < 2; ++j) b[u][j] = *(const bf16x8 *)(yp + ((k + u) * ny + j) * kFrag);
     }
     // keep the whole group of loads ahead of the products
     __builtin_amdgcn_sched_barrier(0);
@@ -173,258 +248,246 @@ __global__ __launch_bounds__(64) void k_gemm(GemmBatch bt) {
         for (int j = 0; j < 2; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u][i], b[u][j], acc[i][j], 0, 0, 0);
   }
-  float *o = g.out_f32 + bz * g.R * g.C;
+  float *o = g.out_f32 + bz * g.R * kH;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int64_t c = c0 + 16 * j + lc;
-      const int64_t rb = r0 + 16 * i + lrow;
+      const int c = c0 + 16 * j + lc;
+      const int rb = r0 + 16 * i + lrow;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) o[(rb + q) * g.C + c] = acc[i][j][q];
+      for (int q = 0; q < 4; ++q) o[(rb + q) * kH + c] = acc[i][j][q];
     }
 }
 
 // ------------------------------------------------ fused training tile
 // One training step's work that is local to a row of the batch, for a tile
-// of 16 rows per block of 4 waves (a batch of 4096 rows fills every CU): the feature layer, the forward products
-// of layers 2 to 4, the loss gradient of the output layer, and the data
-// gradients back through layers 3 and 2.  The activations and gradients
-// that feed the next product stay in LDS (two BF16 row-major tiles, rows
-// padded to 264 so that the 16 rows of an operand fragment fall on
-// different banks), and each product's weight operands are loaded into
-// registers a layer ahead; each wave computes 64 output features of a 256-wide
-// layer (4 accumulators), so it already holds, in the accumulator
-// layout, the GELU derivatives of exactly the positions whose data gradient
-// it forms on the way back.  What leaves the block is what the
-// weight-gradient products and the reduction need: the activations and
-// gradients transposed ([feature][batch row], BF16), the column sums of each
+// of 16 rows per block (a batch of 4096 rows fills every CU): the feature
+// layer, the forward products of layers 2 to 4, the loss gradient of the
+// output layer, and the data gradients back through layers 3 and 2.  The
+// block has 16 waves, 4 on each SIMD (a wave alone on its SIMD issues only
+// every fifth cycle), and wave w computes output features 16 w .. 16 w + 15
+// of a 256-wide layer, so it already holds, in the accumulator layout, the
+// GELU derivatives of exactly the positions whose data gradient it forms on
+// the way back.  The activations and gradients that feed the next product
+// stay in LDS (two BF16 row-major tiles, rows padded to 264 so that the 16
+// rows of an operand fragment fall on different banks), and each product's
+// weight fragments are loaded into registers a layer ahead.  What leaves the
+// block is what the weight-gradient products and the reduction need: the
+// activations and gradients in fragment order over the batch (BF16; a tile
+// is half of the 32 rows of a fragment), the column sums of each
 // gradient over the tile (bias gradients), and the tile's weighted squared
 // error.  Activations and gradients are rounded to BF16 where they become
 // operands; every product accumulates in FP32, its MFMA steps in increasing
 // k.
+// At 4096 rows (one block per CU): 10.2 us, before 20.5 us with 4 waves a block
+// and row-major weights (16 rows of 64 bytes to a load).  Of its 20k cycles
+// about half go to the 448 KB of weights that every CU reads from L2 (some 40
+// bytes a cycle), the rest to the chain of 7 phases between barriers.  More
+// prefetching (W3 at the start, W3T a layer earlier) was slower: the waves wait
+// to issue loads then, instead of for their data.
 constexpr int kTileLd = kH + 8;
-constexpr int kTR = 16, kNI = kTR / 16;  // rows per tile, 16-row groups
+constexpr int kTR = 16;                  // rows per tile
+constexpr int kFbWaves = kH / 16;        // one 16-feature block of a layer per wave
 
 struct TrainArgs {
   const float *x;          // inputs [*][2]: batch row r is dataset row rows[r] (or r)
   const int64_t *rows;     // dataset rows of the batch, or NULL
   const float *tgt;        // targets [*][64], indexed like x
   const float *P;          // FP32 parameters (W1, b1 .. b4 read here)
-  const bf16 *W2, *W3, *W4;  // BF16 weights [out][in]
-  const bf16 *W3T, *W4T;     // BF16 transposes [in][out]
-  int64_t m;               // batch rows (a multiple of 16)
-  bf16 *a1T, *a2T, *a3T;   // [256][m]
-  bf16 *dz4T;              // [64][m]
-  bf16 *dz3T, *dz2T;       // [256][m]
+  WeightCopies W;
+  int m;                   // batch rows
+  int lsplit;              // log2 of the parts of the batch that k_gemm splits it in
+  bf16 *a1, *a2, *a3;      // [m / 32][16] fragments
+  bf16 *dz4;               // [m / 32][4] fragments
+  bf16 *dz3, *dz2;         // [m / 32][16] fragments
   float *cp4, *cp3, *cp2;  // [m/16][64], [m/16][256], [m/16][256]
   float *lpart;            // [m/16]
 };
 
-// The B operands of a tile product: weight rows c0 + 16 j + (l mod 16),
-// k = 32 s + 8 (l / 16) + 0..7 for every MFMA step s of K, from the row-major
-// weights (ld ldw).  Loaded a whole layer ahead: the weights do not depend on
-// the activations, so a layer's loads are issued before the previous layer's
-// epilogue and barrier, which hides their latency at one wave per SIMD.
-template <int NJ, int K>
-__device__ __forceinline__ void tile_weights(const bf16 *__restrict__ W, int64_t ldw, int c0,
-                                             int l, bf16x8 (&b)[K / 32][NJ]) {
-  const bf16 *wp = W + (int64_t)(c0 + (l & 15)) * ldw + (l >> 4) * 8;
+// The B operands of a tile product: the fragments of weight row block fb for
+// every MFMA step of K.  Loaded a whole layer ahead: the weights do not
+// depend on the activations, so a layer's loads are issued before the
+// previous layer's epilogue and barrier, which hides their latency.
+template <int K>
+__device__ __forceinline__ void tile_weights(const bf16 *__restrict__ W, int fb, int l,
+                                             bf16x8 (&b)[K / 32]) {
+  const bf16 *wp = W + fb * (K / 32) * kFrag + l * 8;
 #pragma unroll
-  for (int s = 0; s < K / 32; ++s)
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) b[s][j] = *(const bf16x8 *)(wp + 16 * j * ldw + 32 * s);
+  for (int s = 0; s < K / 32; ++s) b[s] = *(const bf16x8 *)(wp + s * kFrag);
 }
 
-// acc[i][j] = the tile's rows 16 i .. 16 i + 15 times the weight rows of
-// b[.][j] over k = 0 .. K, the A operands from the LDS tile, the MFMA steps
-// in increasing k.
-template <int NJ, int K>
-__device__ __forceinline__ void tile_product(const bf16 (*in)[kTileLd],
-                                             const bf16x8 (&b)[K / 32][NJ], int l,
-                                             f32x4 (&acc)[kNI][NJ]) {
+// The tile's 16 rows times the weight rows of b over k = 0 .. K, the A
+// operands from the LDS tile, the MFMA steps in increasing k.
+template <int K>
+__device__ __forceinline__ f32x4 tile_product(const bf16 (*in)[kTileLd],
+                                              const bf16x8 (&b)[K / 32], int l) {
   const int lr = l & 15, lk = (l >> 4) * 8;
+  f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 a[K / 32];
 #pragma unroll
-  for (int i = 0; i < kNI; ++i)
+  for (int s = 0; s < K / 32; ++s) a[s] = *(const bf16x8 *)&in[lr][32 * s + lk];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int s = 0; s < K / 32; ++s) {
-    bf16x8 a[kNI];
-#pragma unroll
-    for (int i = 0; i < kNI; ++i) a[i] = *(const bf16x8 *)&in[16 * i + lr][32 * s + lk];
-#pragma unroll
-    for (int i = 0; i < kNI; ++i)
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[s][j], acc[i][j], 0, 0, 0);
-  }
+  for (int s = 0; s < K / 32; ++s)
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b[s], acc, 0, 0, 0);
+  return acc;
+}
+
+// Rows 4 rq .. 4 rq + 3 of feature f of the tile (nf features wide) to its
+// place in the batch's fragments.
+__device__ __forceinline__ void put_rows(bf16 *F, int nf, int tile, int f, int rq, bf16x4 v) {
+  const int row = (tile & 1) * 16 + 4 * rq;
+  *(bf16x4 *)(F + ((tile >> 1) * (nf / 16) + (f >> 4)) * kFrag + frag_std(f, row)) = v;
 }
 
 // Column sums over the tile's rows of v (the accumulator layout: lane l
-// holds rows 16 i + 4 (l / 16) + q of column l mod 16): the lane's rows,
-// then the 4 lane groups, in a fixed order; lanes 0 .. 15 hold the sums.
-__device__ __forceinline__ float tile_colsum(const float (&v)[kNI][4]) {
+// holds rows 4 (l / 16) + q of column l mod 16): the lane's rows, then the 4
+// lane groups, in a fixed order; lanes 0 .. 15 hold the sums.
+__device__ __forceinline__ float tile_colsum(const float (&v)[4]) {
   float s0 = 0.f;
 #pragma unroll
-  for (int i = 0; i < kNI; ++i)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) s0 += v[i][q];
+  for (int q = 0; q < 4; ++q) s0 += v[q];
   s0 += __shfl_xor(s0, 16);
   s0 += __shfl_xor(s0, 32);
   return s0;
 }
 
-__global__ __launch_bounds__(256) void k_train_fb(TrainArgs g) {
+__global__ __launch_bounds__(64 * kFbWaves) void k_train_fb(TrainArgs g) {
   __shared__ bf16 act[2][kTR][kTileLd];
-  __shared__ float xs[kTR][2];
-  __shared__ float lw[4];
-  const int64_t m = g.m, r0 = (int64_t)blockIdx.x * kTR;
+  __shared__ float lw[kOut / 16];
+  // consecutive blocks (which go round the XCDs) take tiles of different
+  // parts of the batch, as k_gemm's blocks do
+  const int m = g.m, b = (int)blockIdx.x;
+  const int tile = (b & ((1 << g.lsplit) - 1)) * (m / kTR >> g.lsplit) + (b >> g.lsplit);
+  const int r0 = tile * kTR;
   const int t = threadIdx.x, w = t >> 6, l = t & 63;
-  const int lc = l & 15, lrow = (l >> 4) * 4;
-  bf16x8 bw[kH / 32][4];    // the next 256-wide product's weights
-  tile_weights<4, kH>(g.W2, kH, 64 * w, l, bw);
-  // biases and targets of the lane's output positions, loaded ahead
-  float b23[2][4], tq[kNI][4];
+  const int lc = l & 15, lg = l >> 4;
+  const int c = 16 * w + lc;    // the lane's output feature
+  // layer 1: wave w takes rows 4 (w / 4) .. + 3, lane l feature 64 (w mod 4) + l.
+  // The rows and inputs are the same in all lanes (scalar loads).
+  const int f = t & (kH - 1), rq = __builtin_amdgcn_readfirstlane(t / kH);
+  int64_t src[4], trow[4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    b23[0][j] = g.P[ob2 + 64 * w + 16 * j + lc];
-    b23[1][j] = g.P[ob3 + 64 * w + 16 * j + lc];
+  for (int q = 0; q < 4; ++q) {
+    src[q] = r0 + 4 * rq + q;
+    trow[q] = r0 + 4 * lg + q;
   }
-  const float b4c = g.P[ob4 + 16 * w + lc];
-#pragma unroll
-  for (int i = 0; i < kNI; ++i)
+  if (g.rows) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int64_t rr = r0 + 16 * i + lrow + q;
-      tq[i][q] = g.tgt[(g.rows ? g.rows[rr] : rr) * kOut + 16 * w + lc];
+      src[q] = g.rows[src[q]];
+      trow[q] = g.rows[trow[q]];
     }
-  if (t < kTR) {
-    const int64_t src = g.rows ? g.rows[r0 + t] : r0 + t;
-    xs[t][0] = g.x[2 * src];
-    xs[t][1] = g.x[2 * src + 1];
   }
-  __syncthreads();
-  // layer 1: thread t is feature t of the tile's rows
+  float xin[4][2];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    xin[q][0] = g.x[2 * src[q]];
+    xin[q][1] = g.x[2 * src[q] + 1];
+  }
+  const float w0 = g.P[oW1 + 2 * f], w1 = g.P[oW1 + 2 * f + 1], bb = g.P[ob1 + f];
+  // biases of the lane's output positions
+  const float b23[2] = {g.P[ob2 + c], g.P[ob3 + c]}, b4c = g.P[ob4 + (c & (kOut - 1))];
+  bf16x8 bw[kH / 32];           // the next 256-wide product's weights
+  tile_weights<kH>(g.W.W2, w, l, bw);
+  float tq[4] = {0.f, 0.f, 0.f, 0.f};
+  if (w < kOut / 16) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) tq[q] = g.tgt[trow[q] * kOut + c];
+  }
   {
-    const float w0 = g.P[oW1 + 2 * t], w1 = g.P[oW1 + 2 * t + 1], bb = g.P[ob1 + t];
-    bf16x8 col[kTR / 8];
+    bf16x4 col;
 #pragma unroll
-    for (int k = 0; k < kTR; ++k) {
-      const bf16 f = (bf16)feature_sin(fmaf(xs[k][1], w1, fmaf(xs[k][0], w0, bb)));
-      act[0][k][t] = f;
-      col[k >> 3][k & 7] = f;
+    for (int q = 0; q < 4; ++q) {
+      const bf16 v = (bf16)feature_sin(fmaf(xin[q][1], w1, fmaf(xin[q][0], w0, bb)));
+      act[0][4 * rq + q][f] = v;
+      col[q] = v;
     }
-#pragma unroll
-    for (int q = 0; q < kTR / 8; ++q) *(bf16x8 *)(g.a1T + (int64_t)t * m + r0 + 8 * q) = col[q];
+    put_rows(g.a1, kH, tile, f, rq, col);
   }
   __syncthreads();
   // layers 2 and 3: z = a W^T + b, a' = GELU(z); keep GELU'(z) for the way back
-  float gp[2][kNI][4][4];  // [layer 2, 3][i][j][q]
-  f32x4 acc[kNI][4];
-  bf16x8 bw4[kH / 32][1];   // layer 4's weights
+  float gp[2][4];  // [layer 2, 3][q]
+  f32x4 acc;
 #pragma unroll
   for (int L = 0; L < 2; ++L) {
-    bf16 *aT = L == 0 ? g.a2T : g.a3T;
-    tile_product<4, kH>(act[L], bw, l, acc);
+    acc = tile_product<kH>(act[L], bw, l);
     if (L == 0)
-      tile_weights<4, kH>(g.W3, kH, 64 * w, l, bw);
-    else
-      tile_weights<1, kH>(g.W4, kH, 16 * w, l, bw4);
+      tile_weights<kH>(g.W.W3, w, l, bw);
+    else if (w < kOut / 16)
+      tile_weights<kH>(g.W.W4, w, l, bw);
+    bf16x4 col;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int c = 64 * w + 16 * j + lc;
-      const float bj = b23[L][j];
-#pragma unroll
-      for (int i = 0; i < kNI; ++i) {
-        bf16x4 col;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float z = acc[i][j][q] + bj;
-          gp[L][i][j][q] = gelu_grad_f(z);
-          const bf16 a = (bf16)gelu_f(z);
-          act[1 - L][16 * i + lrow + q][c] = a;
-          col[q] = a;
-        }
-        *(bf16x4 *)(aT + (int64_t)c * m + r0 + 16 * i + lrow) = col;
-      }
+    for (int q = 0; q < 4; ++q) {
+      const float z = acc[q] + b23[L];
+      gp[L][q] = gelu_grad_f(z);
+      const bf16 a = (bf16)gelu_f(z);
+      act[1 - L][4 * lg + q][c] = a;
+      col[q] = a;
     }
+    put_rows(L == 0 ? g.a2 : g.a3, kH, tile, c, lg, col);
     __syncthreads();
   }
-  // layer 4 and the loss gradient 2 w_c (out - t) / (m * 64); wave w takes
-  // the output columns 16 w .. 16 w + 15
-  bf16x8 bwt[kOut / 32][4];  // W4^T for the first product back
-  {
-    f32x4 acc4[kNI][1];
-    tile_product<1, kH>(act[0], bw4, l, acc4);
-    tile_weights<4, kOut>(g.W4T, kOut, 64 * w, l, bwt);
-    const int c = 16 * w + lc;
-    const float bj = b4c;
+  // layer 4 and the loss gradient 2 w_c (out - t) / (m * 64): waves 0 .. 3
+  // take the 64 output columns
+  bf16x8 bwt[kOut / 32];  // W4^T for the first product back
+  tile_weights<kOut>(g.W.W4T, w, l, bwt);
+  if (w < kOut / 16) {
+    acc = tile_product<kH>(act[0], bw, l);
     const float wc = out_weight(c);
-    const float scale = 2.0f * wc / (float)(m * kOut);
-    float gv[kNI][4];
+    const float scale = 2.0f * wc / (float)((int64_t)m * kOut);
+    float gv[4];
     float sq = 0.f;
+    bf16x4 col;
 #pragma unroll
-    for (int i = 0; i < kNI; ++i) {
-      bf16x4 col;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int rr = 16 * i + lrow + q;
-        const float d = (acc4[i][0][q] + bj) - tq[i][q];
-        sq = fmaf(wc * d, d, sq);
-        gv[i][q] = scale * d;
-        const bf16 gb = (bf16)gv[i][q];
-        act[1][rr][c] = gb;
-        col[q] = gb;
-      }
-      *(bf16x4 *)(g.dz4T + (int64_t)c * m + r0 + 16 * i + lrow) = col;
+    for (int q = 0; q < 4; ++q) {
+      const float d = (acc[q] + b4c) - tq[q];
+      sq = fmaf(wc * d, d, sq);
+      gv[q] = scale * d;
+      const bf16 gb = (bf16)gv[q];
+      act[1][4 * lg + q][c] = gb;
+      col[q] = gb;
     }
+    put_rows(g.dz4, kOut, tile, c, lg, col);
     const float cs = tile_colsum(gv);
-    if (l < 16) g.cp4[(int64_t)blockIdx.x * kOut + c] = cs;
+    if (l < 16) g.cp4[tile * kOut + c] = cs;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off);
     if (l == 0) lw[w] = sq;
   }
   __syncthreads();
-  if (t == 0) g.lpart[blockIdx.x] = ((lw[0] + lw[1]) + lw[2]) + lw[3];
+  if (t == 0) g.lpart[tile] = ((lw[0] + lw[1]) + lw[2]) + lw[3];
   // back through layer 3 (dA3 = dZ4 W4, K = 64), then layer 2 (dA2 = dZ3 W3)
 #pragma unroll
   for (int L = 1; L >= 0; --L) {
     if (L == 1) {
-      tile_product<4, kOut>(act[1], bwt, l, acc);
-      tile_weights<4, kH>(g.W3T, kH, 64 * w, l, bw);
+      acc = tile_product<kOut>(act[1], bwt, l);
+      tile_weights<kH>(g.W.W3T, w, l, bw);
     } else {
-      tile_product<4, kH>(act[0], bw, l, acc);
+      acc = tile_product<kH>(act[0], bw, l);
     }
-    bf16 *dT = L == 1 ? g.dz3T : g.dz2T;
-    float *cp = L == 1 ? g.cp3 : g.cp2;
+    float dz[4];
+    bf16x4 col;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int c = 64 * w + 16 * j + lc;
-      float dz[kNI][4];
-#pragma unroll
-      for (int i = 0; i < kNI; ++i) {
-        bf16x4 col;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          dz[i][q] = acc[i][j][q] * gp[L][i][j][q];
-          const bf16 gb = (bf16)dz[i][q];
-          if (L == 1) act[0][16 * i + lrow + q][c] = gb;
-          col[q] = gb;
-        }
-        *(bf16x4 *)(dT + (int64_t)c * m + r0 + 16 * i + lrow) = col;
-      }
-      const float cs = tile_colsum(dz);
-      if (l < 16) cp[(int64_t)blockIdx.x * kH + c] = cs;
+    for (int q = 0; q < 4; ++q) {
+      dz[q] = acc[q] * gp[L][q];
+      const bf16 gb = (bf16)dz[q];
+      if (L == 1) act[0][4 * lg + q][c] = gb;
+      col[q] = gb;
     }
+    put_rows(L == 1 ? g.dz3 : g.dz2, kH, tile, c, lg, col);
+    const float cs = tile_colsum(dz);
+    if (l < 16) (L == 1 ? g.cp3 : g.cp2)[tile * kH + c] = cs;
     if (L == 1) __syncthreads();
   }
 }
 
 // ---------------------------------------------------------------- small kernels
-// Gradients of all parameters from the partial sums of one batch of m rows
-// (T = m / 16 row tiles, S weight-gradient splits), each summed in a fixed
-// order, and the batch loss; acc (optional) accumulates the loss.
+// Gradients of all trained parameters (W2 onwards) from the partial sums of
+// one batch of m rows (T = m / 16 row tiles, S weight-gradient splits), each
+// summed in a fixed order, and the batch loss; acc (optional) accumulates the
+// loss.  ADAM: each summed gradient also takes its Adam step on the FP32
+// master parameters at once, and the BF16 copies follow the updated values.
 struct GradParts {
   const float *w2, *w3;           // [S][256][256]
   const float *b2, *b3;           // [T][256]
@@ -432,155 +495,173 @@ struct GradParts {
   const float *b4;                // [T][64]
   const float *lpart;             // [T]
 };
-constexpr int64_t kNW = 2 * kH * kH + kOut * kH;   // weights of the MFMA layers
-constexpr int kNColSums = 5 * kH + kOut + 1;        // W1 (2 x 256), b1..b4, loss
-constexpr int kReduceWBlocks = (int)((kNW + 255) / 256);
-// Adam on the FP32 master parameters (Kingma and Ba, 2015); the BF16 copies
-// of W2, W3, W4 and their transposes follow the updated values.  The step
-// count is t = t_base + step + 1; with hyper != NULL the learning rate,
-// betas, epsilon and t_base are read from device memory (hyper[0..4]), so a
-// captured epoch replays with new values.
 struct AdamArgs {
   float *P, *Mm, *V;
-  const double *hyper;
-  double lr, b1, b2, eps, t_base;
-  int step;
-  bf16 *W2, *W2T, *W3, *W3T, *W4, *W4T;
+  const float *h;                 // the step's constants (adam_constants)
+  WeightCopies W;
 };
 
-// The block's hyper-parameters and bias corrections (two FP64 powers, in
-// thread 0): h = lr, b1, b2, eps, 1 / (1 - b1^t), 1 / (1 - b2^t).
-__device__ __forceinline__ void adam_setup(const AdamArgs &a, float *h) {
-  if (threadIdx.x == 0) {
-    double lr = a.lr, b1 = a.b1, b2 = a.b2, eps = a.eps, t0 = a.t_base;
-    if (a.hyper) {
-      lr = a.hyper[0];
-      b1 = a.hyper[1];
-      b2 = a.hyper[2];
-      eps = a.hyper[3];
-      t0 = a.hyper[4];
-    }
-    const double t = t0 + (double)a.step + 1.0;
-    h[0] = (float)lr;
-    h[1] = (float)b1;
-    h[2] = (float)b2;
-    h[3] = (float)eps;
-    h[4] = (float)(1.0 / (1.0 - pow(b1, t)));
-    h[5] = (float)(1.0 / (1.0 - pow(b2, t)));
-  }
-  __syncthreads();
-}
-
-// One parameter i (a trained one: W2 onwards) with gradient gr.
-__device__ __forceinline__ void adam_one(const AdamArgs &a, const float *h, int64_t i, float gr) {
+// One parameter p with moments m and v and gradient gr.
+__device__ __forceinline__ void adam_one(const float (&h)[6], float gr, float &p, float &m,
+                                         float &v) {
   const float lr = h[0], b1 = h[1], b2 = h[2], eps = h[3], c1 = h[4], c2 = h[5];
-  const float m = fmaf(b1, a.Mm[i], (1.0f - b1) * gr);
-  const float v = fmaf(b2, a.V[i], (1.0f - b2) * gr * gr);
-  a.Mm[i] = m;
-  a.V[i] = v;
-  const float w = a.P[i] - lr * (m * c1) / (sqrtf(v * c2) + eps);
-  a.P[i] = w;
-  const bf16 wb = (bf16)w;
-  if (i >= oW2 && i < ob2) {
-    const int64_t k = i - oW2, o = k / kH, in = k % kH;
-    a.W2[k] = wb;
-    a.W2T[in * kH + o] = wb;
-  } else if (i >= oW3 && i < ob3) {
-    const int64_t k = i - oW3, o = k / kH, in = k % kH;
-    a.W3[k] = wb;
-    a.W3T[in * kH + o] = wb;
-  } else if (i >= oW4 && i < ob4) {
-    const int64_t k = i - oW4, o = k / kH, in = k % kH;
-    a.W4[k] = wb;
-    a.W4T[in * kOut + o] = wb;
-  }
+  m = fmaf(b1, m, (1.0f - b1) * gr);
+  v = fmaf(b2, v, (1.0f - b2) * gr * gr);
+  p = p - lr * (m * c1) / (sqrtf(v * c2) + eps);
 }
 
-// Blocks [0, kReduceWBlocks): one weight per thread (S partials).  The
-// following blocks: one wave per tile-summed entry (T partials: lane l takes
-// tiles l, l + 64, ..., then a butterfly over the wave).  ADAM: each summed
-// gradient also takes its Adam step at once (the feature layer's entries,
-// whose gradient is 0, and the loss excepted).
+// Weights [o][in .. in + 3] of a layer: a block takes 16 rows and 64 columns,
+// 2 whole fragments of the copies.
+constexpr int kRedTiles = kH / 16 * (kH / 64), kRedTiles4 = kOut / 16 * (kH / 64);
+constexpr int kRedWBlocks = 2 * kRedTiles + kRedTiles4;
+constexpr int kRedCols = 16;   // tile-summed columns (b2, b3, b4) of a block
+constexpr int kRedBlocks = kRedWBlocks + (2 * kH + kOut) / kRedCols + 1;
+
+template <int LAYER, bool ADAM>
+__device__ __forceinline__ void reduce_weights(const float *__restrict__ part, int S, int64_t base,
+                                               int tile, float *G, const AdamArgs &ad) {
+  const int64_t stride = (LAYER == 4 ? kOut : kH) * kH;
+  const int o = (tile / (kH / 64)) * 16 + ((int)threadIdx.x >> 4);
+  const int in = (tile % (kH / 64)) * 64 + 4 * ((int)threadIdx.x & 15);
+  const int64_t k = (int64_t)o * kH + in, i = base + k;
+  f32x4 p, m, v, d[kSplit];
+#pragma unroll
+  for (int u = 0; u < kSplit; ++u) d[u] = *(const f32x4 *)(part + (u < S ? u : 0) * stride + k);
+  float h[6];
+  if (ADAM) {
+    p = *(const f32x4 *)(ad.P + i);
+    m = *(const f32x4 *)(ad.Mm + i);
+    v = *(const f32x4 *)(ad.V + i);
+#pragma unroll
+    for (int u = 0; u < 6; ++u) h[u] = ad.h[u];
+  }
+  f32x4 g{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int u = 0; u < kSplit; ++u)
+    if (u < S) g += d[u];
+  *(f32x4 *)(G + i) = g;
+  if (!ADAM) return;
+  bf16x4 wb;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float pq = p[q], mq = m[q], vq = v[q];
+    adam_one(h, g[q], pq, mq, vq);
+    p[q] = pq;
+    m[q] = mq;
+    v[q] = vq;
+    wb[q] = (bf16)pq;
+  }
+  *(f32x4 *)(ad.P + i) = p;
+  *(f32x4 *)(ad.Mm + i) = m;
+  *(f32x4 *)(ad.V + i) = v;
+  put_weights<LAYER>(ad.W, o, in, wb);
+}
+
+// Blocks [0, kRedWBlocks): weights.  The next blocks: kRedCols tile-summed
+// columns each, 16 threads a column.  The order of a column's sum: 64 partial
+// sums l, of tiles l, l + 64, ..., then a tree that adds l + 32, 16, .. 1;
+// thread t holds those with l = t / 16 mod 16 of column t mod 16.  The last
+// block: the loss, in the same order.  Bound by the latency of one round of
+// loads (8 MB in all, each thread's in flight at once).  At 4096 rows: 4.4 us,
+// before 8.7 us with the Adam constants formed in every block and a column's
+// tiles read by the lanes of one wave, 64 lines to a load.
 template <bool ADAM>
 __global__ __launch_bounds__(256) void k_reduce_grads(GradParts p, int64_t T, int S,
                                                       float count, float *G, float *loss,
                                                       float *acc, int first, AdamArgs ad) {
-  __shared__ float h[6];
-  if (ADAM) adam_setup(ad, h);
-  if ((int)blockIdx.x < kReduceWBlocks) {
-    const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (w >= kNW) return;
-    const float *src;
-    int64_t o, stride;
-    if (w < kH * kH) {
-      src = p.w2 + w; o = oW2 + w; stride = kH * kH;
-    } else if (w < 2 * kH * kH) {
-      src = p.w3 + (w - kH * kH); o = oW3 + (w - kH * kH); stride = kH * kH;
-    } else {
-      src = p.w4 + (w - 2 * kH * kH); o = oW4 + (w - 2 * kH * kH); stride = kOut * kH;
-    }
-    float g = 0.f;
-    for (int k = 0; k < S; ++k) g += src[k * stride];
-    G[o] = g;
-    if (ADAM) adam_one(ad, h, o, g);
+  const int b = (int)blockIdx.x;
+  if (b < kRedTiles) {
+    reduce_weights<2, ADAM>(p.w2, S, oW2, b, G, ad);
     return;
   }
-  const int e = ((int)blockIdx.x - kReduceWBlocks) * 4 + (threadIdx.x >> 6);
-  const int l = threadIdx.x & 63;
-  if (e >= kNColSums) return;
-  const float *src;
-  int64_t ld;
-  float *dst;
-  if (e < kH) {          // the fixed feature layer: no partial sums, gradient 0
-    src = nullptr; ld = 0; dst = G + oW1 + 2 * e;
-  } else if (e < 2 * kH) {
-    src = nullptr; ld = 0; dst = G + oW1 + 2 * (e - kH) + 1;
-  } else if (e < 3 * kH) {
-    src = nullptr; ld = 0; dst = G + ob1 + (e - 2 * kH);
-  } else if (e < 4 * kH) {
-    src = p.b2 + (e - 3 * kH); ld = kH; dst = G + ob2 + (e - 3 * kH);
-  } else if (e < 5 * kH) {
-    src = p.b3 + (e - 4 * kH); ld = kH; dst = G + ob3 + (e - 4 * kH);
-  } else if (e < 5 * kH + kOut) {
-    src = p.b4 + (e - 5 * kH); ld = kOut; dst = G + ob4 + (e - 5 * kH);
-  } else {
-    src = p.lpart; ld = 1; dst = nullptr;
+  if (b < 2 * kRedTiles) {
+    reduce_weights<3, ADAM>(p.w3, S, oW3, b - kRedTiles, G, ad);
+    return;
   }
-  float v = 0.f;
-  if (src)
-    for (int64_t t = l; t < T; t += 64) v += src[t * ld];
+  if (b < kRedWBlocks) {
+    reduce_weights<4, ADAM>(p.w4, S, oW4, b - 2 * kRedTiles, G, ad);
+    return;
+  }
+  if (b == kRedBlocks - 1) {
+    if (threadIdx.x >= 64) return;
+    float v = 0.f;
+    for (int64_t t = threadIdx.x; t < T; t += 64) v += p.lpart[t];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  if (l == 0) {
-    if (dst) {
-      *dst = v;
-      if (ADAM && src) adam_one(ad, h, dst - G, v);
-    } else {
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if (threadIdx.x == 0) {
       const float lv = v / count;
       *loss = lv;
       if (acc) *acc = first ? lv : *acc + lv;
     }
+    return;
+  }
+  __shared__ float red[4][64];
+  const int e0 = (b - kRedWBlocks) * kRedCols, e = e0 + ((int)threadIdx.x & 15);
+  const int l0 = (int)threadIdx.x >> 4;
+  const float *src;
+  int64_t ld, i;
+  if (e0 < kH) {
+    src = p.b2 + e; ld = kH; i = ob2 + e;
+  } else if (e0 < 2 * kH) {
+    src = p.b3 + (e - kH); ld = kH; i = ob3 + (e - kH);
+  } else {
+    src = p.b4 + (e - 2 * kH); ld = kOut; i = ob4 + (e - 2 * kH);
+  }
+  float h[6], pe = 0.f, me = 0.f, ve = 0.f;
+  if (ADAM && threadIdx.x < kRedCols) {
+    pe = ad.P[i];
+    me = ad.Mm[i];
+    ve = ad.V[i];
+#pragma unroll
+    for (int u = 0; u < 6; ++u) h[u] = ad.h[u];
+  }
+  float v[4] = {0.f, 0.f, 0.f, 0.f};
+  for (int64_t t = 0; t < T; t += 256) {
+    float d[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const int64_t r = t + l0 + 16 * k;
+      d[k] = src[(r < T ? r : T - 1) * ld];
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (t + l0 + 16 * k < T) v[k & 3] += d[k];
+  }
+  const float s = (v[0] + v[2]) + (v[1] + v[3]);   // l + 32, l + 16
+  red[threadIdx.x >> 6][threadIdx.x & 63] = s;
+  __syncthreads();
+  if (threadIdx.x >= 64) return;
+  const int l = threadIdx.x;
+  float gr = (red[0][l] + red[2][l]) + (red[1][l] + red[3][l]);   // l + 8, l + 4
+  gr += __shfl_xor(gr, 32);                                        // l + 2
+  gr += __shfl_xor(gr, 16);                                        // l + 1
+  if (l >= kRedCols) return;
+  G[i] = gr;
+  if (ADAM) {
+    adam_one(h, gr, pe, me, ve);
+    ad.P[i] = pe;
+    ad.Mm[i] = me;
+    ad.V[i] = ve;
   }
 }
 
-// BF16 copies of W2, W3, W4 and their transposes from the master weights.
-__global__ void k_refresh(const float *__restrict__ P, bf16 *W2, bf16 *W2T, bf16 *W3, bf16 *W3T,
-                          bf16 *W4, bf16 *W4T) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < kH * kH) {
-    const int64_t o = i / kH, in = i % kH;
-    const bf16 a = (bf16)P[oW2 + i], b = (bf16)P[oW3 + i];
-    W2[i] = a;
-    W2T[in * kH + o] = a;
-    W3[i] = b;
-    W3T[in * kH + o] = b;
+// The BF16 copies of W2, W3, W4 from the master weights: 4 weights a thread.
+__global__ void k_refresh(const float *__restrict__ P, WeightCopies W) {
+  const int i = ((int)blockIdx.x * (int)blockDim.x + (int)threadIdx.x) * 4;
+  if (i >= kH * kH) return;
+  const int o = i / kH, in = i % kH;
+  bf16x4 a, b, c;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    a[q] = (bf16)P[oW2 + i + q];
+    b[q] = (bf16)P[oW3 + i + q];
   }
-  if (i < kOut * kH) {
-    const int64_t o = i / kH, in = i % kH;
-    const bf16 c = (bf16)P[oW4 + i];
-    W4[i] = c;
-    W4T[in * kOut + o] = c;
-  }
+  put_weights<2>(W, o, in, a);
+  put_weights<3>(W, o, in, b);
+  if (i >= kOut * kH) return;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) c[q] = (bf16)P[oW4 + i + q];
+  put_weights<4>(W, o, in, c);
 }
 
 // Sweep inputs -> normalised network inputs: (p_A, ln f) mapped to [-1, 1]
@@ -634,27 +715,12 @@ __global__ void k_targets(const double *__restrict__ rec, int64_t n, const doubl
 //     k slot 8 g + s  <->  feature 32 c + 16 (s / 4) + 4 g + s mod 4,
 // so the weights of layers 3 and 4 are read with their columns permuted the
 // same way; the feature layer's fragments are formed directly in the standard
-// order.  Weights come from L2 (288 KB in all) in fragment order (k_frag_layout),
+// order.  Weights come from L2 (288 KB in all) in fragment order,
 // each fragment serving both point blocks; between layers the activations wait
 // in the wave's slice of LDS.  The arithmetic of every element is the training
 // path's (same features, GELU and roundings to BF16) except for the order of
 // the FP32 sums: the bias starts the accumulation here, and the k order inside
 // an MFMA differs for layers 3 and 4.
-
-// The weights of one layer in fragment order, so that each wave load of an A
-// fragment is 1 KB contiguous: Wf[((fb * 8 + c) * 64 + lane) * 8 + s] holds
-// W[16 fb + lane mod 16][k], k = 32 c + 8 g + s in the standard order, or
-// k = 32 c + 16 (s / 4) + 4 g + s mod 4 in the permuted one (g = lane / 16).
-__global__ void k_frag_layout(const bf16 *__restrict__ W, int64_t rows, int permuted,
-                              bf16 *__restrict__ Wf) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= rows * kH) return;
-  const int s = (int)(e & 7), lane = (int)(e >> 3) & 63;
-  const int64_t c = (e >> 9) & 7, fb = e >> 12;
-  const int g = lane >> 4;
-  const int64_t k = permuted ? 32 * c + 16 * (s >> 2) + 4 * g + (s & 3) : 32 * c + 8 * g + s;
-  Wf[e] = W[(16 * fb + (lane & 15)) * kH + k];
-}
 
 struct FusedArgs {
   int64_t n;                       // points
@@ -663,8 +729,7 @@ struct FusedArgs {
   const float *x;                  // forward: normalised inputs [n][2]
   float *out;                      // forward: network outputs [n][64]
   const float *P;                  // master parameters (W1, b1, b2, b3, b4)
-  const bf16 *W2f, *W3f, *W4f;     // BF16 weights in fragment order (k_frag_layout;
-                                   // 3 and 4 k-permuted)
+  const bf16 *W2f, *W3f, *W4f;     // BF16 weights in fragment order (3 and 4 k-permuted)
   // screen epilogue (k_screen_epi's rule)
   const float *mean, *stdv;
   float margin, spread, flag_margin, label_margin;
@@ -1017,17 +1082,16 @@ struct sur_ctx {
   bool have_norm = false;
   // parameters and optimiser state
   float *P = nullptr, *G = nullptr, *Mm = nullptr, *V = nullptr;
-  bf16 *W2 = nullptr, *W2T = nullptr, *W3 = nullptr, *W3T = nullptr, *W4 = nullptr,
-       *W4T = nullptr;
+  WeightCopies W = {};
   float *d_mean = nullptr, *d_std = nullptr;
   double *d_dmean = nullptr, *d_dstd = nullptr;
-  // one batch: inputs and targets, the activations and gradients
-  // transposed ([feature][batch row]) for the weight-gradient products
+  // one batch: inputs and targets, the activations and gradients in
+  // fragment order over the batch for the weight-gradient products
   float *x = nullptr, *tgt = nullptr;
-  bf16 *a1T = nullptr, *a2T = nullptr, *a3T = nullptr;
-  bf16 *dz4bT = nullptr, *dz3bT = nullptr, *dz2bT = nullptr;
+  bf16 *a1 = nullptr, *a2 = nullptr, *a3 = nullptr;
+  bf16 *dz4 = nullptr, *dz3 = nullptr, *dz2 = nullptr;
   // partial sums of the gradients: split-K weight products, per-16-row-tile
-  // column sums (biases, layer-1 weights), loss
+  // column sums (biases), loss
   float *part2 = nullptr, *part3 = nullptr, *part4 = nullptr;
   float *cp2 = nullptr, *cp3 = nullptr,
         *cp4 = nullptr;
@@ -1050,24 +1114,21 @@ struct sur_ctx {
   int64_t ep_n = 0, ep_batch = 0;
   double *hyper = nullptr;   // device: lr, beta1, beta2, eps, t_base
   double hyper_host[5] = {0, 0, 0, 0, 0};
-  // inference: W2, W3, W4 in fragment order (k_frag_layout), and staging of
-  // host inputs and outputs (sur_forward from host memory: kInferRows rows,
-  // allocated on first use)
-  bf16 *W2f = nullptr, *W3f = nullptr, *W4f = nullptr;
+  float *adam_h = nullptr;   // device: the running step's constants (adam_constants)
+  // inference: staging of host inputs and outputs (sur_forward from host
+  // memory: kInferRows rows, allocated on first use)
   float *ix = nullptr, *iout = nullptr;
 };
 
 namespace {
 
-constexpr int kSplit = 8;   // largest batch split of the weight-gradient products
-
 // Batch split of a weight-gradient product: chunks of 256 rows where the
 // batch allows (at most kSplit of them), else chunks of a multiple of 64 rows
-// (m is a multiple of 64).
-int wgrad_split(int64_t m) {
-  for (int s = kSplit; s > 1; s >>= 1)
-    if (m % (64 * s) == 0 && m / s >= 256) return s;
-  return 1;
+// (m is a multiple of 64).  Returns log2 of the split.
+int wgrad_lsplit(int64_t m) {
+  for (int ls = kLSplit; ls > 0; --ls)
+    if (m % (64 << ls) == 0 && (m >> ls) >= 256) return ls;
+  return 0;
 }
 
 thread_local std::string g_serr;
@@ -1103,35 +1164,22 @@ hipError_t alloc(T **p, int64_t count) {
 
 unsigned nblk(int64_t count, int b) { return (unsigned)((count + b - 1) / b); }
 
-// R, C multiples of 32; K / split a multiple of 64.
-// The three products of bt.g in one launch (each R, C a multiple of 32, the
-// same K with K / split a multiple of 64).
-hipError_t gemm3(hipStream_t st, GemmBatch bt, int split) {
-  bt.split = split;
-  int64_t total = 0;
+// The three products of bt.g (each R a multiple of 32) over m rows of the
+// batch in one launch, m / split a multiple of 64 (m <= 65536).
+hipError_t gemm3(hipStream_t st, GemmBatch bt, int64_t m, int lsplit) {
+  bt.lsplit = lsplit;
+  bt.kchunk = (int)(m >> lsplit);
+  int total = 0;
   for (int p = 0; p < 3; ++p) {
-    bt.nblk[p] = (bt.g[p].R / kTile) * (bt.g[p].C / kTile) * split;
-    total += bt.nblk[p];
+    bt.ntile[p] = (bt.g[p].R / kTile) * (kH / kTile);
+    total += bt.ntile[p] << lsplit;
   }
-  if ((bt.g[0].K / split) % 256 == 0)
+  total += 1;   // the Adam constants
+  if (bt.kchunk % 256 == 0)
     hipLaunchKernelGGL((k_gemm<8>), dim3((unsigned)total), dim3(64), 0, st, bt);
   else
     hipLaunchKernelGGL((k_gemm<2>), dim3((unsigned)total), dim3(64), 0, st, bt);
   return hipGetLastError();
-}
-
-GemmArgs gargs(const bf16 *X, int64_t ldx, const bf16 *Y, int64_t ldy, int64_t R, int64_t C,
-               int64_t K) {
-  GemmArgs g;
-  std::memset(&g, 0, sizeof(g));
-  g.X = X;
-  g.ldx = ldx;
-  g.Y = Y;
-  g.ldy = ldy;
-  g.R = R;
-  g.C = C;
-  g.K = K;
-  return g;
 }
 
 constexpr int64_t kInferRows = 65536;
@@ -1161,20 +1209,13 @@ hipError_t reserve_scan(sur_ctx *s, int64_t n) {
   return e;
 }
 
-// The fragment-order weight copies of the current parameters, then the fused
-// inference of n points (n > 0).
+// The fused inference of n points (n > 0).
 hipError_t fused(sur_ctx *s, FusedArgs a, bool screen) {
   hipStream_t st = s->stream;
-  hipLaunchKernelGGL(k_frag_layout, dim3(nblk(kH * kH, 256)), dim3(256), 0, st, s->W2,
-                     (int64_t)kH, 0, s->W2f);
-  hipLaunchKernelGGL(k_frag_layout, dim3(nblk(kH * kH, 256)), dim3(256), 0, st, s->W3,
-                     (int64_t)kH, 1, s->W3f);
-  hipLaunchKernelGGL(k_frag_layout, dim3(nblk(kOut * kH, 256)), dim3(256), 0, st, s->W4,
-                     (int64_t)kOut, 1, s->W4f);
   a.P = s->P;
-  a.W2f = s->W2f;
-  a.W3f = s->W3f;
-  a.W4f = s->W4f;
+  a.W2f = s->W.W2;
+  a.W3f = s->W.W3p;
+  a.W4f = s->W.W4p;
   const dim3 grid(nblk(a.n, 128));   // 4 waves of 32 points
   if (screen)
     hipLaunchKernelGGL(k_fused<true>, grid, dim3(256), 0, st, a);
@@ -1183,27 +1224,10 @@ hipError_t fused(sur_ctx *s, FusedArgs a, bool screen) {
   return hipGetLastError();
 }
 
-// Adam's arguments for the handle's parameters: hyper-parameters from
-// device memory (hyper != NULL, a captured step `step`) or the handle's.
-AdamArgs adam_args(sur_ctx *s, const double *hyper, int step) {
-  AdamArgs a;
-  a.P = s->P;
-  a.Mm = s->Mm;
-  a.V = s->V;
-  a.hyper = hyper;
-  a.lr = s->lr;
-  a.b1 = s->b1;
-  a.b2 = s->b2;
-  a.eps = s->eps;
-  a.t_base = (double)s->t;
-  a.step = step;
-  a.W2 = s->W2;
-  a.W2T = s->W2T;
-  a.W3 = s->W3;
-  a.W3T = s->W3T;
-  a.W4 = s->W4;
-  a.W4T = s->W4T;
-  return a;
+// The source of a step's Adam constants: hyper-parameters from device memory
+// (hyper != NULL, a captured step `step`) or the handle's.
+AdamHyper adam_hyper(sur_ctx *s, const double *hyper, int step) {
+  return AdamHyper{hyper, s->lr, s->b1, s->b2, s->eps, (double)s->t, step, s->adam_h};
 }
 
 // One batch's loss and gradients of all parameters into s->G and s->loss:
@@ -1214,51 +1238,46 @@ AdamArgs adam_args(sur_ctx *s, const double *hyper, int step) {
 // (first: starts it).
 hipError_t train_batch(sur_ctx *s, int64_t m, const float *x, const float *tgt,
                        const int64_t *rows, float *loss_acc = nullptr, bool first = true,
-                       const AdamArgs *ad = nullptr) {
+                       const AdamHyper *ad = nullptr) {
   hipStream_t st = s->stream;
   hipError_t e;
-  const int split = wgrad_split(m);
+  const int lsplit = wgrad_lsplit(m), split = 1 << lsplit;
   const int64_t T = m / kTR;
   TrainArgs a;
   a.x = x;
   a.rows = rows;
   a.tgt = tgt;
   a.P = s->P;
-  a.W2 = s->W2;
-  a.W3 = s->W3;
-  a.W4 = s->W4;
-  a.W3T = s->W3T;
-  a.W4T = s->W4T;
-  a.m = m;
-  a.a1T = s->a1T;
-  a.a2T = s->a2T;
-  a.a3T = s->a3T;
-  a.dz4T = s->dz4bT;
-  a.dz3T = s->dz3bT;
-  a.dz2T = s->dz2bT;
+  a.W = s->W;
+  a.m = (int)m;
+  a.lsplit = lsplit;
+  a.a1 = s->a1;
+  a.a2 = s->a2;
+  a.a3 = s->a3;
+  a.dz4 = s->dz4;
+  a.dz3 = s->dz3;
+  a.dz2 = s->dz2;
   a.cp4 = s->cp4;
   a.cp3 = s->cp3;
   a.cp2 = s->cp2;
   a.lpart = s->lpart;
-  hipLaunchKernelGGL(k_train_fb, dim3((unsigned)T), dim3(256), 0, st, a);
+  hipLaunchKernelGGL(k_train_fb, dim3((unsigned)T), dim3(64 * kFbWaves), 0, st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   GemmBatch bt;
-  bt.g[0] = gargs(s->dz4bT, m, s->a3T, m, kOut, kH, m);
-  bt.g[0].out_f32 = s->part4;
-  bt.g[1] = gargs(s->dz3bT, m, s->a2T, m, kH, kH, m);
-  bt.g[1].out_f32 = s->part3;
-  bt.g[2] = gargs(s->dz2bT, m, s->a1T, m, kH, kH, m);
-  bt.g[2].out_f32 = s->part2;
-  if ((e = gemm3(st, bt, split)) != hipSuccess) return e;
+  bt.g[0] = GemmArgs{s->dz4, s->a3, kOut, s->part4};
+  bt.g[1] = GemmArgs{s->dz3, s->a2, kH, s->part3};
+  bt.g[2] = GemmArgs{s->dz2, s->a1, kH, s->part2};
+  bt.ad = ad ? *ad : AdamHyper{};
+  if ((e = gemm3(st, bt, m, lsplit)) != hipSuccess) return e;
   GradParts p{s->part2, s->part3, s->cp2, s->cp3, s->part4, s->cp4, s->lpart};
-  const dim3 rg(kReduceWBlocks + (kNColSums + 3) / 4);
+  const AdamArgs aa{s->P, s->Mm, s->V, s->adam_h, s->W};
+  const dim3 rg(kRedBlocks);
   if (ad)
     hipLaunchKernelGGL(k_reduce_grads<true>, rg, dim3(256), 0, st, p, T, split,
-                       (float)(m * kOut), s->G, s->loss, loss_acc, first ? 1 : 0, *ad);
+                       (float)(m * kOut), s->G, s->loss, loss_acc, first ? 1 : 0, aa);
   else
     hipLaunchKernelGGL(k_reduce_grads<false>, rg, dim3(256), 0, st, p, T, split,
-                       (float)(m * kOut), s->G, s->loss, loss_acc, first ? 1 : 0,
-                       adam_args(s, nullptr, 0));
+                       (float)(m * kOut), s->G, s->loss, loss_acc, first ? 1 : 0, aa);
   return hipGetLastError();
 }
 
@@ -1270,8 +1289,7 @@ void free_epoch_graph(sur_ctx *s) {
 }
 
 hipError_t refresh(sur_ctx *s) {
-  hipLaunchKernelGGL(k_refresh, dim3(nblk(kH * kH, 256)), dim3(256), 0, s->stream, s->P, s->W2,
-                     s->W2T, s->W3, s->W3T, s->W4, s->W4T);
+  hipLaunchKernelGGL(k_refresh, dim3(nblk(kH * kH / 4, 256)), dim3(256), 0, s->stream, s->P, s->W);
   return hipGetLastError();
 }
 
@@ -1322,7 +1340,7 @@ int ensure_epoch_graph(sur_ctx *s, const float *x, const float *y, int64_t n, co
   for (int64_t b = 0; e == hipSuccess && b < nb; ++b) {
     const int64_t *rows = perm + b * batch;
     // the step's Adam update from the hyper-parameters in s->hyper
-    const AdamArgs ad = adam_args(s, s->hyper, (int)b);
+    const AdamHyper ad = adam_hyper(s, s->hyper, (int)b);
     e = train_batch(s, batch, x, y, rows, s->loss_acc, b == 0, &ad);
   }
   hipGraph_t gr = nullptr;
@@ -1387,23 +1405,24 @@ int sur_create(int32_t device, void *hip_stream, int64_t max_batch, sur_t *out) 
 #define A(ptr, cnt) \
   if (e == hipSuccess) e = alloc(&s->ptr, (cnt))
   A(P, kNP); A(G, kNP); A(Mm, kNP); A(V, kNP);
-  A(W2, kH * kH); A(W2T, kH * kH); A(W3, kH * kH); A(W3T, kH * kH);
-  A(W4, kOut * kH); A(W4T, kOut * kH); A(W2f, kH * kH); A(W3f, kH * kH);
-  A(W4f, kOut * kH);
+  A(W.W2, kH * kH); A(W.W3, kH * kH); A(W.W3T, kH * kH); A(W.W3p, kH * kH);
+  A(W.W4, kOut * kH); A(W.W4T, kOut * kH); A(W.W4p, kOut * kH);
   A(d_mean, kOut); A(d_std, kOut); A(d_dmean, kOut); A(d_dstd, kOut);
   A(x, B * kIn); A(tgt, B * kOut);
-  A(a1T, B * kH); A(a2T, B * kH); A(a3T, B * kH);
-  A(dz4bT, B * kOut); A(dz3bT, B * kH); A(dz2bT, B * kH);
+  A(a1, B * kH); A(a2, B * kH); A(a3, B * kH);
+  A(dz4, B * kOut); A(dz3, B * kH); A(dz2, B * kH);
   A(part2, (int64_t)kSplit * kH * kH); A(part3, (int64_t)kSplit * kH * kH);
   A(part4, (int64_t)kSplit * kOut * kH);
   A(cp2, B / kTR * kH);
   A(cp3, B / kTR * kH); A(cp4, B / kTR * kOut);
   A(lpart, B / kTR); A(loss, 1);
   A(loss_acc, 1);
-  A(hyper, 5);
+  A(hyper, 5); A(adam_h, 6);
 #undef A
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->cap_stream, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipMemsetAsync(s->P, 0, kNP * sizeof(float), s->stream);
+  // the feature layer's gradients stay 0 (no kernel writes them)
+  if (e == hipSuccess) e = hipMemsetAsync(s->G, 0, kNP * sizeof(float), s->stream);
   if (e == hipSuccess) e = hipMemsetAsync(s->Mm, 0, kNP * sizeof(float), s->stream);
   if (e == hipSuccess) e = hipMemsetAsync(s->V, 0, kNP * sizeof(float), s->stream);
   if (e == hipSuccess) e = refresh(s);
@@ -1422,15 +1441,15 @@ int sur_destroy(sur_t s) {
   if (!s) return ENS_OK;
   DevGuard dg(s->device);
   (void)hipStreamSynchronize(s->stream);
-  void *ptrs[] = {s->P, s->G, s->Mm, s->V, s->W2, s->W2T, s->W3, s->W3T, s->W4, s->W4T,
-                  s->d_mean, s->d_std, s->d_dmean, s->d_dstd, s->x, s->tgt, s->a1T,
-                  s->a2T, s->a3T, s->dz4bT, s->dz3bT, s->dz2bT, s->part2, s->part3,
+  void *ptrs[] = {s->P, s->G, s->Mm, s->V, s->W.W2, s->W.W3, s->W.W4, s->W.W3T, s->W.W4T,
+                  s->W.W3p, s->W.W4p, s->d_mean, s->d_std, s->d_dmean, s->d_dstd, s->x, s->tgt,
+                  s->a1, s->a2, s->a3, s->dz4, s->dz3, s->dz2, s->part2, s->part3,
                   s->part4, s->cp2, s->cp3, s->cp4, s->lpart,
-                  s->loss, s->loss_acc, s->scan, s->nlab, s->srec, s->ix, s->iout, s->W2f,
-                  s->W3f, s->W4f};
+                  s->loss, s->loss_acc, s->scan, s->nlab, s->srec, s->ix, s->iout};
   for (void *p : ptrs) (void)hipFree(p);
   free_epoch_graph(s);
   (void)hipFree(s->hyper);
+  (void)hipFree(s->adam_h);
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
   delete s;
   return ENS_OK;
@@ -1549,7 +1568,7 @@ int sur_train_step(sur_t s, const float *x, const float *target, int64_t m, floa
   if (!x || !target) return sfail(s, ENS_E_INVAL, "sur_train_step: NULL input");
   DevGuard dg(s->device);
   if (int rc = load_batch(s, x, target, m, where)) return rc;
-  const AdamArgs ad = adam_args(s, nullptr, 0);
+  const AdamHyper ad = adam_hyper(s, nullptr, 0);
   SUR_HIP(s, train_batch(s, m, s->x, s->tgt, nullptr, nullptr, true, &ad));
   s->t += 1;
   if (loss) {

@@ -165,6 +165,34 @@ def test_gradients_match_oracle(m):
         _close(gg, rr, name)
 
 
+@pytest.mark.parametrize("m", [320, 512, 4160, 8192])
+def test_gradients_over_batch_splits_and_tile_counts(m):
+    """Batches split in 1, 2, 1 and 8 parts for the weight products, with 20,
+    32, 260 and 512 row tiles (the bias sums take 256 tiles at a time, 64
+    partial sums): gradients against the oracle, tolerances as above; then one
+    Adam step, after which a handle that is given the new parameters computes
+    the same bits, so every BF16 copy of the weights has followed."""
+    sur = _sur()
+    flat = _f32_params(5)
+    x, t = _data(m, 2)
+    with sur.Surrogate(max_batch=m) as s, sur.Surrogate(max_batch=m) as s2:
+        s.set_params(flat)
+        g, loss = s.gradients(x, t)
+        s.train_step(x, t)
+        s2.set_params(s.get_params())
+        xf = x[:100]
+        assert np.array_equal(s.forward(xf), s2.forward(xf))
+        ga, gb = s.gradients(x, t), s2.gradients(x, t)
+        assert np.array_equal(ga[0], gb[0]) and ga[1] == gb[1]
+    ps = M.unpack(flat)
+    out, cache = M.forward(ps, x.astype(np.float64), bf16=True)
+    ref = M.backward(ps, cache, out, t.astype(np.float64), bf16=True, w=M.OUT_WEIGHTS)
+    assert loss == pytest.approx(M.mse(out, t, M.OUT_WEIGHTS), rel=1e-4)
+    names = ["W1", "b1", "W2", "b2", "W3", "b3", "W4", "b4"]
+    for name, gg, rr in zip(names, M.unpack(g.astype(np.float64)), ref):
+        _close(gg, rr, name)
+
+
 def test_adam_steps_follow_the_oracle():
     """Five Adam steps on the GPU against five oracle steps (BF16-mode forward
     and backward, the oracle's Adam with its bias corrections, pinned by the
