@@ -664,45 +664,290 @@ __global__ void k_refresh(const float *__restrict__ P, WeightCopies W) {
   put_weights<4>(W, o, in, c);
 }
 
-// Sweep inputs -> normalised network inputs: (p_A, ln f) mapped to [-1, 1]
-// (k_fused<true> normalises its inputs the same way).
-__global__ void k_inputs(const double *__restrict__ prm, int64_t n, double lo0, double sc0,
-                         double lo1, double sc1, float *x) {
-  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n) return;
-  x[2 * r] = (float)(fma(prm[r] - lo0, sc0, -1.0));
-  x[2 * r + 1] = (float)(fma(log(prm[n + r]) - lo1, sc1, -1.0));
+// ---------------------------------------------------------------- dataset
+// The recorded maxima of a point in decreasing order are the network's
+// targets (the first output then is the point's largest maximum; the order
+// does not depend on the phase of a periodic or chaotic response within the
+// window).  One point per lane: the 64 loads of a wave are 512 bytes
+// contiguous each, and the bitonic network (672 exchanges) runs in registers.
+//
+// 262144 points (134 MB of records in, 67 MB of targets out; 28 and 42 us at
+// the 4.8 TB/s of a copy): k_moments 65 us, k_dataset 54 us, bound by the
+// instructions of the network and the logarithms at 2 waves per SIMD.  Before,
+// a kernel with one wave per point sorted (249 us, 64 lines to a load) and
+// wrote the records out again, twice, and one block per output took all
+// logarithms for the mean (436 us) and for the deviation (458 us), and a
+// thread per target once more (145 us).
+//
+// A wave takes 64 points (a tile) and all 64 outputs, in groups of 16, or,
+// where the points are too few for the SIMDs (few below), one group of them,
+// so that 4 waves sort the same points and share the logarithms.
+constexpr int kGrp = 16;              // outputs passed at a time
+constexpr int kDsWaves = 4;           // waves of a block
+constexpr int kGroups = kOut / kGrp;
+constexpr int kRowLd = kOut + 4;      // 16 lanes' rows on different banks
+
+static_assert(kDsWaves == kGroups, "few points: one group per wave of a block");
+// Few points: the grid of one group per wave still is at most one wave per
+// SIMD (16384 points: k_dataset 11 us, 20 us with all groups in a wave).
+inline bool few_points(int64_t n) { return n <= 64 * 256; }
+
+// Records of point i, sorted (lanes past the last point repeat it).
+__device__ __forceinline__ void sorted_records(const double *__restrict__ rec, int64_t n,
+                                               int64_t i, double (&v)[kOut]) {
+  const double *p = rec + (i < n ? i : n - 1);
+#pragma unroll
+  for (int j = 0; j < kOut; ++j) v[j] = p[j * n];
+#pragma unroll
+  for (int k = 2; k <= kOut; k <<= 1)
+#pragma unroll
+    for (int j = k >> 1; j > 0; j >>= 1)
+#pragma unroll
+      for (int l = 0; l < kOut; ++l)
+        if (!(l & j)) {
+          const double a = v[l], b = v[l | j];
+          const bool down = !(l & k);
+          v[l] = down ? fmax(a, b) : fmin(a, b);
+          v[l | j] = down ? fmin(a, b) : fmax(a, b);
+        }
 }
 
-// The recorded maxima of each point in decreasing order: one wave per point,
-// lane j holding rec[j][i], sorted across the lanes by a bitonic network
-// (the first output then is the point's largest maximum; the order does not
-// depend on the phase of a periodic or chaotic response within the window).
-__global__ __launch_bounds__(256) void k_sort_desc(const double *__restrict__ rec, int64_t n,
-                                                   double *__restrict__ out) {
-  const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  const int l = threadIdx.x & 63;
-  if (i >= n) return;   // the whole wave shares i
-  double v = rec[(int64_t)l * n + i];
+// ln x for finite normal x > 0.  x = 2^e m with m in [1/2, 1); the top 7 bits
+// of m's fraction choose a table entry with inv ~ 1 / m of few bits, and
+//     ln x = k ln 2 + L + log1p(f),   f = m inv - 1,  |f| <= 2^-7,
+// k = e with L = -ln inv for the upper part of the interval, and k = e - 1
+// with L = -ln (inv / 2) below sqrt(1/2), so that k = L = 0 on both sides of
+// x = 1.  ln 2 and L are split: the high parts are multiples of 2^-42, so
+// k ln2_hi + L_hi is exact; the sum with f keeps its rounding error, and the
+// Taylor series of log1p(f) - f is small beside it.  Error at most 0.63 ulp
+// (0.64 for the library's log, of 4 times as many instructions), measured
+// against 64-bit mantissas over 1e-130 .. 1e130 and near 1.
+struct LnEntry {
+  double hi;
+  float lo, inv;
+};
+constexpr int kLnTab = 128, kLnLow = 53;   // entries; those below sqrt(1/2)
+constexpr double kLn2Hi = 0x1.62e42fefa38p-1, kLn2Lo = 0x1.ef35793c7673p-45;
+
+void ln_table(LnEntry *t) {
+  for (int i = 0; i < kLnTab; ++i) {
+    const double centre = 0.5 + (i + 0.5) / (2 * kLnTab);
+    double inv = std::round(1024.0 / centre) / 1024.0;
+    if (i == 0) inv = 2.0;             // next to x = 1 on either side
+    if (i == kLnTab - 1) inv = 1.0;
+    const long double L = -std::log((long double)(i < kLnLow ? inv / 2 : inv));
+    t[i].hi = (double)(std::round(L * 0x1p42L) / 0x1p42L);
+    t[i].lo = (float)(L - (long double)t[i].hi);
+    t[i].inv = (float)inv;
+  }
+}
+
+__device__ __forceinline__ double ln_normal(const LnEntry *tab, double x) {
+  const int i = (__double2hiint(x) >> 13) & (kLnTab - 1);
+  const LnEntry t = tab[i];
+  const double k = (double)(__builtin_amdgcn_frexp_exp(x) - (i < kLnLow ? 1 : 0));
+  const double f = fma(__builtin_amdgcn_frexp_mant(x), (double)t.inv, -1.0);
+  double q = -1.0 / 8;
+  q = fma(q, f, 1.0 / 7);
+  q = fma(q, f, -1.0 / 6);
+  q = fma(q, f, 1.0 / 5);
+  q = fma(q, f, -1.0 / 4);
+  q = fma(q, f, 1.0 / 3);
+  q = fma(q, f, -1.0 / 2);
+  const double h = fma(k, kLn2Hi, t.hi), lo = fma(k, kLn2Lo, (double)t.lo);
+  const double s = h + f, r = (h - s) + f;
+  return s + (r + fma(f * f, q, lo));
+}
+// Sorted records all finite, normal and positive in every lane (a NaN among
+// them does not outlive the sort unless all are)?
+__device__ __forceinline__ bool all_normal(const double (&v)[kOut]) {
+  return __all(v[kOut - 1] >= 0x1p-1022 && v[0] < (double)INFINITY);
+}
+
+// Orders the wave's LDS writes before its lanes' reads of each other's values.
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The output normalisation: y = (ln record - mean) / stdv.
+struct Norm {
+  double mean[kOut], stdv[kOut], rstd[kOut];   // rstd = 1 / stdv
+  float fmean[kOut], fstd[kOut];
+};
+
+// Network inputs and targets of n points: (p_A, ln f) mapped to [-1, 1]
+// (k_fused<true> normalises its inputs the same way), and y[i][j] =
+// (ln rec[j][i] - mean_j) / std_j of the sorted records.  The rows of y are
+// gathered in LDS (each lane has one) and stored 1 KB contiguous: storing 16
+// bytes of every lane's row at a time took 72 us for 262144 points with the
+// sort and the logarithms left out.
+struct DatasetArgs {
+  const double *prm, *rec;
+  const Norm *norm;
+  int64_t n;
+  double lo0, sc0, lo1, sc1;
+  float *x, *y;
+  const LnEntry *lntab;
+  bool plain;   // no step of the division by way of rstd leaves the normal range
+  bool few;
+};
+__global__ __launch_bounds__(64 * kDsWaves, 2) void k_dataset(DatasetArgs a) {
+  __shared__ LnEntry lntab[kLnTab];
+  __shared__ float rows[kDsWaves][64][kRowLd];
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i0 = (a.few ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kDsWaves + w) * 64;
+  const int64_t i = i0 + l;
+  const bool mine = i < a.n;
+  if (threadIdx.x < kLnTab) lntab[threadIdx.x] = a.lntab[threadIdx.x];
+  __syncthreads();
+  if (i0 >= a.n) return;   // the whole wave
+  double v[kOut];
+  sorted_records(a.rec, a.n, i, v);
+  if (mine && (!a.few || w == 0)) {
+    a.x[2 * i] = (float)(fma(a.prm[i] - a.lo0, a.sc0, -1.0));
+    a.x[2 * i + 1] = (float)(fma(log(a.prm[a.n + i]) - a.lo1, a.sc1, -1.0));
+  }
+  const Norm &nm = *a.norm;
+  const bool normal = a.plain && all_normal(v);
 #pragma unroll
-  for (int k = 2; k <= 64; k <<= 1) {
+  for (int g = 0; g < kGroups; ++g) {
+    if (a.few && g != w) continue;
+    if (normal) {
 #pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const double o = __shfl_xor(v, j);
-      const bool keep_max = ((l & k) == 0) == ((l & j) == 0);
-      v = keep_max ? fmax(v, o) : fmin(v, o);
+      for (int j = kGrp * g; j < kGrp * (g + 1); j += 4) {
+        f32x4 o;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          // the quotient by way of the reciprocal and one correction of the
+          // residual (Markstein, 1990)
+          const double d = ln_normal(lntab, v[j + u]) - nm.mean[j + u], q = d * nm.rstd[j + u];
+          o[u] = (float)fma(fma(-q, nm.stdv[j + u], d), nm.rstd[j + u], q);
+        }
+        *(f32x4 *)&rows[w][l][j] = o;
+      }
+    } else {
+#pragma unroll
+      for (int j = kGrp * g; j < kGrp * (g + 1); j += 4) {
+#pragma unroll 1
+        for (int u = 0; u < 4; ++u) {
+          const double x = u < 2 ? (u == 0 ? v[j] : v[j + 1]) : (u == 2 ? v[j + 2] : v[j + 3]);
+          rows[w][l][j + u] = (float)((log(x) - nm.mean[j + u]) / nm.stdv[j + u]);
+        }
+      }
     }
   }
-  out[(int64_t)l * n + i] = v;
+  wave_lds_sync();
+  // whole rows: 4 a store, or the wave's quarter of 16
+  const int c = a.few ? kGrp * w + 4 * (l & 3) : 4 * (l & 15);
+  const int step = a.few ? 16 : 4;
+  for (int r = a.few ? l >> 2 : l >> 4; r < 64 && i0 + r < a.n; r += step)
+    *(f32x4 *)(a.y + (i0 + r) * kOut + c) = *(const f32x4 *)&rows[w][r][c];
 }
 
-// Standardised targets: y[i][j] = (ln rec[j][i] - mean_j) / std_j.
-__global__ void k_targets(const double *__restrict__ rec, int64_t n, const double *mean,
-                          const double *stdv, float *y) {
-  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n * kOut) return;
-  const int64_t i = idx / kOut, j = idx % kOut;
-  y[idx] = (float)((log(rec[j * n + i]) - mean[j]) / stdv[j]);
+// Count, mean and sum of squares about the mean of two sets together (Chan,
+// Golub and LeVeque, 1983).
+struct Moments {
+  double n, mean, m2;
+};
+__device__ __forceinline__ Moments merged(const Moments &a, const Moments &b) {
+  if (b.n == 0.0) return a;
+  Moments c;
+  c.n = a.n + b.n;
+  const double d = b.mean - a.mean;
+  c.mean = fma(d, b.n / c.n, a.mean);
+  c.m2 = (a.m2 + b.m2) + d * d * (a.n * b.n / c.n);
+  return c;
+}
+
+// Moments of ln (sorted records) of each output over n points: each wave's
+// tile in two passes (the mean from the differences to the tile's first
+// point) by 4 lanes per output, the block's tiles merged, to
+// part[output][block].
+__global__ __launch_bounds__(64 * kDsWaves, 2) void k_moments(const double *__restrict__ rec,
+                                                              int64_t n, bool few,
+                                                              const LnEntry *__restrict__ tab,
+                                                              Moments *__restrict__ part) {
+  // rows 65 apart: 16 outputs' values fall on different banks
+  __shared__ double lds[kDsWaves][kGrp][65];
+  __shared__ Moments tile[kDsWaves][kOut];
+  __shared__ LnEntry lntab[kLnTab];
+  if (threadIdx.x < kLnTab) lntab[threadIdx.x] = tab[threadIdx.x];
+  __syncthreads();
+  const int l = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i0 = (few ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kDsWaves + w) * 64;
+  if (i0 < n) {
+    const int jj = l & (kGrp - 1), q = l / kGrp;
+    double *row = lds[w][jj];
+    const int cnt = n - i0 < 64 ? (int)(n - i0) : 64;
+    const int ke = cnt - 16 * q;   // the lane's values: k = 0 .. 15 with k < ke
+    double v[kOut];
+    sorted_records(rec, n, i0 + l, v);
+    const bool normal = all_normal(v);
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+      if (few && g != w) continue;
+#pragma unroll
+      for (int r = 0; r < kGrp; ++r)
+        lds[w][r][l] = normal ? ln_normal(lntab, v[kGrp * g + r]) : v[kGrp * g + r];
+      if (!normal)
+#pragma unroll 1
+        for (int r = 0; r < kGrp; ++r) lds[w][r][l] = log(lds[w][r][l]);
+      wave_lds_sync();
+      // the lane's 16 values, as differences to the tile's first point
+      const double p = row[0];
+      double d[16], sum = 0.0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        d[k] = k < ke ? row[16 * q + k] - p : 0.0;
+        sum += d[k];
+      }
+      sum += __shfl_xor(sum, 16);
+      sum += __shfl_xor(sum, 32);
+      const double dm = sum / (double)cnt;
+      double m2 = 0.0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const double e = k < ke ? d[k] - dm : 0.0;
+        m2 = fma(e, e, m2);
+      }
+      m2 += __shfl_xor(m2, 16);
+      m2 += __shfl_xor(m2, 32);
+      if (q == 0) tile[few ? 0 : w][kGrp * g + jj] = Moments{(double)cnt, p + dm, m2};
+      wave_lds_sync();
+      __builtin_amdgcn_sched_barrier(0);   // one group's values in registers at a time
+    }
+  } else if (!few) {
+    tile[w][l] = Moments{0.0, 0.0, 0.0};
+  }
+  __syncthreads();
+  if (threadIdx.x >= kOut) return;
+  Moments m = tile[0][threadIdx.x];
+  if (!few)
+#pragma unroll
+    for (int k = 1; k < kDsWaves; ++k) m = merged(m, tile[k][threadIdx.x]);
+  part[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = m;
+}
+
+// Mean and standard deviation of each output (one block each) from the
+// moments of nb blocks, merged in a fixed order.
+__global__ __launch_bounds__(256) void k_mean_std(const Moments *__restrict__ part, int64_t nb,
+                                                  double *fit) {
+  __shared__ Moments red[256];
+  const int j = blockIdx.x, t = threadIdx.x;
+  Moments m{0.0, 0.0, 0.0};
+  for (int64_t i = t; i < nb; i += 256) m = merged(m, part[j * nb + i]);
+  red[t] = m;
+  __syncthreads();
+  for (int k = 128; k > 0; k >>= 1) {
+    if (t < k) red[t] = merged(red[t], red[t + k]);
+    __syncthreads();
+  }
+  if (t == 0) {
+    fit[j] = red[0].mean;
+    fit[kOut + j] = sqrt(red[0].m2 / red[0].n);
+  }
 }
 
 // ---------------------------------------------------------------- fused inference
@@ -1015,42 +1260,6 @@ __global__ __launch_bounds__(kScanBlock) void k_write_idx(const uint8_t *__restr
   if (v) idx[offs[blockIdx.x] + pre[threadIdx.x] - 1] = i;
 }
 
-// Mean of ln rec[j][i] over i (one block per output j, fixed-order tree).
-__global__ __launch_bounds__(256) void k_logmean(const double *__restrict__ rec, int64_t n,
-                                                 double *mean) {
-  __shared__ double red[256];
-  const int j = blockIdx.x;
-  double s = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += 256) s += log(rec[j * n + i]);
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) mean[j] = red[0] / (double)n;
-}
-
-// Standard deviation of ln rec[j][i] about the mean (second pass).
-__global__ __launch_bounds__(256) void k_logstd(const double *__restrict__ rec, int64_t n,
-                                                const double *mean, double *stdv) {
-  __shared__ double red[256];
-  const int j = blockIdx.x;
-  const double mu = mean[j];
-  double s = 0.0;
-  for (int64_t i = threadIdx.x; i < n; i += 256) {
-    const double d = log(rec[j * n + i]) - mu;
-    s = fma(d, d, s);
-  }
-  red[threadIdx.x] = s;
-  __syncthreads();
-  for (int k = 128; k > 0; k >>= 1) {
-    if (threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) stdv[j] = sqrt(red[0] / (double)n);
-}
-
 // label[idx[i]] = [max_j rec[j][i] >= 2]; -1 if any record is NaN.
 __global__ void k_exact_labels(const double *__restrict__ rec, int64_t k,
                                const int64_t *__restrict__ idx, int8_t *label) {
@@ -1079,12 +1288,11 @@ struct sur_ctx {
   int64_t t = 0;
   double in_lo[2] = {0, 0}, in_hi[2] = {1, 1};
   double out_mean[kOut], out_std[kOut];
-  bool have_norm = false;
+  bool have_norm = false, norm_plain = false;   // norm_plain: DatasetArgs::plain
   // parameters and optimiser state
   float *P = nullptr, *G = nullptr, *Mm = nullptr, *V = nullptr;
   WeightCopies W = {};
-  float *d_mean = nullptr, *d_std = nullptr;
-  double *d_dmean = nullptr, *d_dstd = nullptr;
+  Norm *norm = nullptr;       // the output normalisation, in device memory
   // one batch: inputs and targets, the activations and gradients in
   // fragment order over the batch for the weight-gradient products
   float *x = nullptr, *tgt = nullptr;
@@ -1101,8 +1309,10 @@ struct sur_ctx {
   int64_t *scan = nullptr;    // compaction scratch
   int64_t scan_cap = 0;
   int8_t *nlab = nullptr;     // exact labels of the training grid [G][G]
-  double *srec = nullptr;     // records sorted per point (fit_norm, build_dataset)
-  int64_t srec_n = 0;
+  LnEntry *lntab = nullptr;
+  double *fit = nullptr;      // means and standard deviations of sur_fit_norm
+  Moments *mom = nullptr;     // [kOut][blocks] (sur_fit_norm), grown as needed
+  int64_t mom_nb = 0;
   int nlab_G = 0;
   // captured training epoch (sur_train_epoch), replayed while the dataset,
   // row list and batch are the same
@@ -1293,23 +1503,6 @@ hipError_t refresh(sur_ctx *s) {
   return hipGetLastError();
 }
 
-// The records [kOut][n] sorted in decreasing order per point, in the
-// handle's scratch (grown as needed); NULL on allocation failure.
-const double *sorted_records(sur_ctx *s, const double *rec, int64_t n, hipError_t *e) {
-  *e = hipSuccess;
-  if (n > s->srec_n) {
-    (void)hipFree(s->srec);
-    s->srec = nullptr;
-    s->srec_n = 0;
-    *e = alloc(&s->srec, n * kOut);
-    if (*e != hipSuccess) return nullptr;
-    s->srec_n = n;
-  }
-  hipLaunchKernelGGL(k_sort_desc, dim3(nblk(n, 4)), dim3(256), 0, s->stream, rec, n, s->srec);
-  *e = hipGetLastError();
-  return *e == hipSuccess ? s->srec : nullptr;
-}
-
 int check_batch(sur_ctx *s, int64_t m) {
   if (m <= 0 || m % 64 || m > s->max_batch)
     return sfail(s, ENS_E_INVAL, "batch must be a positive multiple of 64 <= max_batch");
@@ -1407,7 +1600,7 @@ int sur_create(int32_t device, void *hip_stream, int64_t max_batch, sur_t *out) 
   A(P, kNP); A(G, kNP); A(Mm, kNP); A(V, kNP);
   A(W.W2, kH * kH); A(W.W3, kH * kH); A(W.W3T, kH * kH); A(W.W3p, kH * kH);
   A(W.W4, kOut * kH); A(W.W4T, kOut * kH); A(W.W4p, kOut * kH);
-  A(d_mean, kOut); A(d_std, kOut); A(d_dmean, kOut); A(d_dstd, kOut);
+  A(norm, 1);
   A(x, B * kIn); A(tgt, B * kOut);
   A(a1, B * kH); A(a2, B * kH); A(a3, B * kH);
   A(dz4, B * kOut); A(dz3, B * kH); A(dz2, B * kH);
@@ -1417,7 +1610,7 @@ int sur_create(int32_t device, void *hip_stream, int64_t max_batch, sur_t *out) 
   A(cp3, B / kTR * kH); A(cp4, B / kTR * kOut);
   A(lpart, B / kTR); A(loss, 1);
   A(loss_acc, 1);
-  A(hyper, 5); A(adam_h, 6);
+  A(hyper, 5); A(adam_h, 6); A(lntab, kLnTab); A(fit, 2 * kOut);
 #undef A
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->cap_stream, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipMemsetAsync(s->P, 0, kNP * sizeof(float), s->stream);
@@ -1426,6 +1619,10 @@ int sur_create(int32_t device, void *hip_stream, int64_t max_batch, sur_t *out) 
   if (e == hipSuccess) e = hipMemsetAsync(s->Mm, 0, kNP * sizeof(float), s->stream);
   if (e == hipSuccess) e = hipMemsetAsync(s->V, 0, kNP * sizeof(float), s->stream);
   if (e == hipSuccess) e = refresh(s);
+  LnEntry lntab[kLnTab];
+  ln_table(lntab);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(s->lntab, lntab, sizeof(lntab), hipMemcpyHostToDevice, s->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(s->stream);
   if (e != hipSuccess) {
     int code = sfail(nullptr, e == hipErrorOutOfMemory ? ENS_E_NOMEM : ENS_E_HIP,
@@ -1442,10 +1639,10 @@ int sur_destroy(sur_t s) {
   DevGuard dg(s->device);
   (void)hipStreamSynchronize(s->stream);
   void *ptrs[] = {s->P, s->G, s->Mm, s->V, s->W.W2, s->W.W3, s->W.W4, s->W.W3T, s->W.W4T,
-                  s->W.W3p, s->W.W4p, s->d_mean, s->d_std, s->d_dmean, s->d_dstd, s->x, s->tgt,
+                  s->W.W3p, s->W.W4p, s->norm, s->x, s->tgt,
                   s->a1, s->a2, s->a3, s->dz4, s->dz3, s->dz2, s->part2, s->part3,
                   s->part4, s->cp2, s->cp3, s->cp4, s->lpart,
-                  s->loss, s->loss_acc, s->scan, s->nlab, s->srec, s->ix, s->iout};
+                  s->loss, s->loss_acc, s->scan, s->nlab, s->lntab, s->fit, s->mom, s->ix, s->iout};
   for (void *p : ptrs) (void)hipFree(p);
   free_epoch_graph(s);
   (void)hipFree(s->hyper);
@@ -1492,7 +1689,8 @@ int sur_set_norm(sur_t s, const double *in_lo, const double *in_hi, const double
   for (int j = 0; j < kOut; ++j)
     if (!(out_std[j] > 0.0) || !std::isfinite(out_mean[j]) || !std::isfinite(out_std[j]))
       return sfail(s, ENS_E_INVAL, "sur_set_norm: need finite mean and std > 0");
-  std::vector<float> m(kOut), sd(kOut);
+  Norm nm;
+  s->norm_plain = true;
   for (int i = 0; i < 2; ++i) {
     s->in_lo[i] = in_lo[i];
     s->in_hi[i] = in_hi[i];
@@ -1500,14 +1698,16 @@ int sur_set_norm(sur_t s, const double *in_lo, const double *in_hi, const double
   for (int j = 0; j < kOut; ++j) {
     s->out_mean[j] = out_mean[j];
     s->out_std[j] = out_std[j];
-    m[j] = (float)out_mean[j];
-    sd[j] = (float)out_std[j];
+    nm.mean[j] = out_mean[j];
+    nm.stdv[j] = out_std[j];
+    nm.rstd[j] = 1.0 / out_std[j];
+    nm.fmean[j] = (float)out_mean[j];
+    nm.fstd[j] = (float)out_std[j];
+    s->norm_plain = s->norm_plain && out_std[j] >= 1e-100 && out_std[j] <= 1e100 &&
+                    std::fabs(out_mean[j]) <= 1e100;
   }
   DevGuard dg(s->device);
-  SUR_HIP(s, hipMemcpyAsync(s->d_mean, m.data(), kOut * sizeof(float), hipMemcpyHostToDevice, s->stream));
-  SUR_HIP(s, hipMemcpyAsync(s->d_std, sd.data(), kOut * sizeof(float), hipMemcpyHostToDevice, s->stream));
-  SUR_HIP(s, hipMemcpyAsync(s->d_dmean, s->out_mean, kOut * sizeof(double), hipMemcpyHostToDevice, s->stream));
-  SUR_HIP(s, hipMemcpyAsync(s->d_dstd, s->out_std, kOut * sizeof(double), hipMemcpyHostToDevice, s->stream));
+  SUR_HIP(s, hipMemcpyAsync(s->norm, &nm, sizeof(nm), hipMemcpyHostToDevice, s->stream));
   SUR_HIP(s, hipStreamSynchronize(s->stream));
   s->have_norm = true;
   return ENS_OK;
@@ -1522,14 +1722,9 @@ int sur_build_dataset(sur_t s, const double *params, const double *records, int6
   if (n == 0) return ENS_OK;
   DevGuard dg(s->device);
   const double sc0 = 2.0 / (s->in_hi[0] - s->in_lo[0]), sc1 = 2.0 / (s->in_hi[1] - s->in_lo[1]);
-  hipLaunchKernelGGL(k_inputs, dim3(nblk(n, 256)), dim3(256), 0, s->stream, params, n,
-                     s->in_lo[0], sc0, s->in_lo[1], sc1, x);
-  SUR_HIP(s, hipGetLastError());
-  hipError_t se;
-  const double *sorted = sorted_records(s, records, n, &se);
-  SUR_HIP(s, se);
-  hipLaunchKernelGGL(k_targets, dim3(nblk(n * kOut, 256)), dim3(256), 0, s->stream, sorted, n,
-                     s->d_dmean, s->d_dstd, y);
+  const DatasetArgs a{params, records, s->norm, n, s->in_lo[0], sc0, s->in_lo[1], sc1,
+                      x, y, s->lntab, s->norm_plain, few_points(n)};
+  hipLaunchKernelGGL(k_dataset, dim3(nblk(n, a.few ? 64 : 64 * kDsWaves)), dim3(64 * kDsWaves), 0, s->stream, a);
   SUR_HIP(s, hipGetLastError());
   SUR_HIP(s, hipStreamSynchronize(s->stream));
   return ENS_OK;
@@ -1642,8 +1837,8 @@ int sur_screen(sur_t s, const double *params, int64_t n, const sur_screen_opts *
   a.sc0 = sc0;
   a.lo1 = s->in_lo[1];
   a.sc1 = sc1;
-  a.mean = s->d_mean;
-  a.stdv = s->d_std;
+  a.mean = s->norm->fmean;
+  a.stdv = s->norm->fstd;
   a.margin = (float)o->margin;
   a.spread = (float)o->spread;
   a.flag_margin = (float)o->flag_margin;
@@ -1678,23 +1873,29 @@ int sur_fit_norm(sur_t s, const double *in_lo, const double *in_hi, const double
   if (!in_lo || !in_hi || !records || n <= 0)
     return sfail(s, ENS_E_INVAL, "sur_fit_norm: bad arguments");
   DevGuard dg(s->device);
-  hipError_t se;
-  const double *sorted = sorted_records(s, records, n, &se);
-  SUR_HIP(s, se);
-  hipLaunchKernelGGL(k_logmean, dim3(kOut), dim3(256), 0, s->stream, sorted, n, s->d_dmean);
-  hipLaunchKernelGGL(k_logstd, dim3(kOut), dim3(256), 0, s->stream, sorted, n, s->d_dmean,
-                     s->d_dstd);
+  const bool few = few_points(n);
+  const int64_t nb = nblk(n, few ? 64 : 64 * kDsWaves);
+  if (nb > s->mom_nb) {
+    (void)hipFree(s->mom);
+    s->mom = nullptr;
+    s->mom_nb = 0;
+    SUR_HIP(s, alloc(&s->mom, nb * kOut));
+    s->mom_nb = nb;
+  }
+  hipLaunchKernelGGL(k_moments, dim3((unsigned)nb), dim3(64 * kDsWaves), 0, s->stream, records, n,
+                     few, s->lntab, s->mom);
+  hipLaunchKernelGGL(k_mean_std, dim3(kOut), dim3(256), 0, s->stream, s->mom, nb, s->fit);
   SUR_HIP(s, hipGetLastError());
-  double m[kOut], sd[kOut];
-  SUR_HIP(s, hipMemcpyAsync(m, s->d_dmean, sizeof(m), hipMemcpyDeviceToHost, s->stream));
-  SUR_HIP(s, hipMemcpyAsync(sd, s->d_dstd, sizeof(sd), hipMemcpyDeviceToHost, s->stream));
+  double m[2 * kOut];
+  const double *sd = m + kOut;
+  SUR_HIP(s, hipMemcpyAsync(m, s->fit, sizeof(m), hipMemcpyDeviceToHost, s->stream));
   SUR_HIP(s, hipStreamSynchronize(s->stream));
   for (int j = 0; j < kOut; ++j)
     if (!(sd[j] > 0.0) || !std::isfinite(m[j]))
       return sfail(s, ENS_E_INVAL, "sur_fit_norm: records give a non-positive or non-finite spread");
   if (int rc = sur_set_norm(s, in_lo, in_hi, m, sd)) return rc;
-  if (out_mean) std::memcpy(out_mean, m, sizeof(m));
-  if (out_std) std::memcpy(out_std, sd, sizeof(sd));
+  if (out_mean) std::memcpy(out_mean, m, kOut * sizeof(double));
+  if (out_std) std::memcpy(out_std, sd, kOut * sizeof(double));
   return ENS_OK;
 }
 

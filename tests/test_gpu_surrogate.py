@@ -253,6 +253,55 @@ def test_dataset_targets_are_sorted_standardised_maxima():
     assert np.all(np.diff(y * std + mean, axis=1) <= 1e-6)
 
 
+@pytest.mark.parametrize("n", [1, 63, 65, 257, 16384, 16385])
+@pytest.mark.parametrize("special", [None, np.inf, 0.0, -1.0, 1e-310, np.nan])
+def test_dataset_tiles_and_general_logarithm(n, special):
+    """Ragged tiles of 64 points, the last number of points whose tiles are
+    shared by four waves and the first that is not, and records that the short
+    logarithm does not take (one value of a point, or a point whose records
+    are all NaN), with a plain normalisation and one whose division leaves the
+    short division's range.  Targets are one FP32 rounding (2^-24) of the FP64
+    formula, plus that formula's own rounding (a few 2^-53 of ln and mean over
+    std)."""
+    import torch
+    sur = _sur()
+    rng = np.random.default_rng(n)
+    rec = np.exp(rng.normal(size=(64, n)))
+    i = n // 2
+    if special is not None:
+        rec[:, i] = special if np.isnan(special) else rec[:, i]
+        rec[7, i] = special
+    P = np.stack([rng.uniform(0.5, 1.5, n), rng.uniform(0.5, 1.5, n)])
+    lo, hi = np.array([0.5, -1.0]), np.array([1.5, 1.0])
+    rd, pd = torch.from_numpy(rec).cuda(), torch.from_numpy(P).cuda()
+    with np.errstate(all="ignore"):
+        srt = np.log(-np.sort(-rec, axis=0))
+    srt[:, np.isnan(rec).all(axis=0)] = np.nan
+    with sur.Surrogate(max_batch=64) as s:
+        got = np.empty((2, 64))
+        rc = sur._lib().sur_fit_norm(s.h, sur._dptr(lo), sur._dptr(hi),
+                                     sur.ens.C.c_void_p(rd.data_ptr()), n,
+                                     sur._dptr(got[0]), sur._dptr(got[1]))
+        ok = n > 1 and np.isfinite(srt).all()
+        assert (rc == 0) == ok
+        if ok:
+            assert np.allclose(got[0], srt.mean(axis=1), rtol=1e-12, atol=1e-14)
+            assert np.allclose(got[1], srt.std(axis=1), rtol=1e-10)
+        for mean, std in [(np.linspace(1, -1, 64), np.linspace(0.5, 2, 64)),
+                          (np.linspace(1, -1, 64), np.full(64, 1e-250))]:
+            s.set_norm(lo, hi, mean, std)
+            x, y = s.build_dataset(pd, rd, n)
+            with np.errstate(all="ignore"):
+                want = ((srt - mean[:, None]) / std[:, None]).T
+                tol = 2.0**-24 * np.abs(want) + \
+                    2.0**-50 * ((np.abs(srt) + np.abs(mean[:, None])) / std[:, None]).T
+                y = y.cpu().numpy()
+                same = (y == want.astype(np.float32)) | (np.isnan(y) & np.isnan(want))
+                assert np.all(same | (np.abs(y - want) <= tol))
+            assert np.allclose(x.cpu().numpy()[:, 0], 2 * (P[0] - 0.5) - 1, atol=1e-6)
+            assert np.allclose(x.cpu().numpy()[:, 1], np.log(P[1]), atol=1e-6)
+
+
 def test_adam_step_matches_formula():
     sur = _sur()
     flat = _f32_params(6)
