@@ -21,7 +21,7 @@
 // FP32 master copy at once, refreshing its BF16 copies.  The first layer is a fixed random
 // Fourier-feature map of the two inputs (sin of x W1^T + b1, on the vector
 // unit) and is not trained, so no gradient is propagated to it.  Inference
-// runs the whole network in one kernel (k_fused).
+// runs the whole network in one kernel (k_net).
 //
 // MFMA 16x16x32 BF16 operand layout (lane l, 64 lanes): A fragment = row
 // (l mod 16), k = 8 (l / 16) + 0..7; B fragment = column (l mod 16), same k;
@@ -95,8 +95,10 @@ __device__ __forceinline__ float normal_tail(float z, float *gauss = nullptr) {
   if (gauss) *gauss = e;
   return (t * p) * e;
 }
+// max(z, 0) as a median, which takes z as it is: fmaxf first quiets it with
+// an instruction of its own.
 __device__ __forceinline__ float gelu_f(float z) {
-  return fmaf(-fabsf(z), normal_tail(z), fmaxf(z, 0.0f));
+  return fmaf(-fabsf(z), normal_tail(z), __builtin_amdgcn_fmed3f(z, 0.0f, INFINITY));
 }
 // d GELU / dz = Phi(z) + z phi(z)
 __device__ __forceinline__ float gelu_grad_f(float z) {
@@ -112,7 +114,7 @@ __device__ __forceinline__ float gelu_grad_f(float z) {
 // and holds for lane l the 8 values of row 16 fb + l mod 16 that the lane
 // supplies, 16 bytes per lane, 1 KB in all.  Standard k order: lane group g =
 // l / 16, slot s <-> k = 32 c + 8 g + s.  Permuted order (the inputs of layers
-// 3 and 4 in k_fused): k = 32 c + 16 (s / 4) + 4 g + s mod 4.
+// 3 and 4 in k_net): k = 32 c + 16 (s / 4) + 4 g + s mod 4.
 // In both, element (row, k) within its fragment:
 __device__ __forceinline__ int frag_std(int row, int k) {
   return ((((k >> 3) & 3) << 4) | (row & 15)) * 8 + (k & 7);
@@ -778,7 +780,7 @@ struct Norm {
 };
 
 // Network inputs and targets of n points: (p_A, ln f) mapped to [-1, 1]
-// (k_fused<true> normalises its inputs the same way), and y[i][j] =
+// (k_net<.., true> normalises its inputs the same way), and y[i][j] =
 // (ln rec[j][i] - mean_j) / std_j of the sorted records.  The rows of y are
 // gathered in LDS (each lane has one) and stored 1 KB contiguous: storing 16
 // bytes of every lane's row at a time took 72 us for 262144 points with the
@@ -951,21 +953,33 @@ __global__ __launch_bounds__(256) void k_mean_std(const Moments *__restrict__ pa
 }
 
 // ---------------------------------------------------------------- fused inference
-// The whole network for 32 points per wave in one kernel.  The products are
-// taken transposed, Z^T = W A^T (MFMA rows = output features, columns =
-// points), so the accumulator of feature block fb and point block j holds, in
-// lane 16 g + i, features 16 fb + 4 g + q of point 16 j + i.  Packed pairwise
-// ((fb, fb + 1) = (2c, 2c + 1)) these are already the B fragments of the next
-// layer's k chunk c, in the permuted k order
+// The whole network in one kernel, for a tile of 16 NJ points per block.
+// The products are taken transposed, Z^T = W A^T (MFMA rows = output features,
+// columns = points), so the accumulator of feature block fb and point block j
+// holds, in lane 16 g + i, features 16 fb + 4 g + q of point 16 j + i.  Packed
+// pairwise ((fb, fb + 1) = (2c, 2c + 1)) these are already the B fragments of
+// the next layer's k chunk c, in the permuted k order
 //     k slot 8 g + s  <->  feature 32 c + 16 (s / 4) + 4 g + s mod 4,
 // so the weights of layers 3 and 4 are read with their columns permuted the
 // same way; the feature layer's fragments are formed directly in the standard
-// order.  Weights come from L2 (288 KB in all) in fragment order,
-// each fragment serving both point blocks; between layers the activations wait
-// in the wave's slice of LDS.  The arithmetic of every element is the training
+// order.  A wave takes NF of a layer's 16 feature blocks, whose weights it
+// loads into registers (in fragment order, while it forms the activations of
+// the layer before), and all points of the tile; between layers the
+// activations wait in LDS.  The arithmetic of every element is the training
 // path's (same features, GELU and roundings to BF16) except for the order of
 // the FP32 sums: the bias starts the accumulation here, and the k order inside
 // an MFMA differs for layers 3 and 4.
+//
+// Many points: NJ = 4, NF = 2 (two blocks of 8 waves per CU).  4096 x 4096
+// points take 7.3 ms (680 TFLOP/s): the vector unit, which forms 768 features
+// a point, is issuing 77% of the time, beside matrix cores that are busy 30%.
+// Before, each wave took 32 points through the whole network and read all
+// weights for them (7.6 ms).  NJ = 2, 3, 6, 8, one feature block per wave, and
+// blocks that stay for more tiles were slower (8.1 to 9.3 ms).
+// Few points: NJ = 1, then 2, with NF = 1, so that a layer is spread over the
+// 16 waves of a block and the points over all CUs: 1000 points 19.8 -> 6.4 us,
+// 8192 points 20.3 -> 7.5 us (NJ = 1: 9.3 us; 12288 points with NJ = 4: 13 us).
+// What bounds a call then is the 288 KB of weights that each CU reads from L2.
 
 struct FusedArgs {
   int64_t n;                       // points
@@ -975,7 +989,7 @@ struct FusedArgs {
   float *out;                      // forward: network outputs [n][64]
   const float *P;                  // master parameters (W1, b1, b2, b3, b4)
   const bf16 *W2f, *W3f, *W4f;     // BF16 weights in fragment order (3 and 4 k-permuted)
-  // screen epilogue (k_screen_epi's rule)
+  // screen epilogue (screen_point)
   const float *mean, *stdv;
   float margin, spread, flag_margin, label_margin;
   const int8_t *nlab;
@@ -985,185 +999,10 @@ struct FusedArgs {
   float *pmax;
 };
 
-// One hidden layer, Z^T = W A^T, for the wave's 32 points: the input's B
-// fragments in[c][j] (k chunk c, point block j) in registers, W's rows read in
-// the permuted k order of the fragments (or the standard one for the feature
-// layer).  Output feature blocks are taken in pairs (2c', 2c' + 1), each pair
-// accumulated over the 8 k chunks (4 independent accumulators, starting from
-// the bias) and at once turned into the next layer's chunk c' (GELU, BF16),
-// which goes to the wave's slice of LDS, out[c'][j][lane].  A pair's 16
-// weight fragments are loaded while the previous pair is computed (two
-// register buffers), so one L2 latency is exposed per layer rather than per
-// MFMA group.  The loop over pairs stays rolled (by two): the kernel is a few
-// thousand instructions, which the waves of a CU share in the instruction
-// cache.
-// Wp: the pair's first fragment for this lane, fragments (fb, c) 8 KB x
-// (fb - 2 cp) + 1 KB x c apart.
-__device__ __forceinline__ void load_pair(const bf16 *__restrict__ Wp,
-                                          const float *__restrict__ bp, bf16x8 (&w)[8][2],
-                                          f32x4 (&bb)[2]) {
-  // the bias first: the products wait for loads in issue order
-  bb[0] = *(const f32x4 *)bp;
-  bb[1] = *(const f32x4 *)(bp + 16);
-#pragma unroll
-  for (int c = 0; c < 8; ++c)
-#pragma unroll
-    for (int h = 0; h < 2; ++h) w[c][h] = *(const bf16x8 *)(Wp + (h * 8 + c) * 512);
-}
-
-__device__ __forceinline__ void pair_out(const bf16x8 (&w)[8][2], const f32x4 (&bb)[2],
-                                         const bf16x8 (&in)[8][2], int l, bf16x8 *out) {
-  f32x4 acc[2][2];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) acc[h][j] = bb[h];
-#pragma unroll
-  for (int c = 0; c < 8; ++c)
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        acc[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[c][h], in[c][j], acc[h][j], 0, 0, 0);
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    bf16x8 v;
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[4 * h + q] = (bf16)gelu_f(acc[h][j][q]);
-    out[j * 64 + l] = v;
-  }
-}
-
-__device__ __forceinline__ void hidden_layer(const bf16 *__restrict__ W,
-                                             const float *__restrict__ b, int g, int l,
-                                             const bf16x8 (&in)[8][2], bf16x8 *out) {
-  const bf16 *W0 = W + l * 8;
-  const float *b0 = b + 4 * g;
-  bf16x8 wa[8][2], wb[8][2];
-  f32x4 ba[2], bb[2];
-  load_pair(W0, b0, wa, ba);
-#pragma unroll 1
-  for (int cp = 0; cp < 8; cp += 2) {
-    load_pair(W0 + (cp + 1) * 8192, b0 + 32 * (cp + 1), wb, bb);
-    __builtin_amdgcn_sched_barrier(0);
-    pair_out(wa, ba, in, l, out + 2 * cp * 64);
-    // the last round reloads pair 0 (a harmless L2 hit) rather than branch
-    load_pair(W0 + ((cp + 2) & 7) * 8192, b0 + 32 * ((cp + 2) & 7), wa, ba);
-    __builtin_amdgcn_sched_barrier(0);
-    pair_out(wb, bb, in, l, out + 2 * (cp + 1) * 64);
-  }
-}
-
-__device__ __forceinline__ void load_act(const bf16x8 *act, int l, bf16x8 (&in)[8][2]) {
-#pragma unroll
-  for (int c = 0; c < 8; ++c)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) in[c][j] = act[(2 * c + j) * 64 + l];
-}
-
-template <bool SCREEN>
-__global__ __launch_bounds__(256, 2) void k_fused(FusedArgs a) {
-  // each wave's activations between layers: [chunk][point block][lane]
-  __shared__ bf16x8 lds[4][8 * 2 * 64];
-  const int l = threadIdx.x & 63, g = l >> 4, i = l & 15;
-  const int64_t r0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 32;
-  if (r0 >= a.n) return;   // the whole wave
-  bf16x8 *act = lds[threadIdx.x >> 6];
-  const float *__restrict__ P = a.P;
-  float x0[2], x1[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int64_t r = r0 + 16 * j + i;
-    x0[j] = x1[j] = 0.f;
-    if (r < a.n) {
-      if (SCREEN) {
-        x0[j] = (float)(fma(a.prm[r] - a.lo0, a.sc0, -1.0));
-        x1[j] = (float)(fma(log(a.prm[a.n + r]) - a.lo1, a.sc1, -1.0));
-      } else {
-        x0[j] = a.x[2 * r];
-        x1[j] = a.x[2 * r + 1];
-      }
-    }
-  }
-  // the Fourier features, in the standard k order: chunk c, slot 8 g + s
-  bf16x8 fa[8][2];
-#pragma unroll
-  for (int c = 0; c < 8; ++c)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      const int f = 32 * c + 8 * g + s;
-      const float w0 = P[oW1 + 2 * f], w1 = P[oW1 + 2 * f + 1], bb = P[ob1 + f];
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        fa[c][j][s] = (bf16)feature_sin(fmaf(x1[j], w1, fmaf(x0[j], w0, bb)));
-    }
-  hidden_layer(a.W2f, P + ob2, g, l, fa, act);    // layer 2
-  load_act(act, l, fa);
-  hidden_layer(a.W3f, P + ob3, g, l, fa, act);    // layer 3
-  load_act(act, l, fa);
-  // output layer
-  f32x4 o4[4][2];
-#pragma unroll
-  for (int ob = 0; ob < 4; ++ob) {
-    const f32x4 bb = *(const f32x4 *)(P + ob4 + 16 * ob + 4 * g);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) o4[ob][j] = bb;
-  }
-#pragma unroll
-  for (int c = 0; c < 8; ++c)
-#pragma unroll
-    for (int ob = 0; ob < 4; ++ob) {
-      const bf16x8 w = *(const bf16x8 *)(a.W4f + ((ob * 8 + c) * 64 + l) * 8);
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        o4[ob][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, fa[c][j], o4[ob][j], 0, 0, 0);
-    }
-  if (!SCREEN) {
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int64_t r = r0 + 16 * j + i;
-      if (r < a.n)
-#pragma unroll
-        for (int ob = 0; ob < 4; ++ob) *(f32x4 *)(a.out + r * kOut + 16 * ob + 4 * g) = o4[ob][j];
-    }
-    return;
-  }
-  // de-standardised maximum and minimum over the 64 outputs of each point:
-  // 16 in the lane, then across the four lane groups
-  float mx[2], mn[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    mx[j] = -INFINITY;
-    mn[j] = INFINITY;
-  }
-#pragma unroll
-  for (int ob = 0; ob < 4; ++ob) {
-    const f32x4 sd = *(const f32x4 *)(a.stdv + 16 * ob + 4 * g);
-    const f32x4 mu = *(const f32x4 *)(a.mean + 16 * ob + 4 * g);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float v = fmaf(o4[ob][j][q], sd[q], mu[q]);
-        mx[j] = fmaxf(mx[j], v);
-        mn[j] = fminf(mn[j], v);
-      }
-  }
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int off = 16; off < 64; off <<= 1) {
-      mx[j] = fmaxf(mx[j], __shfl_xor(mx[j], off));
-      mn[j] = fminf(mn[j], __shfl_xor(mn[j], off));
-    }
-  // lane group j (j < 2) finishes point 16 j + i
-  if (g >= 2) return;
-  const int64_t r = r0 + 16 * g + i;
-  if (r >= a.n) return;
-  const float xmx = g ? mx[1] : mx[0], xmn = g ? mn[1] : mn[0];
-  const float u0f = g ? x0[1] : x0[0], v0f = g ? x1[1] : x1[0];
+// Label and re-solve mask of point r from its predicted maximum and minimum
+// and its normalised inputs.
+__device__ __forceinline__ void screen_point(const FusedArgs &a, int64_t r, float xmx, float xmn,
+                                             float u0f, float v0f) {
   const float ln2 = 0.69314718055994531f;
   const float d = fabsf(xmx - ln2);
   const bool unsure = d < a.margin;
@@ -1186,6 +1025,145 @@ __global__ __launch_bounds__(256, 2) void k_fused(FusedArgs a) {
   if (a.pmax) a.pmax[r] = xmx;
 }
 
+template <int NJ, int NF, bool SCREEN>
+__global__ __launch_bounds__(64 * 16 / NF, 4) void k_net(FusedArgs a) {
+  constexpr int NW = 16 / NF;            // waves
+  constexpr int NP = 16 * NJ;            // points of the block
+  typedef __attribute__((__vector_size__(4 * NF * sizeof(__bf16)))) __bf16 part;
+  __shared__ bf16x8 act[2][8][NJ][64];   // [chunk][point block][lane], by turns
+  __shared__ float xs[NP][2];            // normalised inputs
+  __shared__ float red[2][kOut / 16][NP];   // maxima and minima over 16 outputs
+  const int t = threadIdx.x, l = t & 63, g = l >> 4, i = l & 15;
+  const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int64_t r0 = (int64_t)blockIdx.x * NP;
+  const float *__restrict__ P = a.P;
+  const int half = NF == 1 ? w & 1 : 0, chunk = NF * w >> 1;
+  if (t < NP) {
+    const int64_t r = r0 + t < a.n ? r0 + t : a.n - 1;
+    if (SCREEN) {
+      xs[t][0] = (float)(fma(a.prm[r] - a.lo0, a.sc0, -1.0));
+      xs[t][1] = (float)(fma(log(a.prm[a.n + r]) - a.lo1, a.sc1, -1.0));
+    } else {
+      xs[t][0] = a.x[2 * r];
+      xs[t][1] = a.x[2 * r + 1];
+    }
+  }
+  // the wave's features of layer 1: 32 chunk + 8 g + 4 half + q
+  float w0[4 * NF], w1[4 * NF], bb[4 * NF];
+#pragma unroll
+  for (int q = 0; q < 4 * NF; ++q) {
+    const int f = 32 * chunk + 8 * g + 4 * half + q;
+    w0[q] = P[oW1 + 2 * f];
+    w1[q] = P[oW1 + 2 * f + 1];
+    bb[q] = P[ob1 + f];
+  }
+  bf16x8 wt[8][NF];
+  const int64_t at = (int64_t)NF * w * 8 * kFrag + l * 8;
+#pragma unroll
+  for (int c = 0; c < 8; ++c)
+#pragma unroll
+    for (int h = 0; h < NF; ++h) wt[c][h] = *(const bf16x8 *)(a.W2f + at + (h * 8 + c) * kFrag);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) {
+    const float x0 = xs[16 * j + i][0], x1 = xs[16 * j + i][1];
+    part v;
+#pragma unroll
+    for (int q = 0; q < 4 * NF; ++q)
+      v[q] = (bf16)feature_sin(fmaf(x1, w1[q], fmaf(x0, w0[q], bb[q])));
+    *((part *)&act[0][chunk][j][l] + half) = v;
+  }
+  __syncthreads();
+  const int ob = w & 3;
+#pragma unroll
+  for (int L = 0; L < 2; ++L) {
+    f32x4 acc[NF][NJ];
+#pragma unroll
+    for (int h = 0; h < NF; ++h) {
+      const f32x4 b = *(const f32x4 *)(P + (L == 0 ? ob2 : ob3) + 16 * (NF * w + h) + 4 * g);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[h][j] = b;
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const bf16x8 in = act[L][c][j][l];
+#pragma unroll
+        for (int h = 0; h < NF; ++h)
+          acc[h][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[c][h], in, acc[h][j], 0, 0, 0);
+      }
+    // the next layer's weights
+    if (L == 0) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+#pragma unroll
+        for (int h = 0; h < NF; ++h)
+          wt[c][h] = *(const bf16x8 *)(a.W3f + at + (h * 8 + c) * kFrag);
+    } else if (w < 4 * NJ) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        wt[c][0] = *(const bf16x8 *)(a.W4f + (ob * 8 + c) * kFrag + l * 8);
+    }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      part v;
+#pragma unroll
+      for (int h = 0; h < NF; ++h)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[4 * h + q] = (bf16)gelu_f(acc[h][j][q]);
+      *((part *)&act[1 - L][chunk][j][l] + half) = v;
+    }
+    __syncthreads();
+  }
+  // the output layer: output block ob of point blocks w / 4, w / 4 + NW / 4, ...
+  const f32x4 b4 = *(const f32x4 *)(P + ob4 + 16 * ob + 4 * g);
+#pragma unroll
+  for (int j0 = 0; j0 < NJ; j0 += NW / 4) {
+    const int j = j0 + (w >> 2);
+    if (j >= NJ) break;
+    f32x4 o = b4;
+#pragma unroll
+    for (int c = 0; c < 8; ++c)
+      o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[c][0], act[0][c][j][l], o, 0, 0, 0);
+    if (!SCREEN) {
+      const int64_t r = r0 + 16 * j + i;
+      if (r < a.n) *(f32x4 *)(a.out + r * kOut + 16 * ob + 4 * g) = o;
+    } else {
+      // de-standardised maximum and minimum over the wave's 16 outputs: 4 in
+      // the lane, then across the four lane groups
+      const f32x4 sd = *(const f32x4 *)(a.stdv + 16 * ob + 4 * g);
+      const f32x4 mu = *(const f32x4 *)(a.mean + 16 * ob + 4 * g);
+      float mx = -INFINITY, mn = INFINITY;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float v = fmaf(o[q], sd[q], mu[q]);
+        mx = fmaxf(mx, v);
+        mn = fminf(mn, v);
+      }
+#pragma unroll
+      for (int off = 16; off < 64; off <<= 1) {
+        mx = fmaxf(mx, __shfl_xor(mx, off));
+        mn = fminf(mn, __shfl_xor(mn, off));
+      }
+      if (g == 0) {
+        red[0][ob][16 * j + i] = mx;
+        red[1][ob][16 * j + i] = mn;
+      }
+    }
+  }
+  if (!SCREEN) return;
+  __syncthreads();
+  if (t >= NP || r0 + t >= a.n) return;
+  float mx = red[0][0][t], mn = red[1][0][t];
+#pragma unroll
+  for (int k = 1; k < kOut / 16; ++k) {
+    mx = fmaxf(mx, red[0][k][t]);
+    mn = fminf(mn, red[1][k][t]);
+  }
+  screen_point(a, r0 + t, mx, mn, xs[t][0], xs[t][1]);
+}
+
 // Exact label of each training node: [max_j rec[j][i] >= 2], -1 if a record
 // is NaN.
 __global__ void k_node_label(const double *__restrict__ rec, int64_t n, int8_t *lab) {
@@ -1202,62 +1180,81 @@ __global__ void k_node_label(const double *__restrict__ rec, int64_t n, int8_t *
 }
 
 // Deterministic compaction of the re-solve mask: block counts, one-block
-// exclusive scan, ordered write.
-constexpr int kScanBlock = 1024;
-__global__ __launch_bounds__(kScanBlock) void k_count(const uint8_t *__restrict__ f, int64_t n,
-                                                      int64_t *counts) {
-  __shared__ int red[kScanBlock];
-  const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
-  red[threadIdx.x] = (i < n && f[i]) ? 1 : 0;
-  __syncthreads();
-  for (int s = kScanBlock / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-    __syncthreads();
+// exclusive scan, ordered write.  A thread takes 16 flags.  16.8 million
+// flags: k_count 7, k_scan 6, k_write_idx 11 us (46, 41 and 80 us with one
+// flag a thread, scans of 10 barriers and the block counts' scan in one
+// thread).
+constexpr int kScanThreads = 256, kScanPer = 16, kScanBlock = kScanThreads * kScanPer;
+
+// Bit k: flag i0 + k is set (none past n).
+__device__ __forceinline__ unsigned flag_bits(const uint8_t *__restrict__ f, int64_t i0, int64_t n) {
+  unsigned bits = 0;
+  if (i0 + kScanPer <= n && ((uintptr_t)f & 15) == 0) {
+    const uint4 v = *(const uint4 *)(f + i0);
+    const unsigned q[4] = {v.x, v.y, v.z, v.w};
+    // flags are bytes 0 or 1: bit 0 of byte b goes to bit 28 + b
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bits |= (q[k] * 0x10204080u) >> 28 << (4 * k);
+  } else {
+    for (int k = 0; k < kScanPer; ++k)
+      if (i0 + k < n && f[i0 + k]) bits |= 1u << k;
   }
-  if (threadIdx.x == 0) counts[blockIdx.x] = red[0];
+  return bits;
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_scan(int64_t *counts, int64_t nb, int64_t *total) {
-  __shared__ int64_t part[kScanBlock];
-  const int64_t per = (nb + kScanBlock - 1) / kScanBlock;
-  const int64_t b = threadIdx.x * per, e = b + per < nb ? b + per : nb;
-  int64_t s = 0;
-  for (int64_t i = b; i < e; ++i) s += counts[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int64_t run = 0;
-    for (int k = 0; k < kScanBlock; ++k) {
-      const int64_t v = part[k];
-      part[k] = run;
-      run += v;
-    }
-    *total = run;
+// Sum of v over the threads before this one of the block (T threads), and
+// over all of them (*total).
+template <int T>
+__device__ __forceinline__ int64_t block_scan(int64_t v, int64_t *total) {
+  __shared__ int64_t wsum[T / 64];
+  const int l = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int64_t x = v;   // inclusive sum over the wave
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const int64_t y = __shfl_up(x, d);
+    if (l >= d) x += y;
   }
+  if (l == 63) wsum[w] = x;
   __syncthreads();
-  int64_t run = part[threadIdx.x];
+  int64_t before = 0, all = 0;
+#pragma unroll
+  for (int k = 0; k < T / 64; ++k) {
+    if (k < w) before += wsum[k];
+    all += wsum[k];
+  }
+  *total = all;
+  return before + x - v;
+}
+
+__global__ __launch_bounds__(kScanThreads) void k_count(const uint8_t *__restrict__ f, int64_t n,
+                                                        int64_t *counts) {
+  const int64_t i0 = (int64_t)blockIdx.x * kScanBlock + threadIdx.x * kScanPer;
+  int64_t total;
+  block_scan<kScanThreads>(__popc(flag_bits(f, i0, n)), &total);
+  if (threadIdx.x == 0) counts[blockIdx.x] = total;
+}
+
+__global__ __launch_bounds__(1024) void k_scan(int64_t *counts, int64_t nb, int64_t *total) {
+  const int64_t per = (nb + 1023) / 1024;
+  const int64_t b = threadIdx.x * per, e = b + per < nb ? b + per : nb;
+  int64_t s = 0, all;
+  for (int64_t i = b; i < e; ++i) s += counts[i];
+  int64_t run = block_scan<1024>(s, &all);
   for (int64_t i = b; i < e; ++i) {
     const int64_t v = counts[i];
     counts[i] = run;
     run += v;
   }
+  if (threadIdx.x == 0) *total = all;
 }
 
-__global__ __launch_bounds__(kScanBlock) void k_write_idx(const uint8_t *__restrict__ f, int64_t n,
-                                                          const int64_t *offs, int64_t *idx) {
-  __shared__ int pre[kScanBlock];
-  const int64_t i = (int64_t)blockIdx.x * kScanBlock + threadIdx.x;
-  const int v = (i < n && f[i]) ? 1 : 0;
-  pre[threadIdx.x] = v;
-  __syncthreads();
-  // inclusive Hillis--Steele scan over the block
-  for (int s = 1; s < kScanBlock; s <<= 1) {
-    const int add = threadIdx.x >= s ? pre[threadIdx.x - s] : 0;
-    __syncthreads();
-    pre[threadIdx.x] += add;
-    __syncthreads();
-  }
-  if (v) idx[offs[blockIdx.x] + pre[threadIdx.x] - 1] = i;
+__global__ __launch_bounds__(kScanThreads) void k_write_idx(const uint8_t *__restrict__ f, int64_t n,
+                                                            const int64_t *offs, int64_t *idx) {
+  const int64_t i0 = (int64_t)blockIdx.x * kScanBlock + threadIdx.x * kScanPer;
+  unsigned bits = flag_bits(f, i0, n);
+  int64_t total;
+  int64_t at = offs[blockIdx.x] + block_scan<kScanThreads>(__popc(bits), &total);
+  for (; bits; bits &= bits - 1) idx[at++] = i0 + (__ffs(bits) - 1);
 }
 
 // label[idx[i]] = [max_j rec[j][i] >= 2]; -1 if any record is NaN.
@@ -1426,11 +1423,16 @@ hipError_t fused(sur_ctx *s, FusedArgs a, bool screen) {
   a.W2f = s->W.W2;
   a.W3f = s->W.W3p;
   a.W4f = s->W.W4p;
-  const dim3 grid(nblk(a.n, 128));   // 4 waves of 32 points
+  // few points: one tile per CU (256 of them) while that can be had
+  const dim3 g1(nblk(a.n, 16)), g2(nblk(a.n, 32)), g4(nblk(a.n, 64));
   if (screen)
-    hipLaunchKernelGGL(k_fused<true>, grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_net<4, 2, true>), g4, dim3(512), 0, st, a);
+  else if (a.n <= 16 * 256)
+    hipLaunchKernelGGL((k_net<1, 1, false>), g1, dim3(1024), 0, st, a);
+  else if (a.n <= 32 * 256)
+    hipLaunchKernelGGL((k_net<2, 1, false>), g2, dim3(1024), 0, st, a);
   else
-    hipLaunchKernelGGL(k_fused<false>, grid, dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_net<4, 2, false>), g4, dim3(512), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1852,12 +1854,12 @@ int sur_screen(sur_t s, const double *params, int64_t n, const sur_screen_opts *
   if (resolve) {
     const int64_t nb = (n + kScanBlock - 1) / kScanBlock;
     SUR_HIP(s, reserve_scan(s, n));
-    hipLaunchKernelGGL(k_count, dim3((unsigned)nb), dim3(kScanBlock), 0, s->stream, resolve, n,
+    hipLaunchKernelGGL(k_count, dim3((unsigned)nb), dim3(kScanThreads), 0, s->stream, resolve, n,
                        s->scan);
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(kScanBlock), 0, s->stream, s->scan, nb,
+    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s->stream, s->scan, nb,
                        s->scan + nb);
     if (resolve_idx)
-      hipLaunchKernelGGL(k_write_idx, dim3((unsigned)nb), dim3(kScanBlock), 0, s->stream,
+      hipLaunchKernelGGL(k_write_idx, dim3((unsigned)nb), dim3(kScanThreads), 0, s->stream,
                          resolve, n, s->scan, resolve_idx);
     SUR_HIP(s, hipGetLastError());
     SUR_HIP(s, hipMemcpyAsync(n_resolve, s->scan + nb, sizeof(int64_t), hipMemcpyDeviceToHost,

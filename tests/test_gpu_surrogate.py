@@ -364,6 +364,44 @@ def test_screen_matches_forward_and_compacts_in_order():
     assert np.array_equal(label.astype(bool)[ok], (pmax >= np.log(2))[ok])
 
 
+@pytest.mark.parametrize("n", [1, 17, 4096, 4097, 8192, 8193, 20000])
+def test_forward_tilings_give_the_same_bits(n):
+    """16, 32 and 64 points per block (up to 4096, up to 8192, and more): every
+    point's outputs are the same bits as in a call of at most 1000 points."""
+    import torch
+    sur = _sur()
+    x = torch.rand(n, 2, device="cuda", generator=torch.Generator("cuda").manual_seed(n)) * 2 - 1
+    with sur.Surrogate(max_batch=64) as s:
+        s.set_params(I.mlp_init(7))
+        y = s.forward(x)
+        parts = [s.forward(x[k:k + 1000].contiguous()) for k in range(0, n, 1000)]
+    assert torch.equal(y, torch.cat(parts))
+
+
+@pytest.mark.parametrize("n,shift", [(1, 0), (15, 0), (4095, 0), (4096, 0), (4097, 0), (5000, 1),
+                                     (1 << 20, 0), (4100000, 0), (4100000, 3)])
+def test_screen_compaction_sizes_and_alignment(n, shift):
+    """Re-solve lists around a thread's 16 flags, a block's 4096, and more than
+    1024 block counts, with the mask at an address that is not a multiple of
+    16 too: the positions of the mask's ones, in order."""
+    import torch
+    sur = _sur()
+    g = torch.Generator("cuda").manual_seed(n)
+    P = torch.rand(2, n, device="cuda", dtype=torch.float64, generator=g) + 0.5
+    with sur.Surrogate(max_batch=64) as s:
+        s.set_params(I.mlp_init(7))
+        s.set_norm(np.array([0.5, np.log(0.5)]), np.array([1.5, np.log(1.5)]),
+                   np.full(64, 0.6), np.full(64, 0.3))
+        out = s.screen_outputs(n, P.device)
+        mask = torch.zeros(n + 16, dtype=torch.uint8, device="cuda")[shift:shift + n]
+        pmax = s.screen(P, margin=0.0, spread=1e30, flag_margin=0.0)[2]
+        margin = float(torch.median(torch.abs(pmax - np.log(2))))   # half of the points
+        label, resolve, pmax, idx = s.screen(P, margin=margin, spread=1e30, flag_margin=0.0,
+                                             out=(out[0], mask, out[2], out[3]))
+        assert torch.equal(idx, torch.nonzero(resolve).flatten())
+        assert n < 1000 or 0 < len(idx) < n
+
+
 def test_epoch_graph_replays_equal_eager_steps():
     """sur_train_epoch captures an epoch's launches once and replays them with
     the current learning rate, step count and row order: after three epochs
