@@ -434,7 +434,7 @@ struct MKM {
   static constexpr int kMinWaves = DUAL ? 3 : 4;
   static constexpr bool kPrio = true;  // issue priority by remaining work
   static constexpr bool kLocate = true;  // y2 = y1': maxima can be located
-  static constexpr bool kDrive2 = DUAL;
+  static constexpr bool kDrive2 = DUAL, kDrive2PerSystem = PSYS;
   static constexpr int kF = 1;
   static constexpr bool kTangent = false;
   double K0, K1, K2, K3, K4, K5, K7, K9, K10, K49, K9h;  // K9h = K9 / 2
@@ -468,8 +468,9 @@ struct MKM {
       const double w2 = 2.0 * M_PI * (PSYS ? P[3 * n + i] : sh[9]);
       const double th = PSYS ? P[4 * n + i] : sh[10];
       dual = pa2 != 0.0;
-      K6 = pa2 * q2 / rhoL;
-      K8 = re * w2 * pa2 * q2 / (rhoL * cL);
+      // without a second drive its terms vanish whatever its frequency
+      K6 = dual ? pa2 * q2 / rhoL : 0.0;
+      K8 = dual ? re * w2 * pa2 * q2 / (rhoL * cL) : 0.0;
       K11 = w2 / w;                 // omega2 / omega1, correctly rounded
       thpi = th * M_1_PI;           // theta / pi
     }
@@ -522,8 +523,15 @@ struct MKM {
   }
   // Second drive: phi = its phase in cycles when the current phase began;
   // within the phase its angle is 2 pi (phi + K11 tau) + theta.
+  // A wave evaluates it in all lanes (on, set for each attempt) if one of its
+  // systems has a second drive, and always if the drive is shared, instead of
+  // branching in each of the six stages; the terms of a lane without one
+  // vanish (K6 = K8 = 0, angle 0).  45 x 45 systems, Dormand--Prince, shared
+  // drive: 16.1 -> 13.4 ms; 45 x 45 systems with a drive each, Cash--Karp:
+  // 54.2 -> 49.4 ms.
   double K6, K8, K11, thpi, phi;
-  bool dual;
+  double K11a, thpia, phia;   // K11, thpi, phi, or 0 without a second drive
+  bool dual, on;
   // A phase of length tp ended: the drive went through K11 tp cycles
   // (multiply and add rounded separately, then reduced modulo 1).
   __device__ void next_phase(double tp) {
@@ -545,6 +553,11 @@ struct MKM {
       k5c = K5 * c0;
       k7s = K7 * s0;
       k7c = K7 * c0;
+    }
+    if constexpr (DUAL) {
+      K11a = dual ? K11 : 0.0;
+      thpia = dual ? thpi : 0.0;
+      phia = dual ? phi : 0.0;
     }
   }
   // SC: the scheme; S: the stage (1..7); tau: its time; h: the attempted step.
@@ -635,9 +648,9 @@ struct MKM {
       fc = fma(k7c, co, -(k7s * so));
     }
     if constexpr (DUAL) {
-      if (dual) {
+      if (on) {
         double s2, c2;
-        sincospi_quarter(fma(2.0, fma(K11, tau, phi), thpi), &s2, &c2);
+        sincospi_quarter(fma(2.0, fma(K11a, tau, phia), thpia), &s2, &c2);
         fs = fma(K6, s2, fs);
         fc = fma(K8, c2, fc);
       }
@@ -1056,10 +1069,24 @@ __device__ __forceinline__ void step_fixed(const HotArgs &a, Mask act,
   h_try = in(trunc) ? a.t_phase - L.t : h_try;
   L.attempts++;
   const Mask cap = ballot(L.attempts >= a.cap);
-  if constexpr (SC == kDP)
-    dp_attempt(m, tabs, L.t, y, h_try, fs, L.nrhs, y5, err, k7);
-  else
-    ck_attempt(m, tabs, L.t, y, h_try, y5, err);
+  const auto attempt = [&]() {
+    if constexpr (SC == kDP)
+      dp_attempt(m, tabs, L.t, y, h_try, fs, L.nrhs, y5, err, k7);
+    else
+      ck_attempt(m, tabs, L.t, y, h_try, y5, err);
+  };
+  if constexpr (M::kDrive2) {
+    // one branch for the attempt; with a shared second drive none
+    if (!M::kDrive2PerSystem || (ballot(m.dual) & act)) {
+      m.on = true;
+      attempt();
+    } else {
+      m.on = false;
+      attempt();
+    }
+  } else {
+    attempt();
+  }
   double E;
   o.bad = error_ratio<D>(a.rtol, a.atol, y, y5, err, E);
   // Accept (E <= 1, or at the step-size floor) or reject, by selects.

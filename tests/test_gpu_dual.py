@@ -146,3 +146,32 @@ def test_km6_equals_km_with_the_same_values():
     b = gpu_ck(6, P6, y0, o, shared=sh[:7])
     assert np.array_equal(a.y, b.y) and np.array_equal(a.records, b.records)
     assert np.array_equal(a.stats, b.stats) and np.array_equal(a.phi, b.phi)
+
+
+@pytest.mark.parametrize("scheme,dt_max", [(O.CASH_KARP, 0.1), (O.DORMAND_PRINCE, 0.1),
+                                           (O.CASH_KARP, 0.2)])
+@pytest.mark.parametrize("off", ["none", "third", "all", "wave"])
+def test_km6_waves_with_and_without_a_second_drive(scheme, dt_max, off):
+    """Waves whose systems all, partly or nowhere have a second drive: a
+    system without one (amplitude 0) gives the bits of the single-drive model,
+    whatever its frequency and phase (NaN here) and whatever its neighbours
+    do; a system with one gives the same bits in either company."""
+    ens = _ens()
+    P6, y0 = km6_grid(16)
+    P6[5] = I.KM_WATER[7]
+    n = P6.shape[1]
+    i = np.arange(n)
+    single = {"none": i < 0, "third": i % 3 == 0, "all": i >= 0, "wave": i // 64 % 2 == 0}[off]
+    fluid = list(I.KM_WATER[:7])
+    o = O.Opts(n_phases=4, n_record=4, scheme=scheme, dt_max=dt_max)
+    kw = dict(solver=_solver(ens, scheme))
+    both = gpu_ck(6, P6, y0, o, shared=fluid, **kw)
+    one = gpu_ck(2, P6[:2], y0, o, shared=list(I.KM_WATER), **kw)
+    Q = P6.copy()
+    Q[2, single] = 0.0
+    Q[3:5, single] = np.nan
+    g = gpu_ck(6, Q, y0, o, shared=fluid, **kw)
+    for ref, k in ((one, single), (both, ~single)):
+        assert np.array_equal(g.y[..., k], ref.y[..., k])
+        assert np.array_equal(g.records[..., k], ref.records[..., k])
+        assert np.array_equal(g.stats[..., k], ref.stats[..., k])
