@@ -780,6 +780,7 @@ static int solve_rkck(ens_t h, const ens_solve_opts *o) {
   if (grid > cap) return fail(h, ENS_E_INVAL, "ens_solve: grid above resident capacity");
   ens::RkckArgs a;
   std::memset(&a, 0, sizeof(a));  // padding too: the struct is compared bytewise
+  a.prioritize = std::getenv("ENS_NO_PRIORITY") ? 0 : 1;
   ens::rkck_plan(cap, block, h->n, o->spread, h->use_order, &grid, &a);
 
   // records
@@ -850,7 +851,6 @@ static int solve_rkck(ens_t h, const ens_solve_opts *o) {
   a.v_stick = o->v_stick;
   a.max_steps = o->max_steps;
   a.max_event_iter = o->max_event_iter;
-  a.prioritize = std::getenv("ENS_NO_PRIORITY") ? 0 : 1;
   a.locate_max = o->locate_max ? 1 : 0;
   const bool fill_h = !h->h_init;
 

@@ -66,6 +66,7 @@ struct RkckArgs {
   int64_t max_steps;
   int32_t max_event_iter;
   int32_t prioritize;       // waves raise their issue priority by remaining work
+                            // (rkck_plan clears it where no two waves share a SIMD)
   int32_t locate_max;       // Keller--Miksis: maxima located on the step interpolant
 };
 

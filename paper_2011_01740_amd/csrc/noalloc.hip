@@ -200,6 +200,7 @@ extern "C" int ens_solve_noalloc(const ens_noalloc_args *a, const ens_solve_opts
   ka.R = R;
   ka.n_ens = a->n_ensembles;
   ka.refill = refill;
+  ka.prioritize = std::getenv("ENS_NO_PRIORITY") ? 0 : 1;
   ens::rkck_plan(cap, block, n, o->spread, a->order != nullptr, &grid, &ka);
   ka.t_phase = o->t_phase;
   ka.dt_min = o->dt_min;
@@ -211,7 +212,6 @@ extern "C" int ens_solve_noalloc(const ens_noalloc_args *a, const ens_solve_opts
   ka.v_stick = o->v_stick;
   ka.max_steps = o->max_steps;
   ka.max_event_iter = o->max_event_iter;
-  ka.prioritize = std::getenv("ENS_NO_PRIORITY") ? 0 : 1;
   ka.locate_max = o->locate_max ? 1 : 0;
   NA_HIP(ens::launch_rkck(kmodel, a->solver, block, grid, ka, s));
   return ENS_OK;
