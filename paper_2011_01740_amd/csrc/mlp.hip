@@ -779,6 +779,16 @@ struct Norm {
   float fmean[kOut], fstd[kOut];
 };
 
+// (passed by value: no copy from the caller's memory to wait for)
+__global__ void k_set_norm(Norm nm, Norm *out) {
+  const int j = threadIdx.x;
+  out->mean[j] = nm.mean[j];
+  out->stdv[j] = nm.stdv[j];
+  out->rstd[j] = nm.rstd[j];
+  out->fmean[j] = nm.fmean[j];
+  out->fstd[j] = nm.fstd[j];
+}
+
 // Network inputs and targets of n points: (p_A, ln f) mapped to [-1, 1]
 // (k_net<.., true> normalises its inputs the same way), and y[i][j] =
 // (ln rec[j][i] - mean_j) / std_j of the sorted records.  The rows of y are
@@ -1307,7 +1317,11 @@ struct sur_ctx {
   int64_t scan_cap = 0;
   int8_t *nlab = nullptr;     // exact labels of the training grid [G][G]
   LnEntry *lntab = nullptr;
-  double *fit = nullptr;      // means and standard deviations of sur_fit_norm
+  // Pinned host memory that kernels write small results to (the host reads
+  // them after its wait, without a copy): means and standard deviations of
+  // sur_fit_norm; a screen's number of points to re-solve (an 8-byte copy back
+  // took 9 of a small screen's 62 us)
+  double *pin = nullptr, *pin_d = nullptr;   // [2 kOut]: host's and device's address
   Moments *mom = nullptr;     // [kOut][blocks] (sur_fit_norm), grown as needed
   int64_t mom_nb = 0;
   int nlab_G = 0;
@@ -1406,7 +1420,7 @@ hipError_t ensure_infer(sur_ctx *s) {
 // Compaction scratch (block counts and their scan) for screens of up to n
 // points, grown when a larger screen comes.
 hipError_t reserve_scan(sur_ctx *s, int64_t n) {
-  const int64_t need = (n + kScanBlock - 1) / kScanBlock + 1;
+  const int64_t need = (n + kScanBlock - 1) / kScanBlock;
   if (need <= s->scan_cap) return hipSuccess;
   (void)hipFree(s->scan);
   s->scan = nullptr;
@@ -1612,8 +1626,11 @@ int sur_create(int32_t device, void *hip_stream, int64_t max_batch, sur_t *out) 
   A(cp3, B / kTR * kH); A(cp4, B / kTR * kOut);
   A(lpart, B / kTR); A(loss, 1);
   A(loss_acc, 1);
-  A(hyper, 5); A(adam_h, 6); A(lntab, kLnTab); A(fit, 2 * kOut);
+  A(hyper, 5); A(adam_h, 6); A(lntab, kLnTab);
 #undef A
+  if (e == hipSuccess)
+    e = hipHostMalloc((void **)&s->pin, 2 * kOut * sizeof(double), hipHostMallocMapped);
+  if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&s->pin_d, s->pin, 0);
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->cap_stream, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipMemsetAsync(s->P, 0, kNP * sizeof(float), s->stream);
   // the feature layer's gradients stay 0 (no kernel writes them)
@@ -1644,11 +1661,12 @@ int sur_destroy(sur_t s) {
                   s->W.W3p, s->W.W4p, s->norm, s->x, s->tgt,
                   s->a1, s->a2, s->a3, s->dz4, s->dz3, s->dz2, s->part2, s->part3,
                   s->part4, s->cp2, s->cp3, s->cp4, s->lpart,
-                  s->loss, s->loss_acc, s->scan, s->nlab, s->lntab, s->fit, s->mom, s->ix, s->iout};
+                  s->loss, s->loss_acc, s->scan, s->nlab, s->lntab, s->mom, s->ix, s->iout};
   for (void *p : ptrs) (void)hipFree(p);
   free_epoch_graph(s);
   (void)hipFree(s->hyper);
   (void)hipFree(s->adam_h);
+  if (s->pin) (void)hipHostFree(s->pin);
   if (s->cap_stream) (void)hipStreamDestroy(s->cap_stream);
   delete s;
   return ENS_OK;
@@ -1709,8 +1727,8 @@ int sur_set_norm(sur_t s, const double *in_lo, const double *in_hi, const double
                     std::fabs(out_mean[j]) <= 1e100;
   }
   DevGuard dg(s->device);
-  SUR_HIP(s, hipMemcpyAsync(s->norm, &nm, sizeof(nm), hipMemcpyHostToDevice, s->stream));
-  SUR_HIP(s, hipStreamSynchronize(s->stream));
+  hipLaunchKernelGGL(k_set_norm, dim3(1), dim3(kOut), 0, s->stream, nm, s->norm);
+  SUR_HIP(s, hipGetLastError());
   s->have_norm = true;
   return ENS_OK;
 }
@@ -1857,15 +1875,14 @@ int sur_screen(sur_t s, const double *params, int64_t n, const sur_screen_opts *
     hipLaunchKernelGGL(k_count, dim3((unsigned)nb), dim3(kScanThreads), 0, s->stream, resolve, n,
                        s->scan);
     hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s->stream, s->scan, nb,
-                       s->scan + nb);
+                       (int64_t *)s->pin_d);
     if (resolve_idx)
       hipLaunchKernelGGL(k_write_idx, dim3((unsigned)nb), dim3(kScanThreads), 0, s->stream,
                          resolve, n, s->scan, resolve_idx);
     SUR_HIP(s, hipGetLastError());
-    SUR_HIP(s, hipMemcpyAsync(n_resolve, s->scan + nb, sizeof(int64_t), hipMemcpyDeviceToHost,
-                              s->stream));
   }
   SUR_HIP(s, hipStreamSynchronize(s->stream));
+  if (resolve) std::memcpy(n_resolve, s->pin, sizeof(int64_t));
   return ENS_OK;
 }
 
@@ -1886,11 +1903,9 @@ int sur_fit_norm(sur_t s, const double *in_lo, const double *in_hi, const double
   }
   hipLaunchKernelGGL(k_moments, dim3((unsigned)nb), dim3(64 * kDsWaves), 0, s->stream, records, n,
                      few, s->lntab, s->mom);
-  hipLaunchKernelGGL(k_mean_std, dim3(kOut), dim3(256), 0, s->stream, s->mom, nb, s->fit);
+  hipLaunchKernelGGL(k_mean_std, dim3(kOut), dim3(256), 0, s->stream, s->mom, nb, s->pin_d);
   SUR_HIP(s, hipGetLastError());
-  double m[2 * kOut];
-  const double *sd = m + kOut;
-  SUR_HIP(s, hipMemcpyAsync(m, s->fit, sizeof(m), hipMemcpyDeviceToHost, s->stream));
+  const double *m = s->pin, *sd = m + kOut;
   SUR_HIP(s, hipStreamSynchronize(s->stream));
   for (int j = 0; j < kOut; ++j)
     if (!(sd[j] > 0.0) || !std::isfinite(m[j]))
