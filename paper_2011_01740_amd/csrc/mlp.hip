@@ -1572,17 +1572,93 @@ int ensure_epoch_graph(sur_ctx *s, const float *x, const float *y, int64_t n, co
 
 // Epoch e's row order: the training rows sorted by a hash of (seed, e, i)
 // (SplitMix64's output function of a Weyl sequence), i.e. a seeded uniformly
-// random permutation; equal keys keep index order.
-__global__ void k_epoch_keys(const int64_t *__restrict__ rows, int64_t n, uint64_t seed,
-                             int64_t epoch, unsigned long long *key, int64_t *val) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  uint64_t z = seed + 0x9E3779B97F4A7C15ull * (uint64_t)(epoch * n + i + 1);
+// random permutation; equal keys keep index order.  The orders of several
+// epochs are made at once: all their (epoch, row) pairs are sorted by the
+// hash, then, stably, by the epoch.
+__global__ void k_epoch_keys(int64_t n, int64_t count, uint64_t seed, int64_t epoch,
+                             unsigned long long *key, uint32_t *val) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= count) return;
+  uint64_t z = seed + 0x9E3779B97F4A7C15ull * (uint64_t)(epoch * n + p + 1);
   z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
   z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-  key[i] = (unsigned long long)(z ^ (z >> 31));
-  val[i] = rows[i];
+  key[p] = (unsigned long long)(z ^ (z >> 31));
+  val[p] = (uint32_t)p;
 }
+// A sorted pair p = epoch n + i as the key and the value of the second sort.
+__global__ void k_epoch_rows(const int64_t *__restrict__ rows, uint32_t n, int64_t count,
+                             const uint32_t *__restrict__ val, uint32_t *epoch, int64_t *row) {
+  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (p >= count) return;
+  const uint32_t e = val[p] / n;
+  epoch[p] = e;
+  row[p] = rows[val[p] - e * n];
+}
+
+// The row orders of up to `group` epochs at a time, [epochs][n], in one
+// allocation.  At most 2^20 pairs a group: a sort of 65536 pairs is 10 launches
+// of some 6 us, bound by their latency, and so is one of 10 times as many.  10
+// epochs of 65536 rows in batches of 4096: 4.31 -> 4.05 ms.
+constexpr int64_t kOrderPairs = 1 << 20;
+struct EpochOrders {
+  int64_t n, group;
+  size_t tmp = 0;
+  unsigned long long *key_in, *key_out;
+  uint32_t *val_in, *val_out;
+  int64_t *rows, *order;   // the second sort's values, in and out
+  void *sort_tmp;
+
+  size_t size(int64_t n_, int64_t epochs, hipStream_t st, hipError_t *e) {
+    n = n_;
+    group = n < kOrderPairs ? kOrderPairs / n : 1;
+    group = group < epochs ? group : epochs;
+    const size_t m = (size_t)(n * group);
+    size_t t1 = 0, t2 = 0;
+    *e = rocprim::radix_sort_pairs(nullptr, t1, (const unsigned long long *)nullptr,
+                                   (unsigned long long *)nullptr, (const uint32_t *)nullptr,
+                                   (uint32_t *)nullptr, m, 0u, 64u, st);
+    if (*e == hipSuccess)
+      *e = rocprim::radix_sort_pairs(nullptr, t2, (const uint32_t *)nullptr, (uint32_t *)nullptr,
+                                     (const int64_t *)nullptr, (int64_t *)nullptr, m, 0u, 32u, st);
+    tmp = t1 > t2 ? t1 : t2;
+    return 3 * part(m * 8) + 2 * part(m * 4) + tmp;
+  }
+  static size_t part(size_t bytes) { return (bytes + 255) & ~(size_t)255; }
+  void place(char *b) {
+    const size_t m = (size_t)(n * group);
+    key_in = (unsigned long long *)b;
+    key_out = (unsigned long long *)(b + part(m * 8));
+    order = (int64_t *)(b + 2 * part(m * 8));
+    val_in = (uint32_t *)(b + 3 * part(m * 8));
+    val_out = (uint32_t *)(b + 3 * part(m * 8) + part(m * 4));
+    rows = (int64_t *)key_in;   // the keys are done with by then
+    sort_tmp = b + 3 * part(m * 8) + 2 * part(m * 4);
+  }
+  // Orders of epochs first .. first + count - 1 (count <= group).
+  hipError_t make(const int64_t *rows_in, uint64_t seed, int64_t first, int64_t count,
+                  hipStream_t st) {
+    const int64_t m = n * count;
+    hipLaunchKernelGGL(k_epoch_keys, dim3(nblk(m, 256)), dim3(256), 0, st, n, m, seed, first,
+                       key_in, val_in);
+    hipError_t e = hipGetLastError();
+    size_t t = tmp;
+    if (e == hipSuccess)
+      e = rocprim::radix_sort_pairs(sort_tmp, t, key_in, key_out, val_in, val_out, (size_t)m, 0u,
+                                    64u, st);
+    if (e != hipSuccess) return e;
+    // one epoch: its rows are in order
+    int64_t *to = count > 1 ? rows : order;
+    hipLaunchKernelGGL(k_epoch_rows, dim3(nblk(m, 256)), dim3(256), 0, st, rows_in, (uint32_t)n, m,
+                       val_out, val_in, to);
+    e = hipGetLastError();
+    if (e != hipSuccess || count == 1) return e;
+    unsigned bits = 0;
+    while (((int64_t)1 << bits) < count) ++bits;
+    t = tmp;
+    return rocprim::radix_sort_pairs(sort_tmp, t, val_in, val_out, rows, order, (size_t)m, 0u,
+                                     bits, st);
+  }
+};
 
 }  // namespace
 
@@ -1954,24 +2030,21 @@ int sur_train_epochs(sur_t s, const float *x, const float *y, const int64_t *row
   if (epochs == 0) return ENS_OK;
   DevGuard dg(s->device);
   const int64_t nb = n / batch;
-  // device buffers of this call: sort keys and values, the epoch's order,
-  // the per-epoch hyper-parameters, the per-epoch losses, sort scratch
-  size_t tmp = 0;
-  SUR_HIP(s, rocprim::radix_sort_pairs(nullptr, tmp, (const unsigned long long *)nullptr,
-                                       (unsigned long long *)nullptr, (const int64_t *)nullptr,
-                                       (int64_t *)nullptr, (size_t)n, 0u, 64u, s->stream));
+  // device buffers of this call: the epochs' orders, the running epoch's, the
+  // per-epoch hyper-parameters, the per-epoch losses
+  EpochOrders eo;
+  hipError_t oe;
+  const size_t ob = (eo.size(n, epochs, s->stream, &oe) + 255) & ~(size_t)255;
+  SUR_HIP(s, oe);
   const size_t kb = ((size_t)n * 8 + 255) & ~(size_t)255;
   const size_t hb = ((size_t)epochs * 5 * sizeof(double) + 255) & ~(size_t)255;
   const size_t lb = ((size_t)epochs * sizeof(float) + 255) & ~(size_t)255;
   char *buf = nullptr;
-  SUR_HIP(s, hipMalloc((void **)&buf, 4 * kb + hb + lb + tmp));
-  auto *key_in = (unsigned long long *)buf;
-  auto *key_out = (unsigned long long *)(buf + kb);
-  auto *val_in = (int64_t *)(buf + 2 * kb);
-  auto *order = (int64_t *)(buf + 3 * kb);
-  auto *hyp = (double *)(buf + 4 * kb);
-  auto *loss_d = (float *)(buf + 4 * kb + hb);
-  void *sort_tmp = buf + 4 * kb + hb + lb;
+  SUR_HIP(s, hipMalloc((void **)&buf, ob + kb + hb + lb));
+  eo.place(buf);
+  auto *order = (int64_t *)(buf + ob);
+  auto *hyp = (double *)(buf + ob + kb);
+  auto *loss_d = (float *)(buf + ob + kb + hb);
   std::vector<double> h((size_t)epochs * 5);
   for (int64_t e = 0; e < epochs; ++e) {
     h[5 * e + 0] = lr[e];
@@ -1985,12 +2058,11 @@ int sur_train_epochs(sur_t s, const float *x, const float *y, const int64_t *row
   int rc = ENS_OK;
   if (err == hipSuccess) rc = ensure_epoch_graph(s, x, y, n, order, batch);
   for (int64_t e = 0; err == hipSuccess && rc == ENS_OK && e < epochs; ++e) {
-    hipLaunchKernelGGL(k_epoch_keys, dim3(nblk(n, 256)), dim3(256), 0, s->stream, rows, n,
-                       (uint64_t)seed, e, key_in, val_in);
-    err = hipGetLastError();
+    if (e % eo.group == 0)
+      err = eo.make(rows, seed, e, epochs - e < eo.group ? epochs - e : eo.group, s->stream);
     if (err == hipSuccess)
-      err = rocprim::radix_sort_pairs(sort_tmp, tmp, key_in, key_out, val_in, order, (size_t)n,
-                                      0u, 64u, s->stream);
+      err = hipMemcpyAsync(order, eo.order + e % eo.group * n, (size_t)n * sizeof(int64_t),
+                           hipMemcpyDeviceToDevice, s->stream);
     if (err == hipSuccess)
       err = hipMemcpyAsync(s->hyper, hyp + 5 * e, 5 * sizeof(double), hipMemcpyDeviceToDevice,
                            s->stream);

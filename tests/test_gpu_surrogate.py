@@ -534,3 +534,41 @@ def test_train_epochs_equals_single_epochs_with_its_orders():
         single = s.get_params()
     assert np.array_equal(multi, single)
     assert np.allclose(losses, single_losses, rtol=0, atol=0)
+
+
+@pytest.mark.parametrize("n,epochs", [(500, 1), (500, 9), (300000, 4), (349525, 4), (600000, 2)])
+def test_epoch_orders_made_in_groups(n, epochs):
+    """Epochs whose orders are made 1, 9, 3 (and 1 left), 3 (the largest n for
+    3; and 1 left) and 1 at a time: losses and parameters are those of single
+    epochs with the documented orders."""
+    import torch
+    sur = _sur()
+    from paper_2011_01740_amd import ens
+    batch = min(65536, n // 64 * 64)
+    total = n + 77
+    x, t = _data(1000, 11)
+    k = torch.arange(total, device="cuda") % 1000
+    xd, td = torch.from_numpy(x).cuda()[k].contiguous(), torch.from_numpy(t).cuda()[k].contiguous()
+    rows = np.random.default_rng(3).permutation(total)[:n].astype(np.int64)
+    rd = torch.from_numpy(rows).cuda()
+    lrs = [1e-3 * (e + 1) for e in range(epochs)]
+    flat = _f32_params(12)
+    with sur.Surrogate(max_batch=batch) as s:
+        s.set_params(flat)
+        losses = s.train_epochs(xd, td, rd, batch, lrs, 99)
+        multi = s.get_params()
+        s.set_params(flat)
+        perm = torch.empty(n, dtype=torch.int64, device="cuda")
+        L = sur._lib()
+        single = []
+        for e, lr in enumerate(lrs):
+            s.set_adam(lr=lr)
+            perm.copy_(torch.from_numpy(_epoch_order(rows, 99, e)))
+            loss = ens.C.c_float()
+            sur._check(L.sur_train_epoch(s.h, ens.C.c_void_p(xd.data_ptr()),
+                                         ens.C.c_void_p(td.data_ptr()), n,
+                                         ens.C.c_void_p(perm.data_ptr()), batch,
+                                         ens.C.byref(loss)), s.h)
+            single.append(loss.value)
+        assert np.array_equal(multi, s.get_params())
+    assert np.array_equal(np.asarray(losses, np.float32), np.asarray(single, np.float32))
