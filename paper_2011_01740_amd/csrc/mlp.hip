@@ -1192,7 +1192,7 @@ __global__ void k_node_label(const double *__restrict__ rec, int64_t n, int8_t *
 
 // Deterministic compaction of the re-solve mask: block counts, one-block
 // exclusive scan, ordered write.  A thread takes 16 flags.  16.8 million
-// flags: k_count 7, k_scan 6, k_write_idx 11 us (46, 41 and 80 us with one
+// flags: k_count 5, k_scan 5, k_write_idx 12 us (46, 41 and 80 us with one
 // flag a thread, scans of 10 barriers and the block counts' scan in one
 // thread).
 constexpr int kScanThreads = 256, kScanPer = 16, kScanBlock = kScanThreads * kScanPer;
