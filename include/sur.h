@@ -95,8 +95,7 @@ int sur_set_norm(sur_t s, const double *in_lo, const double *in_hi,
  * (consecutive record slots, in any order).  Writes x [n][2] (normalised
  * inputs) and y [n][SUR_OUT] (each point's ln y1max in decreasing order,
  * standardised) as float, all device pointers.  Uses the bounds and
- * standardisation set by sur_set_norm.  The sorted copy of the records
- * lives in handle-owned scratch (grown on first use). */
+ * standardisation set by sur_set_norm. */
 int sur_build_dataset(sur_t s, const double *params, const double *records, int64_t n,
                       float *x, float *y);
 
@@ -105,7 +104,10 @@ int sur_build_dataset(sur_t s, const double *params, const double *records, int6
  * in decreasing order, as sur_build_dataset does), mean and standard
  * deviation of ln y1max over the n points; they become the handle's output
  * standardisation (input bounds as given here) and are copied to out_mean /
- * out_std (host, SUR_OUT doubles each, may be NULL). */
+ * out_std (host, SUR_OUT doubles each, may be NULL).  A rank that is the same
+ * at every point has no spread and is refused, as a non-finite one is.  The
+ * partial moments live in handle-owned scratch (6 bytes a point, grown as
+ * needed). */
 int sur_fit_norm(sur_t s, const double *in_lo, const double *in_hi, const double *records,
                  int64_t n, double *out_mean, double *out_std);
 
