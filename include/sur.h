@@ -150,8 +150,8 @@ int sur_gradients(sur_t s, const float *x, const float *target, int64_t m, float
                   float *loss, int32_t where);
 
 /* Network output (standardised) for m inputs x [m][2] -> out [m][SUR_OUT].
- * One launch of the fused inference kernel (every layer, 32 points per
- * wave) for device arrays; host arrays pass through the handle's staging
+ * One launch of the fused inference kernel (every layer; one for every 2^28
+ * points) for device arrays; host arrays pass through the handle's staging
  * buffers 65,536 rows at a time.  m may be any size >= 0. */
 int sur_forward(sur_t s, const float *x, int64_t m, float *out, int32_t where);
 
@@ -184,8 +184,8 @@ int sur_reserve(sur_t s, int64_t n_screen);
  * (predicted max_j ln y1max), resolve_idx [n] int64 receiving the indices of
  * the points to re-solve in ascending order; *n_resolve (host) their count.
  * Any output pointer except n_resolve may be NULL.  All array pointers are
- * device memory.  The network and the screening rule run as one launch over
- * all n points (the inputs normalised in the kernel, no intermediate arrays);
+ * device memory.  The network and the screening rule run as one launch for
+ * every 2^28 points (the inputs normalised in the kernel, no intermediate arrays);
  * the re-solve list is then compacted in a fixed order.  Returns when the
  * outputs are complete. */
 int sur_screen(sur_t s, const double *params, int64_t n, const sur_screen_opts *opts,

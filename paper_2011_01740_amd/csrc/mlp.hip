@@ -994,7 +994,8 @@ __global__ __launch_bounds__(256) void k_mean_std(const Moments *__restrict__ pa
 
 struct FusedArgs {
   int64_t n;                       // points
-  const double *prm;               // screen: sweep parameters [2][n] (p_A, f)
+  const double *prm;               // screen: sweep parameters [2][ldp] (p_A, f)
+  int64_t ldp;
   double lo0, sc0, lo1, sc1;       //   and their normalisation
   const float *x;                  // forward: normalised inputs [n][2]
   float *out;                      // forward: network outputs [n][64]
@@ -1053,7 +1054,7 @@ __global__ __launch_bounds__(64 * 16 / NF, 4) void k_net(FusedArgs a) {
     const int64_t r = r0 + t < a.n ? r0 + t : a.n - 1;
     if (SCREEN) {
       xs[t][0] = (float)(fma(a.prm[r] - a.lo0, a.sc0, -1.0));
-      xs[t][1] = (float)(fma(log(a.prm[a.n + r]) - a.lo1, a.sc1, -1.0));
+      xs[t][1] = (float)(fma(log(a.prm[a.ldp + r]) - a.lo1, a.sc1, -1.0));
     } else {
       xs[t][0] = a.x[2 * r];
       xs[t][1] = a.x[2 * r + 1];
@@ -1432,13 +1433,12 @@ hipError_t reserve_scan(sur_ctx *s, int64_t n) {
   return e;
 }
 
-// The fused inference of n points (n > 0).
-hipError_t fused(sur_ctx *s, FusedArgs a, bool screen) {
-  hipStream_t st = s->stream;
-  a.P = s->P;
-  a.W2f = s->W.W2;
-  a.W3f = s->W.W3p;
-  a.W4f = s->W.W4p;
+// The fused inference of n points (n > 0), kNetPoints a launch: a launch's
+// threads are counted in 32 bits (a larger grid is cut without an error), and
+// k_net<4, 2> takes 8 a point.
+constexpr int64_t kNetPoints = 1 << 28;
+static_assert(kNetPoints * 8 <= UINT32_MAX && kNetPoints % 64 == 0, "threads of a launch");
+hipError_t fused_launch(hipStream_t st, const FusedArgs &a, bool screen) {
   // few points: one tile per CU (256 of them) while that can be had
   const dim3 g1(nblk(a.n, 16)), g2(nblk(a.n, 32)), g4(nblk(a.n, 64));
   if (screen)
@@ -1450,6 +1450,27 @@ hipError_t fused(sur_ctx *s, FusedArgs a, bool screen) {
   else
     hipLaunchKernelGGL((k_net<4, 2, false>), g4, dim3(512), 0, st, a);
   return hipGetLastError();
+}
+hipError_t fused(sur_ctx *s, FusedArgs a, bool screen) {
+  a.P = s->P;
+  a.W2f = s->W.W2;
+  a.W3f = s->W.W3p;
+  a.W4f = s->W.W4p;
+  const int64_t n = a.n;
+  for (int64_t first = 0;; first += kNetPoints) {
+    a.n = n - first < kNetPoints ? n - first : kNetPoints;
+    const hipError_t e = fused_launch(s->stream, a, screen);
+    if (e != hipSuccess || first + a.n == n) return e;
+    if (screen) {
+      a.prm += kNetPoints;
+      if (a.label) a.label += kNetPoints;
+      if (a.resolve) a.resolve += kNetPoints;
+      if (a.pmax) a.pmax += kNetPoints;
+    } else {
+      a.x += kNetPoints * kIn;
+      a.out += kNetPoints * kOut;
+    }
+  }
 }
 
 // The source of a step's Adam constants: hyper-parameters from device memory
@@ -1930,6 +1951,7 @@ int sur_screen(sur_t s, const double *params, int64_t n, const sur_screen_opts *
   std::memset(&a, 0, sizeof(a));
   a.n = n;
   a.prm = params;
+  a.ldp = n;
   a.lo0 = s->in_lo[0];
   a.sc0 = sc0;
   a.lo1 = s->in_lo[1];
