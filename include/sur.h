@@ -104,8 +104,9 @@ int sur_build_dataset(sur_t s, const double *params, const double *records, int6
  * in decreasing order, as sur_build_dataset does), mean and standard
  * deviation of ln y1max over the n points; they become the handle's output
  * standardisation (input bounds as given here) and are copied to out_mean /
- * out_std (host, SUR_OUT doubles each, may be NULL).  A rank that is the same
- * at every point has no spread and is refused, as a non-finite one is.  The
+ * out_std (host, SUR_OUT doubles each, may be NULL).  A spread of 0 or a
+ * non-finite one is refused; a rank that is the same at every point has the
+ * spread that the rounding of its sums leaves, 0 or about 1e-16.  The
  * partial moments live in handle-owned scratch (6 bytes a point, grown as
  * needed). */
 int sur_fit_norm(sur_t s, const double *in_lo, const double *in_hi, const double *records,

@@ -963,6 +963,43 @@ __global__ __launch_bounds__(256) void k_mean_std(const Moments *__restrict__ pa
   }
 }
 
+// The ranks (bits of `ranks`) whose spread is at the rounding of their
+// logarithms, as where every point has the same record: what is then taken for
+// the spread, and whether there is any, is the rounding of the mean, so the order of
+// the sums is part of the result.  It is 256 partial sums of the points t,
+// t + 256, ..., added by a tree, of the logarithms, then of the squared
+// deviations from the rounded mean.  One block per rank.  Rare: every block
+// sorts every point, twice.
+__global__ __launch_bounds__(256) void k_rounding_spread(const double *__restrict__ rec, int64_t n,
+                                                         uint64_t ranks, double *fit) {
+  __shared__ double red[256];
+  const int j = blockIdx.x, t = threadIdx.x;
+  if (!(ranks >> j & 1)) return;
+  double mean = 0.0;
+  for (int pass = 0; pass < 2; ++pass) {
+    double s = 0.0;
+    for (int64_t i = t; i < n; i += 256) {
+      double v[kOut];
+      sorted_records(rec, n, i, v);
+      double x = v[0];
+#pragma unroll
+      for (int l = 1; l < kOut; ++l) x = l == j ? v[l] : x;
+      const double d = log(x) - mean;   // pass 0: the logarithm
+      s = pass == 0 ? s + d : fma(d, d, s);
+    }
+    red[t] = s;
+    __syncthreads();
+    for (int k = 128; k > 0; k >>= 1) {
+      if (t < k) red[t] += red[t + k];
+      __syncthreads();
+    }
+    const double total = red[0] / (double)n;
+    __syncthreads();
+    if (pass == 0) mean = total;
+    if (t == 0) fit[pass * kOut + j] = pass == 0 ? total : sqrt(total);
+  }
+}
+
 // ---------------------------------------------------------------- fused inference
 // The whole network in one kernel, for a tile of 16 NJ points per block.
 // The products are taken transposed, Z^T = W A^T (MFMA rows = output features,
@@ -2006,6 +2043,16 @@ int sur_fit_norm(sur_t s, const double *in_lo, const double *in_hi, const double
   SUR_HIP(s, hipGetLastError());
   const double *m = s->pin, *sd = m + kOut;
   SUR_HIP(s, hipStreamSynchronize(s->stream));
+  // spreads within 4 ulp of the logarithms
+  uint64_t ranks = 0;
+  for (int j = 0; j < kOut; ++j)
+    if (sd[j] <= 0x1p-50 * std::fabs(m[j])) ranks |= (uint64_t)1 << j;
+  if (ranks) {
+    hipLaunchKernelGGL(k_rounding_spread, dim3(kOut), dim3(256), 0, s->stream, records, n, ranks,
+                       s->pin_d);
+    SUR_HIP(s, hipGetLastError());
+    SUR_HIP(s, hipStreamSynchronize(s->stream));
+  }
   for (int j = 0; j < kOut; ++j)
     if (!(sd[j] > 0.0) || !std::isfinite(m[j]))
       return sfail(s, ENS_E_INVAL, "sur_fit_norm: records give a non-positive or non-finite spread");

@@ -1,5 +1,7 @@
 """The surrogate's calls at the ends of their ranges: screens and forwards of
-more points than one launch takes."""
+more points than one launch takes, and records without spread."""
+import decimal
+
 import numpy as np
 import pytest
 
@@ -73,3 +75,64 @@ def test_forward_of_more_points_than_a_launch_takes():
             assert torch.equal(y[k:k + part], s.forward(x[k:k + part]))
     del x, y
     torch.cuda.empty_cache()
+
+
+def _firm_logs(count, seed):
+    """Values whose logarithm lies within 0.2 ulp of a double, so that every
+    logarithm with an error below 0.8 ulp returns that double."""
+    rng = np.random.default_rng(seed)
+    out = []
+    with decimal.localcontext() as ctx:
+        ctx.prec = 40
+        while len(out) < count:
+            c = float(np.exp(rng.normal()))
+            exact = decimal.Decimal(c).ln()
+            v = float(exact)
+            if abs(exact - decimal.Decimal(v)) <= decimal.Decimal(0.2 * np.spacing(abs(v))):
+                out.append((c, v))
+    return out
+
+
+def _equal_points(v, n):
+    """Mean and standard deviation of n equal values v: 256 partial sums of
+    the points t, t + 256, ... in order, added by a tree, the deviation from
+    the rounded mean likewise."""
+    def total(x):
+        q, rem = divmod(n, 256)
+        sums = np.cumsum(np.concatenate([[0.0], np.full(q + 1, x)]))   # (adds one after another)
+        red = np.where(np.arange(256) < rem, sums[q + 1], sums[q])
+        k = 128
+        while k:
+            red[:k] += red[k:2 * k]
+            k //= 2
+        return red[0]
+    mean = total(v) / n
+    return mean, np.sqrt(total((v - mean) ** 2) / n)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 63, 64, 65, 255, 1000, 16384, 16385, 20000])
+@pytest.mark.parametrize("ranks", [64, 1])
+def test_fit_norm_of_equal_points(n, ranks):
+    """A rank that is the same at every point has the spread that rounding of
+    its sums leaves: none, and the call is refused, or about 1e-16, and it is
+    fitted.  All ranks equal, or the largest one only.  Mean and refusal are
+    exact; the deviation, a sum of at most 79 + 8 squares, to 1e-13."""
+    import torch
+    sur = _sur()
+    lo, hi = np.array([0.5, -1.0]), np.array([1.5, 1.0])
+    rng = np.random.default_rng(n)
+    for c, v in _firm_logs(12, 5):
+        rec = np.full((64, n), c)
+        if ranks == 1:
+            rec[1:] = c * rng.uniform(0.2, 0.9, (63, n))
+        rd = torch.from_numpy(rec).cuda()
+        mean, std = _equal_points(v, n)
+        got = np.empty((2, 64))
+        with sur.Surrogate(max_batch=64) as s:
+            rc = sur._lib().sur_fit_norm(s.h, sur._dptr(lo), sur._dptr(hi),
+                                         sur.ens.C.c_void_p(rd.data_ptr()), n,
+                                         sur._dptr(got[0]), sur._dptr(got[1]))
+        assert (rc == 0) == (std > 0.0 and n > 1), (c, std)
+        if rc == 0:
+            assert np.all(got[0, :ranks] == mean)
+            assert np.allclose(got[1, :ranks], std, rtol=1e-13, atol=0.0)
