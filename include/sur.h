@@ -139,7 +139,8 @@ int sur_train_epoch(sur_t s, const float *x, const float *y, int64_t n, const in
  * order).  One epoch's launches are captured as a graph and replayed with
  * each epoch's order, learning rate and step count from device memory, with
  * no host synchronisation between epochs.  losses (host, `epochs` floats,
- * may be NULL) receives each epoch's mean batch loss.  The handle's Adam
+ * may be NULL) receives each epoch's mean batch loss.  n is at most
+ * 2^32 - 256 (ENS_E_INVAL above).  The handle's Adam
  * betas / epsilon apply; its learning rate is not changed. */
 int sur_train_epochs(sur_t s, const float *x, const float *y, const int64_t *rows, int64_t n,
                      int64_t batch, int64_t epochs, const double *lr, uint64_t seed,

@@ -1660,6 +1660,9 @@ __global__ void k_epoch_rows(const int64_t *__restrict__ rows, uint32_t n, int64
 // of some 6 us, bound by their latency, and so is one of 10 times as many.  10
 // epochs of 65536 rows in batches of 4096: 4.31 -> 4.05 ms.
 constexpr int64_t kOrderPairs = 1 << 20;
+// Rows of an epoch: a launch over them, in blocks of 256 threads, has fewer
+// than 2^32 threads, and a pair's number fits val.
+constexpr int64_t kEpochRows = ((int64_t)1 << 32) - 256;
 struct EpochOrders {
   int64_t n, group;
   size_t tmp = 0;
@@ -2095,6 +2098,8 @@ int sur_train_epochs(sur_t s, const float *x, const float *y, const int64_t *row
   if (int rc = check_batch(s, batch)) return rc;
   if (!x || !y || !rows || n < batch || epochs < 0 || (epochs > 0 && !lr))
     return sfail(s, ENS_E_INVAL, "sur_train_epochs: bad arguments");
+  if (n > kEpochRows)
+    return sfail(s, ENS_E_INVAL, "sur_train_epochs: more than 2^32 - 256 rows");
   for (int64_t e = 0; e < epochs; ++e)
     if (!(lr[e] > 0)) return sfail(s, ENS_E_INVAL, "sur_train_epochs: learning rates must be > 0");
   if (epochs == 0) return ENS_OK;

@@ -136,3 +136,21 @@ def test_fit_norm_of_equal_points(n, ranks):
         if rc == 0:
             assert np.all(got[0, :ranks] == mean)
             assert np.allclose(got[1, :ranks], std, rtol=1e-13, atol=0.0)
+
+
+@pytest.mark.parametrize("n", [2**32 - 255, 2**32, 2**32 + 64, 2**40])
+def test_train_epochs_refuses_rows_beyond_32_bits(n):
+    """Refused before anything is allocated or read (the row list here is one
+    row long): more rows than a launch has threads or a pair's number bits."""
+    import torch
+    sur = _sur()
+    from paper_2011_01740_amd import ens
+    C = ens.C
+    z = torch.zeros(64, device="cuda")
+    rows = torch.zeros(1, dtype=torch.int64, device="cuda")
+    lr = np.array([1e-3])
+    with sur.Surrogate(max_batch=64) as s:
+        rc = sur._lib().sur_train_epochs(s.h, C.c_void_p(z.data_ptr()), C.c_void_p(z.data_ptr()),
+                                         C.c_void_p(rows.data_ptr()), n, 64, 1, sur._dptr(lr), 1,
+                                         None)
+    assert rc == ens.ENS_E_INVAL
