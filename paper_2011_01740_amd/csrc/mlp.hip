@@ -2111,13 +2111,14 @@ int sur_train_epochs(sur_t s, const float *x, const float *y, const int64_t *row
   hipError_t oe;
   const size_t ob = (eo.size(n, epochs, s->stream, &oe) + 255) & ~(size_t)255;
   SUR_HIP(s, oe);
-  const size_t kb = ((size_t)n * 8 + 255) & ~(size_t)255;
+  // (orders made one at a time are read in place)
+  const size_t kb = eo.group > 1 ? ((size_t)n * 8 + 255) & ~(size_t)255 : 0;
   const size_t hb = ((size_t)epochs * 5 * sizeof(double) + 255) & ~(size_t)255;
   const size_t lb = ((size_t)epochs * sizeof(float) + 255) & ~(size_t)255;
   char *buf = nullptr;
   SUR_HIP(s, hipMalloc((void **)&buf, ob + kb + hb + lb));
   eo.place(buf);
-  auto *order = (int64_t *)(buf + ob);
+  auto *order = eo.group > 1 ? (int64_t *)(buf + ob) : eo.order;
   auto *hyp = (double *)(buf + ob + kb);
   auto *loss_d = (float *)(buf + ob + kb + hb);
   std::vector<double> h((size_t)epochs * 5);
@@ -2135,7 +2136,7 @@ int sur_train_epochs(sur_t s, const float *x, const float *y, const int64_t *row
   for (int64_t e = 0; err == hipSuccess && rc == ENS_OK && e < epochs; ++e) {
     if (e % eo.group == 0)
       err = eo.make(rows, seed, e, epochs - e < eo.group ? epochs - e : eo.group, s->stream);
-    if (err == hipSuccess)
+    if (err == hipSuccess && eo.group > 1)
       err = hipMemcpyAsync(order, eo.order + e % eo.group * n, (size_t)n * sizeof(int64_t),
                            hipMemcpyDeviceToDevice, s->stream);
     if (err == hipSuccess)

@@ -154,3 +154,38 @@ def test_train_epochs_refuses_rows_beyond_32_bits(n):
                                          C.c_void_p(rows.data_ptr()), n, 64, 1, sur._dptr(lr), 1,
                                          None)
     assert rc == ens.ENS_E_INVAL
+
+
+def test_train_epochs_scratch_of_orders_made_one_at_a_time():
+    """An epoch of 2^27 rows takes less than 48 bytes a row of the card: keys
+    twice, pair numbers twice, the order (32 bytes a row) and the sort's
+    copies of a key and a number (12)."""
+    import threading
+    import torch
+    sur = _sur()
+    _need_memory(16)
+    n, batch = 2**27, 65536
+    rows = torch.arange(n, device="cuda") % 64
+    x = torch.rand(64, 2, device="cuda") * 2 - 1
+    y = torch.rand(64, 64, device="cuda")
+    least, done = [2**62], threading.Event()
+
+    def watch():
+        while not done.is_set():
+            least[0] = min(least[0], torch.cuda.mem_get_info()[0])
+            done.wait(0.002)
+    with sur.Surrogate(max_batch=batch) as s:
+        s.set_params(I.mlp_init(7))
+        s.train_epochs(x, y, rows[:2 * batch], batch, [1e-3], 1)
+        torch.cuda.empty_cache()
+        free = torch.cuda.mem_get_info()[0]
+        t = threading.Thread(target=watch)
+        t.start()
+        try:
+            losses = s.train_epochs(x, y, rows, batch, [1e-3], 1)
+        finally:
+            done.set()
+            t.join()
+    print(f"{(free - least[0]) / n:.2f} bytes a row")
+    assert np.all(np.isfinite(losses))
+    assert 40 * n < free - least[0] < 48 * n
