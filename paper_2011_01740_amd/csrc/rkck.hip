@@ -125,11 +125,20 @@ __device__ __forceinline__ Mask uniform(Mask m) {
 __device__ __forceinline__ uint32_t uniform32(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
 }
-// n + 1 in the lanes of m, as one add with the mask as its carry.  m is the
-// result of scalar instructions, which a vector instruction may read at once.
-__device__ __forceinline__ uint32_t count(uint32_t n, Mask m) {
+// The lanes outside m.  m passes through an empty asm in scalar registers, so
+// the complement is a scalar instruction, whose result a vector instruction
+// may read at once (the compiler would fold the complement of a compare into the
+// compare otherwise).
+__device__ __forceinline__ Mask outside(Mask m) {
+  asm("" : "+s"(m));
+  return ~m;
+}
+// n + 1 in the lanes outside m, as one add with the mask as its carry: a mask
+// that a vector compare has just written would need a wait, which the compiler
+// does not put in front of inline assembly.
+__device__ __forceinline__ uint32_t count_outside(uint32_t n, Mask m) {
   Mask carry;
-  asm("v_addc_co_u32 %0, %1, %2, 0, %3" : "=v"(n), "=s"(carry) : "v"(n), "s"(m));
+  asm("v_addc_co_u32 %0, %1, %2, 0, %3" : "=v"(n), "=s"(carry) : "v"(n), "s"(outside(m)));
   return n;
 }
 
@@ -1091,10 +1100,10 @@ __device__ __forceinline__ void step_fixed(const HotArgs &a, Mask act,
   o.bad = error_ratio<D>(a.rtol, a.atol, y, y5, err, E);
   // Accept (E <= 1, or at the step-size floor) or reject, by selects.
   const Mask over = ballot(E > 1.0), rej = over & ballot(h_try > a.dt_min);
-  const Mask acc = ~(rej | o.bad);
+  const Mask not_acc = rej | o.bad, acc = outside(not_acc);
   const double fac = step_factor(kCtl, E, in(acc));
   const double h_new = clampd(h_try * fac, a.dt_min, a.dt_max);
-  L.accepted = count(L.accepted, acc);
+  L.accepted = count_outside(L.accepted, not_acc);
   if constexpr (LOC) {
     if (in(acc & act & ballot(y[1] > 0.0) & ballot(y5[1] <= 0.0))) {
       // the maximum of y1 between the step points, on the interpolant
