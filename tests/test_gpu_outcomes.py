@@ -7,6 +7,7 @@ import pytest
 
 import oracle as O
 from paper_2011_01740_amd import inputs as I
+from tests.parity import CK_ATOL, CK_RTOL, PERTURB, close, per_system, sensitivity_mask
 from tests.test_gpu_rkck import _ens, gpu_ck
 
 pytestmark = pytest.mark.gpu
@@ -97,3 +98,40 @@ def test_non_finite_component_stops_the_system(model, tangent, scheme):
     assert not np.any(g.status[ok] & O.SYS_NONFINITE)
     assert np.all(np.isfinite(g.y[:, ok])) and np.all(g.stats[O.ST_PHASES][ok] == 2)
     assert np.all(g.y[:, ok] == g.y[:, 1:2])
+
+
+@pytest.mark.parametrize("scheme", SCHEMES)
+@pytest.mark.parametrize("model,dt,tol", [(0, 0.05, 1e-11), (2, 1e-3, 1e-9), (3, 0.01, 5e-8)])
+def test_step_size_floor(model, dt, tol, scheme):
+    """Every step at the floor (dt0 = dt_min = dt_max), over the error bound in
+    some systems and within it in their neighbours: status, accepted, rejected,
+    event-retry and evaluation counts are the oracle's, the state to the
+    adaptive tolerance.  Compared are the systems whose outcome is the same
+    at half and twice the bound and for a perturbed start.  (The valves are
+    those that stay off their seat: below a flow of 1 or so every change of
+    the start's last digits gives other impacts, in the oracle too.)"""
+    n = 70
+    if model == 0:
+        P, y0, sh, kw = *I.quad_linspace(n), None, dict(t_phase=0.5, n_phases=3)
+    elif model == 2:
+        P, y0, sh, kw = *I.km_grid(7, 10), I.KM_WATER, dict(t_phase=0.1, n_phases=2)
+    else:
+        P, y0, sh, kw = *I.prv_linspace(n, 3.0, 10.0), I.PRV_DEFAULT, dict(n_phases=2)
+
+    def oracle(f=1.0, eps=0.0):
+        o = O.Opts(dt0=dt, dt_min=dt, dt_max=dt, rtol=f * tol, atol=f * tol, n_record=4,
+                   max_steps=2000, scheme=scheme, **kw)
+        return o, O.rkck45(model, P, None if sh is None else np.array(sh), y0 * (1.0 + eps), o)
+    o, a = oracle()
+    keep = np.ones(n, bool)
+    for b in (oracle(f=0.5)[1], oracle(f=2.0)[1], oracle(eps=PERTURB)[1]):
+        keep &= (b.status == a.status) & np.all(b.stats == a.stats, axis=0)
+    keep &= sensitivity_mask([a.y], [b.y], 1e-9, 1e-11)
+    floor = (a.status & O.SYS_DT_MIN) != 0
+    assert keep.mean() >= 0.5 and (floor & keep).any() and (~floor & keep).any()
+    g = gpu_ck(model, P, y0, o, shared=None if sh is None else list(sh), solver=_solver(scheme))
+    assert np.array_equal(g.status[keep], a.status[keep])
+    for k in (O.ST_ACCEPTED, O.ST_REJECTED, O.ST_EVRETRY, O.ST_NRHS, O.ST_PHASES):
+        assert np.array_equal(g.stats[k][keep], a.stats[k][keep]), k
+    assert np.all(g.stats[O.ST_REJECTED] == 0)
+    assert np.all(per_system(close(g.y, a.y, CK_RTOL, CK_ATOL))[keep])
