@@ -44,6 +44,8 @@ typedef __bf16 bf16;
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
+// four floats of a caller's array, aligned as its floats are
+typedef f32x4 __attribute__((aligned(4))) f32x4_of_floats;
 
 constexpr int kIn = SUR_IN, kH = SUR_HIDDEN, kOut = SUR_OUT;
 // packed parameter offsets: W1, b1, W2, b2, W3, b3, W4, b4
@@ -856,7 +858,7 @@ __global__ __launch_bounds__(64 * kDsWaves, 2) void k_dataset(DatasetArgs a) {
   const int c = a.few ? kGrp * w + 4 * (l & 3) : 4 * (l & 15);
   const int step = a.few ? 16 : 4;
   for (int r = a.few ? l >> 2 : l >> 4; r < 64 && i0 + r < a.n; r += step)
-    *(f32x4 *)(a.y + (i0 + r) * kOut + c) = *(const f32x4 *)&rows[w][r][c];
+    *(f32x4_of_floats *)(a.y + (i0 + r) * kOut + c) = *(const f32x4 *)&rows[w][r][c];
 }
 
 // Count, mean and sum of squares about the mean of two sets together (Chan,
@@ -1177,7 +1179,7 @@ __global__ __launch_bounds__(64 * 16 / NF, 4) void k_net(FusedArgs a) {
       o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[c][0], act[0][c][j][l], o, 0, 0, 0);
     if (!SCREEN) {
       const int64_t r = r0 + 16 * j + i;
-      if (r < a.n) *(f32x4 *)(a.out + r * kOut + 16 * ob + 4 * g) = o;
+      if (r < a.n) *(f32x4_of_floats *)(a.out + r * kOut + 16 * ob + 4 * g) = o;
     } else {
       // de-standardised maximum and minimum over the wave's 16 outputs: 4 in
       // the lane, then across the four lane groups

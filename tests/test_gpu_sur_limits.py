@@ -189,3 +189,31 @@ def test_train_epochs_scratch_of_orders_made_one_at_a_time():
     print(f"{(free - least[0]) / n:.2f} bytes a row")
     assert np.all(np.isfinite(losses))
     assert 40 * n < free - least[0] < 48 * n
+
+
+@pytest.mark.parametrize("n", [1, 65, 16385])
+def test_outputs_at_any_float_address(n):
+    """Targets and network outputs need the alignment of a float only."""
+    import torch
+    sur = _sur()
+    rng = np.random.default_rng(n)
+    rd = torch.from_numpy(np.exp(rng.normal(size=(64, n)))).cuda()
+    pd = torch.from_numpy(rng.uniform(0.5, 1.5, (2, n))).cuda()
+    C = sur.ens.C
+    with sur.Surrogate(max_batch=64) as s:
+        s.set_norm([0.5, -1.0], [1.5, 1.0], np.zeros(64), np.ones(64))
+        s.set_params(I.mlp_init(7))
+        x, y = s.build_dataset(pd, rd, n)
+        out = s.forward(x)
+        for shift in (1, 2, 3):
+            buf = torch.full((n * 64 + 4,), -7.0, device="cuda")
+            at = buf.data_ptr() + 4 * shift
+            sur._check(sur._lib().sur_build_dataset(s.h, C.c_void_p(pd.data_ptr()),
+                                                    C.c_void_p(rd.data_ptr()), n,
+                                                    C.c_void_p(x.data_ptr()), C.c_void_p(at)), s.h)
+            assert torch.equal(buf[shift:shift + n * 64].reshape(n, 64), y)
+            assert torch.all(buf[:shift] == -7.0) and torch.all(buf[shift + n * 64:] == -7.0)
+            sur._check(sur._lib().sur_forward(s.h, C.c_void_p(x.data_ptr()), n, C.c_void_p(at),
+                                              sur.ens.ENS_DEVICE), s.h)
+            assert torch.equal(buf[shift:shift + n * 64].reshape(n, 64), out)
+            assert torch.all(buf[:shift] == -7.0) and torch.all(buf[shift + n * 64:] == -7.0)
