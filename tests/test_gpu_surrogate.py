@@ -572,3 +572,18 @@ def test_epoch_orders_made_in_groups(n, epochs):
             single.append(loss.value)
         assert np.array_equal(multi, s.get_params())
     assert np.array_equal(np.asarray(losses, np.float32), np.asarray(single, np.float32))
+
+
+@pytest.mark.parametrize("m", [15, 16, 17, 4095, 4096, 4097, 8191, 8192, 8193, 8257])
+def test_forward_at_tile_edges_matches_oracle(m):
+    """Around one tile of 16 points and around the changes from 16 to 32 to 64
+    points a block: the last 80 points (a ragged tile and whole ones before
+    it) against the oracle, tolerances as above."""
+    sur = _sur()
+    flat = _f32_params(9)
+    x, _ = _data(m, 8)
+    with sur.Surrogate(max_batch=64) as s:
+        s.set_params(flat)
+        out = s.forward(x)
+    ref, _ = M.forward(M.unpack(flat), x[-80:].astype(np.float64), bf16=True)
+    _close(out[-80:], ref, f"output m={m}")
