@@ -107,8 +107,8 @@ int sur_build_dataset(sur_t s, const double *params, const double *records, int6
  * out_std (host, SUR_OUT doubles each, may be NULL).  A spread of 0 or a
  * non-finite one is refused; a rank that is the same at every point has the
  * spread that the rounding of its sums leaves, 0 or about 1e-16.  The
- * partial moments live in handle-owned scratch (6 bytes a point, grown as
- * needed). */
+ * partial moments live in handle-owned scratch, grown as needed: 24 bytes a
+ * point up to 16384 points, 6 above (1536 bytes for every 64 or 256 points). */
 int sur_fit_norm(sur_t s, const double *in_lo, const double *in_hi, const double *records,
                  int64_t n, double *out_mean, double *out_std);
 
@@ -152,8 +152,8 @@ int sur_gradients(sur_t s, const float *x, const float *target, int64_t m, float
                   float *loss, int32_t where);
 
 /* Network output (standardised) for m inputs x [m][2] -> out [m][SUR_OUT].
- * One launch of the fused inference kernel (every layer; one for every 2^28
- * points) for device arrays; host arrays pass through the handle's staging
+ * One launch of the fused inference kernel (every layer, 16, 32 or 64 points
+ * per block by their number; one launch for every 2^28) for device arrays; host arrays pass through the handle's staging
  * buffers 65,536 rows at a time.  m may be any size >= 0. */
 int sur_forward(sur_t s, const float *x, int64_t m, float *out, int32_t where);
 

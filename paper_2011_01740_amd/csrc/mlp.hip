@@ -717,7 +717,8 @@ __device__ __forceinline__ void sorted_records(const double *__restrict__ rec, i
         }
 }
 
-// ln x for finite normal x > 0.  x = 2^e m with m in [1/2, 1); the top 7 bits
+// ln x for finite normal x > 0, from a table and a short series (the method of
+// Tang, 1990).  x = 2^e m with m in [1/2, 1); the top 7 bits
 // of m's fraction choose a table entry with inv ~ 1 / m of few bits, and
 //     ln x = k ln 2 + L + log1p(f),   f = m inv - 1,  |f| <= 2^-7,
 // k = e with L = -ln inv for the upper part of the interval, and k = e - 1
@@ -1033,8 +1034,7 @@ __global__ __launch_bounds__(256) void k_rounding_spread(const double *__restric
 
 struct FusedArgs {
   int64_t n;                       // points
-  const double *prm;               // screen: sweep parameters [2][ldp] (p_A, f)
-  int64_t ldp;
+  const double *prm;               // screen: sweep parameters [2][n] (p_A, f)
   double lo0, sc0, lo1, sc1;       //   and their normalisation
   const float *x;                  // forward: normalised inputs [n][2]
   float *out;                      // forward: network outputs [n][64]
@@ -1048,6 +1048,7 @@ struct FusedArgs {
   int8_t *label;
   uint8_t *resolve;
   float *pmax;
+  int64_t first;                   // the launch's first point
 };
 
 // Label and re-solve mask of point r from its predicted maximum and minimum
@@ -1086,14 +1087,14 @@ __global__ __launch_bounds__(64 * 16 / NF, 4) void k_net(FusedArgs a) {
   __shared__ float red[2][kOut / 16][NP];   // maxima and minima over 16 outputs
   const int t = threadIdx.x, l = t & 63, g = l >> 4, i = l & 15;
   const int w = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int64_t r0 = (int64_t)blockIdx.x * NP;
+  const int64_t r0 = a.first + (int64_t)blockIdx.x * NP;
   const float *__restrict__ P = a.P;
   const int half = NF == 1 ? w & 1 : 0, chunk = NF * w >> 1;
   if (t < NP) {
     const int64_t r = r0 + t < a.n ? r0 + t : a.n - 1;
     if (SCREEN) {
       xs[t][0] = (float)(fma(a.prm[r] - a.lo0, a.sc0, -1.0));
-      xs[t][1] = (float)(fma(log(a.prm[a.ldp + r]) - a.lo1, a.sc1, -1.0));
+      xs[t][1] = (float)(fma(log(a.prm[a.n + r]) - a.lo1, a.sc1, -1.0));
     } else {
       xs[t][0] = a.x[2 * r];
       xs[t][1] = a.x[2 * r + 1];
@@ -1477,14 +1478,16 @@ hipError_t reserve_scan(sur_ctx *s, int64_t n) {
 // k_net<4, 2> takes 8 a point.
 constexpr int64_t kNetPoints = 1 << 28;
 static_assert(kNetPoints * 8 <= UINT32_MAX && kNetPoints % 64 == 0, "threads of a launch");
-hipError_t fused_launch(hipStream_t st, const FusedArgs &a, bool screen) {
-  // few points: one tile per CU (256 of them) while that can be had
-  const dim3 g1(nblk(a.n, 16)), g2(nblk(a.n, 32)), g4(nblk(a.n, 64));
+hipError_t fused_launch(hipStream_t st, const FusedArgs &a, int64_t count, bool screen) {
+  // few points: one tile per CU (256 of them) while that can be had (a screen
+  // takes 64 points a block at any size: the smaller tiles have been measured
+  // for the forward only)
+  const dim3 g1(nblk(count, 16)), g2(nblk(count, 32)), g4(nblk(count, 64));
   if (screen)
     hipLaunchKernelGGL((k_net<4, 2, true>), g4, dim3(512), 0, st, a);
-  else if (a.n <= 16 * 256)
+  else if (count <= 16 * 256)
     hipLaunchKernelGGL((k_net<1, 1, false>), g1, dim3(1024), 0, st, a);
-  else if (a.n <= 32 * 256)
+  else if (count <= 32 * 256)
     hipLaunchKernelGGL((k_net<2, 1, false>), g2, dim3(1024), 0, st, a);
   else
     hipLaunchKernelGGL((k_net<4, 2, false>), g4, dim3(512), 0, st, a);
@@ -1495,21 +1498,10 @@ hipError_t fused(sur_ctx *s, FusedArgs a, bool screen) {
   a.W2f = s->W.W2;
   a.W3f = s->W.W3p;
   a.W4f = s->W.W4p;
-  const int64_t n = a.n;
-  for (int64_t first = 0;; first += kNetPoints) {
-    a.n = n - first < kNetPoints ? n - first : kNetPoints;
-    const hipError_t e = fused_launch(s->stream, a, screen);
-    if (e != hipSuccess || first + a.n == n) return e;
-    if (screen) {
-      a.prm += kNetPoints;
-      if (a.label) a.label += kNetPoints;
-      if (a.resolve) a.resolve += kNetPoints;
-      if (a.pmax) a.pmax += kNetPoints;
-    } else {
-      a.x += kNetPoints * kIn;
-      a.out += kNetPoints * kOut;
-    }
-  }
+  hipError_t e = hipSuccess;
+  for (a.first = 0; a.first < a.n && e == hipSuccess; a.first += kNetPoints)
+    e = fused_launch(s->stream, a, a.n - a.first < kNetPoints ? a.n - a.first : kNetPoints, screen);
+  return e;
 }
 
 // The source of a step's Adam constants: hyper-parameters from device memory
@@ -1993,7 +1985,6 @@ int sur_screen(sur_t s, const double *params, int64_t n, const sur_screen_opts *
   std::memset(&a, 0, sizeof(a));
   a.n = n;
   a.prm = params;
-  a.ldp = n;
   a.lo0 = s->in_lo[0];
   a.sc0 = sc0;
   a.lo1 = s->in_lo[1];

@@ -1331,9 +1331,11 @@ __device__ __forceinline__ bool settle_valve(const RkckArgs &a, ColdArgs &ca, MP
 // a CU, and their waves its SIMDs) and wave w of the block.  In index order the
 // four waves of a block take places a quarter of the round apart, so that
 // whichever SIMD each is on, the CU's SIMDs get alike parts of a parameter
-// grid's fast axis, and each round is turned by 99 blocks (3 modulo 8) against
-// the one before, so that the waves that share a SIMD do not all get the part
-// with the longest systems.  In a given order, longest first, every other round
+// grid's fast axis, and each round is turned by 99 blocks against the one
+// before, so that the waves that share a SIMD do not all get the part with the
+// longest systems.  (A turn of 3 modulo 8: 8 waves take a row of a 512 x 512
+// grid, on which it was measured, so a round moves by 3/8 of the fast axis;
+// for other rows it is some turn, not a fitted one.)  In a given order, longest first, every other round
 // runs backwards: the longest share a SIMD with the shortest.
 __device__ __forceinline__ uint32_t place_of_wave(ColdArgs &a) {
   const uint32_t cus = (uint32_t)a.place, wpb = blockDim.x >> 6;
