@@ -15,7 +15,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libens.so")
-SOURCES = ["ens_api.hip", "rk4.hip", "rkck.hip", "mlp.hip", "micro.hip", "noalloc.hip"]
+SOURCES = ["ens_api.hip", "rk4.hip", "rkck.hip", "mlp.hip", "spread.hip", "micro.hip", "noalloc.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = ["--offload-arch=gfx950"]
 FLAGS = [*ARCH, "-O3", "-std=c++17", "-fPIC",

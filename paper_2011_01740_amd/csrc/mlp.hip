@@ -37,6 +37,7 @@
 
 #include "../../include/sur.h"
 #include "ens_internal.h"
+#include "records.h"
 
 namespace {
 
@@ -47,7 +48,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 // four floats of a caller's array, aligned as its floats are
 typedef f32x4 __attribute__((aligned(4))) f32x4_of_floats;
 
-constexpr int kIn = SUR_IN, kH = SUR_HIDDEN, kOut = SUR_OUT;
+using ens::kOut;
+using ens::sorted_records;
+constexpr int kIn = SUR_IN, kH = SUR_HIDDEN;
 // packed parameter offsets: W1, b1, W2, b2, W3, b3, W4, b4
 constexpr int64_t oW1 = 0, ob1 = oW1 + kH * kIn, oW2 = ob1 + kH, ob2 = oW2 + kH * kH,
                   oW3 = ob2 + kH, ob3 = oW3 + kH * kH, oW4 = ob3 + kH, ob4 = oW4 + kOut * kH,
@@ -697,26 +700,6 @@ static_assert(kDsWaves == kGroups, "few points: one group per wave of a block");
 // SIMD (16384 points: k_dataset 11 us, 20 us with all groups in a wave).
 inline bool few_points(int64_t n) { return n <= 64 * 256; }
 
-// Records of point i, sorted (lanes past the last point repeat it).
-__device__ __forceinline__ void sorted_records(const double *__restrict__ rec, int64_t n,
-                                               int64_t i, double (&v)[kOut]) {
-  const double *p = rec + (i < n ? i : n - 1);
-#pragma unroll
-  for (int j = 0; j < kOut; ++j) v[j] = p[j * n];
-#pragma unroll
-  for (int k = 2; k <= kOut; k <<= 1)
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1)
-#pragma unroll
-      for (int l = 0; l < kOut; ++l)
-        if (!(l & j)) {
-          const double a = v[l], b = v[l | j];
-          const bool down = !(l & k);
-          v[l] = down ? fmax(a, b) : fmin(a, b);
-          v[l | j] = down ? fmin(a, b) : fmax(a, b);
-        }
-}
-
 // ln x for finite normal x > 0, from a table and a short series (the method of
 // Tang, 1990).  x = 2^e m with m in [1/2, 1); the top 7 bits
 // of m's fraction choose a table entry with inv ~ 1 / m of few bits, and
@@ -963,43 +946,6 @@ __global__ __launch_bounds__(256) void k_mean_std(const Moments *__restrict__ pa
   if (t == 0) {
     fit[j] = red[0].mean;
     fit[kOut + j] = sqrt(red[0].m2 / red[0].n);
-  }
-}
-
-// The ranks (bits of `ranks`) whose spread is at the rounding of their
-// logarithms, as where every point has the same record: what is then taken for
-// the spread, and whether there is any, is the rounding of the mean, so the order of
-// the sums is part of the result.  It is 256 partial sums of the points t,
-// t + 256, ..., added by a tree, of the logarithms, then of the squared
-// deviations from the rounded mean.  One block per rank.  Rare: every block
-// sorts every point, twice.
-__global__ __launch_bounds__(256) void k_rounding_spread(const double *__restrict__ rec, int64_t n,
-                                                         uint64_t ranks, double *fit) {
-  __shared__ double red[256];
-  const int j = blockIdx.x, t = threadIdx.x;
-  if (!(ranks >> j & 1)) return;
-  double mean = 0.0;
-  for (int pass = 0; pass < 2; ++pass) {
-    double s = 0.0;
-    for (int64_t i = t; i < n; i += 256) {
-      double v[kOut];
-      sorted_records(rec, n, i, v);
-      double x = v[0];
-#pragma unroll
-      for (int l = 1; l < kOut; ++l) x = l == j ? v[l] : x;
-      const double d = log(x) - mean;   // pass 0: the logarithm
-      s = pass == 0 ? s + d : fma(d, d, s);
-    }
-    red[t] = s;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-      if (t < k) red[t] += red[t + k];
-      __syncthreads();
-    }
-    const double total = red[0] / (double)n;
-    __syncthreads();
-    if (pass == 0) mean = total;
-    if (t == 0) fit[pass * kOut + j] = pass == 0 ? total : sqrt(total);
   }
 }
 
@@ -2037,24 +1983,28 @@ int sur_fit_norm(sur_t s, const double *in_lo, const double *in_hi, const double
                      few, s->lntab, s->mom);
   hipLaunchKernelGGL(k_mean_std, dim3(kOut), dim3(256), 0, s->stream, s->mom, nb, s->pin_d);
   SUR_HIP(s, hipGetLastError());
-  const double *m = s->pin, *sd = m + kOut;
   SUR_HIP(s, hipStreamSynchronize(s->stream));
+  double m[kOut], sd[kOut];
+  const auto results = [&] {
+    std::memcpy(m, s->pin, sizeof(m));
+    std::memcpy(sd, s->pin + kOut, sizeof(sd));
+  };
+  results();
   // spreads within 4 ulp of the logarithms
   uint64_t ranks = 0;
   for (int j = 0; j < kOut; ++j)
-    if (sd[j] <= 0x1p-50 * std::fabs(m[j])) ranks |= (uint64_t)1 << j;
+    ranks |= (uint64_t)(sd[j] <= 0x1p-50 * std::fabs(m[j])) << j;
   if (ranks) {
-    hipLaunchKernelGGL(k_rounding_spread, dim3(kOut), dim3(256), 0, s->stream, records, n, ranks,
-                       s->pin_d);
-    SUR_HIP(s, hipGetLastError());
+    SUR_HIP(s, ens::launch_rounding_spread(records, n, ranks, s->pin_d, s->stream));
     SUR_HIP(s, hipStreamSynchronize(s->stream));
+    results();
   }
   for (int j = 0; j < kOut; ++j)
     if (!(sd[j] > 0.0) || !std::isfinite(m[j]))
       return sfail(s, ENS_E_INVAL, "sur_fit_norm: records give a non-positive or non-finite spread");
   if (int rc = sur_set_norm(s, in_lo, in_hi, m, sd)) return rc;
-  if (out_mean) std::memcpy(out_mean, m, kOut * sizeof(double));
-  if (out_std) std::memcpy(out_std, sd, kOut * sizeof(double));
+  if (out_mean) std::memcpy(out_mean, m, sizeof(m));
+  if (out_std) std::memcpy(out_std, sd, sizeof(sd));
   return ENS_OK;
 }
 
