@@ -680,7 +680,7 @@ __global__ void k_refresh(const float *__restrict__ P, WeightCopies W) {
 // contiguous each, and the bitonic network (672 exchanges) runs in registers.
 //
 // 262144 points (134 MB of records in, 67 MB of targets out; 28 and 42 us at
-// the 4.8 TB/s of a copy): k_moments 65 us, k_dataset 54 us, bound by the
+// the 4.8 TB/s of a copy): k_moments 68 us, k_dataset 57 us, bound by the
 // instructions of the network and the logarithms at 2 waves per SIMD.  Before,
 // a kernel with one wave per point sorted (249 us, 64 lines to a load) and
 // wrote the records out again, twice, and one block per output took all
