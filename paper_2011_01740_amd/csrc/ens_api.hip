@@ -778,10 +778,6 @@ static int solve_rkck(ens_t h, const ens_solve_opts *o) {
   const int cap = ens::rkck_max_blocks(kmodel, h->solver, o->locate_max != 0, block);
   if (cap <= 0) return fail(h, ENS_E_HIP, "ens_solve: occupancy query failed");
   if (grid > cap) return fail(h, ENS_E_INVAL, "ens_solve: grid above resident capacity");
-  ens::RkckArgs a;
-  std::memset(&a, 0, sizeof(a));  // padding too: the struct is compared bytewise
-  a.prioritize = std::getenv("ENS_NO_PRIORITY") ? 0 : 1;
-  ens::rkck_plan(cap, block, h->n, o->spread, h->use_order, &grid, &a);
 
   // records
   const int64_t R = o->n_record;
@@ -795,6 +791,7 @@ static int solve_rkck(ens_t h, const ens_solve_opts *o) {
   }
   // sub-ensemble descriptors: upload only when they change
   std::vector<EnsDesc> desc(h->n_ens);
+  int64_t phases = 0;   // most phases of a system
   for (int e = 0; e < h->n_ens; ++e) {
     std::memset(&desc[e], 0, sizeof(EnsDesc));
     for (int i = 0; i < ENS_MAX_SHARED; ++i) desc[e].shared[i] = h->shared[e][i];
@@ -808,7 +805,12 @@ static int solve_rkck(ens_t h, const ens_solve_opts *o) {
           (desc[e].max_impacts == 0 || desc[e].max_impacts > h->trial_cap))
         desc[e].max_impacts = h->trial_cap;
     }
+    if (desc[e].n_phases > phases) phases = desc[e].n_phases;
   }
+  ens::RkckArgs a;
+  std::memset(&a, 0, sizeof(a));  // padding too: the struct is compared bytewise
+  a.prioritize = std::getenv("ENS_NO_PRIORITY") ? 0 : 1;
+  ens::rkck_plan(cap, block, h->n, phases, o->spread, h->use_order, &grid, &a);
   if (desc.size() != h->desc_dev_copy.size() ||
       std::memcmp(desc.data(), h->desc_dev_copy.data(), desc.size() * sizeof(EnsDesc))) {
     ENS_HIP(h, hipMemcpyAsync(h->d_desc, desc.data(), desc.size() * sizeof(EnsDesc),

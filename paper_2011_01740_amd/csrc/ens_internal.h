@@ -66,7 +66,7 @@ struct RkckArgs {
   int64_t max_steps;
   int32_t max_event_iter;
   int32_t prioritize;       // waves raise their issue priority by remaining work
-                            // (rkck_plan clears it where no two waves share a SIMD)
+                            // (rkck_plan clears it where that does not pay)
   int32_t locate_max;       // Keller--Miksis: maxima located on the step interpolant
 };
 
@@ -115,10 +115,11 @@ hipError_t launch_rkck(int model, int solver, int block, int grid, const RkckArg
 // Resident-wave capacity of the persistent kernel for this model, solver and block.
 int rkck_max_blocks(int model, int solver, bool locate_max, int block);
 // The grid (if *grid is not given: at most `cap`) and how the waves share n
-// systems out, the first `spread` of them at the head of the queue (the
-// share_*, place, taken and ordered fields of *a).
-void rkck_plan(int cap, int block, int64_t n, int64_t spread, bool order, int *grid,
-               RkckArgs *a);
+// systems of at most `phases` phases out, the first `spread` of them at the
+// head of the queue (the share_*, place, taken and ordered fields of *a);
+// clears a->prioritize where priority levels do not pay.
+void rkck_plan(int cap, int block, int64_t n, int64_t phases, int64_t spread, bool order,
+               int *grid, RkckArgs *a);
 hipError_t launch_fill_f64(double *p, double v, int64_t count, hipStream_t s);
 hipError_t launch_fill_u64(unsigned long long *p, unsigned long long v, int64_t count,
                            hipStream_t s);

@@ -119,6 +119,7 @@ extern "C" int ens_solve_noalloc(const ens_noalloc_args *a, const ens_solve_opts
     off[1] = n;
   }
   double shared[ENS_MAX_ENSEMBLES][ENS_MAX_SHARED] = {};
+  int64_t phases = 0;   // most phases of a system
   DescPack pk;
   std::memset(&pk, 0, sizeof(pk));
   for (int e = 0; e < a->n_ensembles; ++e) {
@@ -140,6 +141,7 @@ extern "C" int ens_solve_noalloc(const ens_noalloc_args *a, const ens_solve_opts
       return fail(ENS_E_INVAL, "ens_solve_noalloc: bad budget");
     d.n_phases = ph >= 0 ? ph : o->n_phases;
     d.max_impacts = a->model == ENS_PRV ? imp : 0;
+    if (d.n_phases > phases) phases = d.n_phases;
   }
   int block = o->block ? o->block : 256;
   const int refill = o->refill ? o->refill : 1;
@@ -201,7 +203,7 @@ extern "C" int ens_solve_noalloc(const ens_noalloc_args *a, const ens_solve_opts
   ka.n_ens = a->n_ensembles;
   ka.refill = refill;
   ka.prioritize = std::getenv("ENS_NO_PRIORITY") ? 0 : 1;
-  ens::rkck_plan(cap, block, n, o->spread, a->order != nullptr, &grid, &ka);
+  ens::rkck_plan(cap, block, n, phases, o->spread, a->order != nullptr, &grid, &ka);
   ka.t_phase = o->t_phase;
   ka.dt_min = o->dt_min;
   ka.dt_max = o->dt_max;

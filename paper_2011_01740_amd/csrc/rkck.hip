@@ -1734,8 +1734,8 @@ hipError_t launch_rkck(int model, int solver, int block, int grid, const RkckArg
 // 16 cycles in index order, four waves to a SIMD: 95 to 104 ms by arrival,
 // 61.4 ms by place.  The queue then holds what is left.  Not with a head, which has its own
 // rule, nor on a grid that is no whole number of rounds of the chip.
-void rkck_plan(int cap, int block, int64_t n, int64_t spread, bool order, int *grid,
-               RkckArgs *a) {
+void rkck_plan(int cap, int block, int64_t n, int64_t phases, int64_t spread, bool order,
+               int *grid, RkckArgs *a) {
   const int wpb = block / 64, cus = cu_count(), simds = 4 * cus;
   if (*grid <= 0) {
     const int64_t one = simds > 0 ? (simds + wpb - 1) / wpb : cap;   // blocks: a wave per SIMD
@@ -1757,6 +1757,15 @@ void rkck_plan(int cap, int block, int64_t n, int64_t spread, bool order, int *g
   // waves that have a SIMD each have nobody to go before (48 phases of 512 x
   // 512 systems on one wave per SIMD: 125.4 -> 124.5 ms without the levels)
   if (waves <= simds) a->prioritize = 0;
+  // Nor do levels pay in a launch of few phases with more systems than lanes.  A
+  // phase is the least that tells long systems from short ones; where it is half
+  // or a fifth of a system, waves that have just refilled, of unknown length,
+  // hold up those with little left.  Keller--Miksis, rtol = atol = 1e-10, with
+  // levels and without: 2 phases of 512 x 800 systems 15.5 and 15.3 ms (general
+  // arithmetic 44.8 and 38.0), of 640 x 640 17.6 and 14.9 ms (45.9 and 41.8); 5
+  // phases of 512 x 800, general arithmetic, 119 and 99 ms.  With 7 or 16 phases
+  // they gain as often as they lose.
+  if (phases <= 5 && n > 64 * waves) a->prioritize = 0;
 }
 
 int rkck_max_blocks(int model, int solver, bool locate_max, int block) {
