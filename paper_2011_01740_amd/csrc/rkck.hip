@@ -1738,7 +1738,11 @@ void rkck_plan(int cap, int block, int64_t n, int64_t phases, int64_t spread, bo
                int *grid, RkckArgs *a) {
   const int wpb = block / 64, cus = cu_count(), simds = 4 * cus;
   if (*grid <= 0) {
-    const int64_t one = simds > 0 ? (simds + wpb - 1) / wpb : cap;   // blocks: a wave per SIMD
+    // blocks: a wave for each of the 4 SIMDs of a CU, the same number on every
+    // CU (block 192: 512 of them; 342, a wave per SIMD in all, left two waves to
+    // some SIMDs: 5000 Lorenz systems 254 and 305 us, 20000 Keller--Miksis ones
+    // 2.2 and 2.9 ms)
+    const int64_t one = cus > 0 ? (int64_t)cus * ((4 + wpb - 1) / wpb) : cap;
     const int64_t rounds = (n + one * block - 1) / (one * block);
     const int64_t want = one * (rounds > 0 ? rounds : 1);
     *grid = want < cap ? (int)want : cap;

@@ -55,3 +55,13 @@ def test_share_of_the_head(n, spread, launch):
     o = O.Opts(n_phases=2, n_record=2, rtol=1e-6, atol=1e-6)
     ref = gpu_ck(3, P, y0, o, block=256, grid=256, budgets=[(2, 3)])
     _same(gpu_ck(3, P, y0, o, spread=spread, budgets=[(2, 3)], **launch), ref)
+
+
+@pytest.mark.parametrize("block", [64, 128, 192, 256])
+@pytest.mark.parametrize("n", [1, 5000, 70000, 400000])
+def test_default_grid_gives_every_cu_the_same_blocks(n, block):
+    import torch
+    P, y0 = I.quad_linspace(n)
+    g = gpu_ck(0, P, y0, O.Opts(n_phases=1, n_record=1, rtol=1e-6, atol=1e-6), block=block)
+    assert g.launch["block"] == block
+    assert g.launch["grid"] % torch.cuda.get_device_properties(0).multi_processor_count == 0
