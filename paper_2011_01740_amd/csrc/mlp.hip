@@ -1990,11 +1990,11 @@ int sur_fit_norm(sur_t s, const double *in_lo, const double *in_hi, const double
     std::memcpy(sd, s->pin + kOut, sizeof(sd));
   };
   results();
-  // spreads within 4 ulp of the logarithms
+  // spreads within 4 ulp of the logarithms (one point has none)
   uint64_t ranks = 0;
   for (int j = 0; j < kOut; ++j)
     ranks |= (uint64_t)(sd[j] <= 0x1p-50 * std::fabs(m[j])) << j;
-  if (ranks) {
+  if (ranks && n > 1) {
     SUR_HIP(s, ens::launch_rounding_spread(records, n, ranks, s->pin_d, s->stream));
     SUR_HIP(s, hipStreamSynchronize(s->stream));
     results();
