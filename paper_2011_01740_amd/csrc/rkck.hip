@@ -1761,15 +1761,17 @@ void rkck_plan(int cap, int block, int64_t n, int64_t phases, int64_t spread, bo
   // waves that have a SIMD each have nobody to go before (48 phases of 512 x
   // 512 systems on one wave per SIMD: 125.4 -> 124.5 ms without the levels)
   if (waves <= simds) a->prioritize = 0;
-  // Nor do levels pay in a launch of few phases with more systems than lanes.  A
-  // phase is the least that tells long systems from short ones; where it is half
-  // or a fifth of a system, waves that have just refilled, of unknown length,
-  // hold up those with little left.  Keller--Miksis, rtol = atol = 1e-10, with
-  // levels and without: 2 phases of 512 x 800 systems 15.5 and 15.3 ms (general
-  // arithmetic 44.8 and 38.0), of 640 x 640 17.6 and 14.9 ms (45.9 and 41.8); 5
-  // phases of 512 x 800, general arithmetic, 119 and 99 ms.  With 7 or 16 phases
-  // they gain as often as they lose.
-  if (phases <= 5 && n > 64 * waves) a->prioritize = 0;
+  // Nor do levels pay in a launch of few phases with up to twice as many systems
+  // as lanes.  A phase is the least that tells long systems from short ones;
+  // where it is half or a fifth of a system, waves that have just refilled, of
+  // unknown length, hold up those with little left.  Keller--Miksis, rtol = atol =
+  // 1e-10, with levels and without: 2 phases of 512 x 800 systems 15.5 and 15.3 ms
+  // (general arithmetic 44.8 and 38.0), of 640 x 640 17.6 and 14.9 ms (45.9 and
+  // 41.8); 5 phases of 512 x 800, general arithmetic, 119 and 99 ms.  With 7 or
+  // 16 phases they gain as often as they lose, and so they do with 3 or 4 times
+  // as many systems as lanes (1024 x 1024, 2 phases: 25.7 and 24.5 ms, general
+  // arithmetic 62.3 and 63.4).
+  if (phases <= 5 && n > 64 * waves && n <= 128 * waves) a->prioritize = 0;
 }
 
 int rkck_max_blocks(int model, int solver, bool locate_max, int block) {
